@@ -18,12 +18,13 @@
 //
 // Pipeline.  NS-1 slabs are in flight from global memory while one is computed: measured on
 // MI355X a 64 KB slab takes about 1.4 us from issue to landing, as long as its MFMA work, so
-// a single slab in flight leaves the matrix cores waiting.  Operand fragments are double
-// buffered in registers: while the MFMAs of k-step kk run, the fragments of kk+1 are read
-// from LDS.  The one barrier per slab sits before the slab's last k-step: by then every wave
-// holds the slab's last fragments in registers, so the slab's stage is free for the loads of
+// a single slab in flight leaves the matrix cores waiting.  In the 2- and 4-wave tiles operand
+// fragments are double buffered in registers: while the MFMAs of k-step kk run, the fragments of
+// kk+1 are read from LDS.  The one barrier per slab sits before the slab's last k-step: by then every
+// wave holds the slab's last fragments in registers, so the slab's stage is free for the loads of
 // slab+NS, and the next slab becomes visible, so the last k-step already prefetches the next
-// slab's first fragments.
+// slab's first fragments.  The 8-wave tiles alternate instead: four waves multiply while the other
+// four read and load (SCHED 4 and 5 below).
 //
 // Several problems (for example the text and the image stream of one joint block, which
 // have different weights) are launched as one grid.  Workgroup ids are first de-interleaved
@@ -145,9 +146,11 @@ __device__ __forceinline__ void tile_coords(const GemmProblem& P, int t, int& tm
 // 64-bit lane addresses (measured +2..7 %, convolutions +2.5 %).
 // SCHED: how the loop is laid out.
 //   2  k-steps of a slab in order, the barrier after the last fragment read
-//   3  the loop rotated: an iteration starts right after the barrier with the LAST k-step of a
-//      slab, so its first MFMAs wait for no LDS read (measured 0..+3 % on the 8-wave 256x256 tile, not on
-//      the 4-wave 128x128 one)
+//   4  two groups of waves half a phase apart, two phases per slab (256- and 320-row tiles, 8 waves)
+//   5  two groups, one phase per slab (256x128 tile, 8 waves)
+//      Forms 4 and 5 multiply with v_mfma_f32_16x16x32_bf16: the same cycles per flop as 32x32x16, but these
+//      kernels keep the matrix cores 90 % busy and the board then lowers its clock to what it can feed, and per
+//      flop the 16x16 form draws less (8192^3: 768 us with 32x32x16, 705 us with 16x16x32, nothing else changed).
 template <int BM, int BN, int WM, int WN, int BKT, int NS, int MODE, bool CONV = false, int SCHED = 2>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batch) {
   constexpr int NT = WM * WN * 64;
@@ -182,6 +185,21 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
 
+  // One load of a wave fills RPL slab rows.  Form 4 fetches A in two parts, the first 64 rows of every
+  // wave's sub-tile and the rest; row_a: first of the rows that the wave's i-th load of A fills.
+  constexpr int RPL = 64 / CPR;
+  constexpr int LAU = SCHED == 4 ? WM * 64 * CPR / NT : LA;
+  auto row_a = [&](int i) {
+    if constexpr (SCHED == 4) {
+      const bool up = i < LAU;
+      const int per = up ? 64 : TM * 32 - 64;
+      const int rr = ((up ? i : i - LAU) * (WM * WN) + wave) * RPL;
+      return rr / per * (TM * 32) + rr % per + (up ? 0 : 64);
+    } else {
+      return (i * (WM * WN) + wave) * RPL;
+    }
+  };
+
   // ---- per-thread global source offsets ------------------------------------------------
   // (element offsets from the matrix base; every operand is far below 2^31 elements)
   uint32_t ga[LA], gb[LB];
@@ -194,7 +212,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   }
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
-    int q = i * NT + tid, r = q / CPR, pc = q % CPR, c = pc ^ swz_key<BKT>(r);
+    const int r = row_a(i) + lane / CPR, pc = lane % CPR, c = pc ^ swz_key<BKT>(r);
     int m = m0 + r; if (m >= P.M) m = P.M - 1;            // clamp: rows past M are never stored
     if constexpr (CONV) {    // top-left pixel of the 3x3 window in the stack of bordered images
       const int b = m / P.conv_img, r = m - b * P.conv_img;
@@ -208,18 +226,37 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   }
 #pragma unroll
   for (int i = 0; i < LB; ++i) {
-    int q = i * NT + tid, r = q / CPR, pc = q % CPR, c = pc ^ swz_key<BKT>(r);
+    const int r = (i * (WM * WN) + wave) * RPL + lane / CPR, pc = lane % CPR, c = pc ^ swz_key<BKT>(r);
     gb[i] = (uint32_t)r * (uint32_t)P.ldw + c * 8; // weights are padded to N_pad rows
   }
 
 
-  f32x16 acc[TM][TN];
+  // accumulators: one f32x16 per 32x32 tile, or its four 16x16 quarters (row-major) in forms 4 and 5
+  constexpr bool M16 = SCHED >= 4;
+  f32x16 acc[M16 ? 1 : TM][M16 ? 1 : TN];
+  f32x4 acc4[M16 ? TM : 1][M16 ? TN : 1][4];
+  if constexpr (M16) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        for (int q = 0; q < 4; ++q) acc4[i][j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  } else {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  }
+  // element e of tile (i, j) and its place in the 32x32 tile
+  auto acc_at = [&](int i, int j, int e) -> float {
+    if constexpr (M16) return acc4[i][j][e >> 2][e & 3];
+    else return acc[i][j][e];
+  };
+  auto acc_row = [&](int e) { return M16 ? 16 * (e >> 3) + 4 * (lane >> 4) + (e & 3) : 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); };
+  auto acc_col = [&](int e) { return M16 ? 16 * ((e >> 2) & 1) + (lane & 15) : lane & 31; };
 
   int nk = P.K / BKT;
   if (MODE == 4) {              // my share of the slabs (shares differ by at most one slab)
@@ -238,10 +275,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   const int akey = swz_key<BKT>(arow), bkey = swz_key<BKT>(brow);
   const int abase = arow * ROWB, bbase = OFFB + brow * ROWB;
 
-  // chunk q = i*NT + tid lands at LDS byte q*16 = (i*NT + wave*64)*16 + lane*16.  Slab indices
+  // A load's lanes land at LDS byte row*ROWB + lane*16 of their slab (row: its first).  Slab indices
   // past the end are clamped (the copy is redundant but keeps the load count per slab fixed,
   // which the vmcnt arithmetic below relies on).
-  auto issue = [&](int kt) {
+  auto issue_a = [&](int kt, auto first, auto last) {      // loads [first, last) of slab kt of A
     unsigned char* dA = smem + (kt % NS) * STAGE;
     const int ks = (kt < nk ? kt : nk - 1) * BKT;
     int ka = ks;             // A-side offset of the slab
@@ -253,12 +290,20 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
       const int ky = tap / 3, kx = tap - 3 * ky;
       ka = ((kf * (P.conv_img / P.conv_w + 2) + ky) * (P.conv_w + 2) + kx) * P.conv_cin + c0;
     }
-    unsigned char* dB = dA + OFFB;
 #pragma unroll
-    for (int i = 0; i < LA; ++i) buffer_load_lds16(tileA, (lptr_t)(dA + (i * NT + wave * 64) * 16), ga[i] * 2u, ka * 2);
+    for (int i = decltype(first)::value; i < decltype(last)::value; ++i)
+      buffer_load_lds16(tileA, (lptr_t)(dA + row_a(i) * ROWB), ga[i] * 2u, ka * 2);
+  };
+  auto issue_b = [&](int kt) {
+    unsigned char* dB = smem + (kt % NS) * STAGE + OFFB;
+    const int ks = (kt < nk ? kt : nk - 1) * BKT;
 #pragma unroll
     for (int i = 0; i < LB; ++i) buffer_load_lds16(tileW, (lptr_t)(dB + (i * NT + wave * 64) * 16), gb[i] * 2u, ks * 2);
   };
+  constexpr std::integral_constant<int, 0> A_FIRST{};
+  constexpr std::integral_constant<int, LAU> A_REST{};
+  constexpr std::integral_constant<int, LA> A_END{};
+  auto issue = [&](int kt) { issue_a(kt, A_FIRST, A_END); issue_b(kt); };
   auto load_frags = [&](const unsigned char* st, int kk, bf16x8 (&a)[TM], bf16x8 (&b)[TN]) {
     const int c = kk * 2 + half;
     const unsigned char* pa = st + abase + ((c ^ akey) << 4);
@@ -269,53 +314,112 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
     for (int j = 0; j < TN; ++j) b[j] = *(const bf16x8*)(pb + j * 32 * ROWB);
   };
   auto mfma_all = [&](const bf16x8 (&a)[TM], const bf16x8 (&b)[TN]) {
+    if constexpr (!M16)
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
   };
 
+  if constexpr (M16) {
+    // Two groups of four waves (wave / 4; each has one wave on every SIMD), half a phase apart: while one group's
+    // waves do nothing but multiply, the other's read the fragments of their next product and issue loads, so
+    // the matrix cores change hands at a barrier instead of idling while a wave waits for LDS (8192^3: 839 us with
+    // each wave interleaving reads and products, matrix cores 78 % busy; 768 us this way with the same MFMA form, 91 %).
+    //
+    // A group's reads are in registers before the barrier that ends its reading half, so what it read may be
+    // overwritten by loads of either group from its next phase on.  The wait at the end of a reading half covers
+    // the group's own loads of what the NEXT phase reads; the barriers in between make them visible to the other.
+    static_assert(WM * WN == 8 && BKT == 64 && TN == 2, "two groups of four waves, 64 columns a wave");
+    constexpr int RT = TM * 2, CT = TN * 2;                     // 16-row and 16-column tiles of the sub-tile
+    constexpr int PH = SCHED == 4 ? 2 : 1, RP = RT / PH;        // phases per slab, row tiles per phase
+    constexpr int KS = BKT / 32;
+    const int l16 = lane & 15, kq = lane >> 4;
+    const int fkey = swz_key<BKT>(l16);                         // (rows 16 apart have the same key)
+    const int fa0 = (wm * (BM / WM) + l16) * ROWB, fb0 = OFFB + (wn * (BN / WN) + l16) * ROWB;
+    bf16x8 fa[KS][RP], fb[KS][CT];
+    auto read_a = [&](const unsigned char* st, int phase) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int r = 0; r < RP; ++r)
+          fa[ks][r] = *(const bf16x8*)(st + fa0 + (((ks * 4 + kq) ^ fkey) << 4) + (phase * RP + r) * 16 * ROWB);
+    };
+    auto read_b = [&](const unsigned char* st) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) fb[ks][c] = *(const bf16x8*)(st + fb0 + (((ks * 4 + kq) ^ fkey) << 4) + c * 16 * ROWB);
+    };
+    auto multiply = [&](auto phase) {
+      wg_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int r = 0; r < RP; ++r)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            constexpr int r0 = decltype(phase)::value * RP;
+            f32x4& d = acc4[(r0 + r) >> 1][c >> 1][((r0 + r) & 1) * 2 + (c & 1)];
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[ks][r], fb[ks][c], d, 0, 0, 0);
+          }
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      wg_barrier();
+    };
+    const bool second = wave >= WM * WN / 2;
+    if constexpr (SCHED == 4) {
+      // phase 2kt reads the upper half of A and W of slab kt and issues the rest of A of slab kt+1 (over slab kt-1,
+      // last read one phase ago); phase 2kt+1 reads the lower half of A and issues W and the first part of A of slab kt+2.
+      // Where phase 0 reads none of the rest of A (256 rows), the rest has one phase more to arrive.
+      static_assert(NS == 2 && RP * 16 >= 64, "the first part of A is read in phase 0 alone");
+      constexpr bool LATE = RP * 16 == 64;
+      issue_b(0); issue_a(0, A_FIRST, A_END);
+      issue_b(1); issue_a(1, A_FIRST, A_REST);
+      wait_vm<LB + LAU, false>();
+      wg_barrier();
+      if (second) wg_barrier();
+      for (int kt = 0; kt < nk; ++kt) {
+        const unsigned char* cur = smem + (kt & 1) * STAGE;
+        read_b(cur);
+        read_a(cur, 0);
+        issue_a(kt + 1, A_REST, A_END);
+        wait_vm<LATE ? LPS : 63, true>();      // the rest of A of slab kt (mine; without LATE slab kt is complete already)
+        multiply(std::integral_constant<int, 0>{});
+        read_a(cur, 1);
+        issue_b(kt + 2); issue_a(kt + 2, A_FIRST, A_REST);
+        wait_vm<LATE ? LPS : LB + LAU, true>();// W and the first part of A of slab kt+1 (mine; without LATE all of it)
+        multiply(std::integral_constant<int, PH - 1>{});
+      }
+    } else {
+      // phase kt reads slab kt and issues slab kt+2 into the stage that slab kt-1 left
+      static_assert(NS == 3, "three stages");
+      issue(0); issue(1);
+      wait_vm<LPS, false>();
+      wg_barrier();
+      if (second) wg_barrier();
+      int st = 0;
+      for (int kt = 0; kt < nk; ++kt) {
+        const unsigned char* cur = smem + st * STAGE;
+        read_b(cur);
+        read_a(cur, 0);
+        issue(kt + 2);
+        wait_vm<LPS, true>();                  // slab kt+1 (mine)
+        multiply(std::integral_constant<int, 0>{});
+        st = st + 1 == NS ? 0 : st + 1;
+      }
+    }
+    if (!second) wg_barrier();
+  } else {
   bf16x8 a0[TM], b0[TN], a1[TM], b1[TN];
 #pragma unroll
   for (int sidx = 0; sidx < NS; ++sidx) issue(sidx);
   wait_vm<(NS - 1) * LPS, false>();          // slab 0 has landed (mine)
   wg_barrier();   // ... and everyone's
   load_frags(smem, 0, a0, b0);
-  if constexpr (SCHED == 3) {
-    // Rotated loop: an iteration starts right after the barrier (nothing outstanding on LDS, so its first
-    // MFMAs wait for nothing) with the LAST k-step of slab kt, then runs all but the last k-step of slab kt+1.
-    auto front = [&](const unsigned char* cur) {       // k-steps 0 .. KK-2 of the slab in `cur`; leaves its last fragments in a1/b1
-      load_frags(cur, 1, a1, b1);
-      mfma_all(a0, b0);
-      interleave_hint<TM + TN, TM * TN>();
-      if (KK == 4) {
-        load_frags(cur, 2, a0, b0);
-        mfma_all(a1, b1);
-        interleave_hint<TM + TN, TM * TN>();
-        load_frags(cur, 3, a1, b1);
-        mfma_all(a0, b0);
-        interleave_hint<TM + TN, TM * TN>();
-      }
-    };
-    front(smem);
-    wait_vm<(NS - 2) * LPS, true>();         // slab 1 (mine) and my last fragments of slab 0
-    wg_barrier();
-    int st_cur = 0;
-    for (int kt = 0; kt < nk - 1; ++kt) {
-      const int st_nxt = st_cur + 1 == NS ? 0 : st_cur + 1;
-      const unsigned char* nxt = smem + st_nxt * STAGE;
-      issue(kt + NS);                        // into the stage of slab kt: every wave holds its last fragments
-      load_frags(nxt, 0, a0, b0);
-      mfma_all(a1, b1);
-      interleave_hint<TM + TN, TM * TN>();
-      front(nxt);
-      wait_vm<(NS - 2) * LPS, true>();       // slab kt+2 (mine) has landed; my fragments are in registers
-      wg_barrier();
-      st_cur = st_nxt;
-    }
-    mfma_all(a1, b1);                        // last k-step of the last slab
-  } else {
   int st_cur = 0;                            // stage of slab kt
   for (int kt = 0; kt < nk; ++kt) {
     const unsigned char* cur = smem + st_cur * STAGE;
@@ -362,8 +466,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   }
 
   // ---- epilogue ---------------------------------------------------------------------------
-  // acc[i][j][e] is C[32i + 8*(e/4) + 4*half + e%4][32j + lane%32] of the wave's sub-tile: a lane
-  // holds one column, so direct stores would be 2- or 4-byte pieces.  Each wave therefore turns
+  // acc_at(i, j, e) is C[32i + acc_row(e)][32j + acc_col(e)] of the wave's sub-tile: a lane
+  // holds one or two columns, so direct stores would be 2- or 4-byte pieces.  Each wave therefore turns
   // its sub-tile 32 rows at a time through a private LDS patch (row stride TN*128 + 32 bytes:
   // the two half-waves, 4 rows apart, then fall into disjoint bank halves) and reads it back
   // row-major, 4 (fp32 out) or 8 (bf16 out) consecutive columns per lane: global accesses are
@@ -414,7 +518,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          *(float*)(stg + (8 * (e >> 2) + 4 * half + (e & 3)) * RS + (j * 32 + (lane & 31)) * 4) = acc[i][j][e];
+          *(float*)(stg + acc_row(e) * RS + (j * 32 + acc_col(e)) * 4) = acc_at(i, j, e);
       f32x4 xr[RESID ? NIT : 1], gr[RESID ? NIT : 1];
       // (tiles with 128 or more accumulator registers per lane fetch half a patch at a time)
       constexpr int GRP = (RESID && TM * TN >= 8) ? NIT / 2 : NIT;
@@ -557,7 +661,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
         for (int j = 0; j < TN; ++j)
 #pragma unroll
           for (int e = 0; e < 16; ++e)
-            *(float*)(stg + (8 * (e >> 2) + 4 * half + (e & 3)) * RS + (j * 32 + (lane & 31)) * 4) = acc[i][j][e];
+            *(float*)(stg + acc_row(e) * RS + (j * 32 + acc_col(e)) * 4) = acc_at(i, j, e);
         int drows[4];
         f32x4 rc0[4], rc1[4];
         constexpr int RG = TM * TN >= 10 ? 1 : 4;     // (the 320-row tile has no registers to spare: row by row there;
@@ -642,7 +746,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          *(float*)(stg + (j * 32 + (lane & 31)) * CS + (8 * (e >> 2) + 4 * half + (e & 3)) * 4) = acc[i][j][e];
+          *(float*)(stg + (j * 32 + acc_col(e)) * CS + acc_row(e) * 4) = acc_at(i, j, e);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       const int mb = m0 + wm * (BM / WM) + i * 32;     // first row of the patch
       // whole patch in range, its 32 rows neighbours in the transposed matrix, starting at a multiple of 8:
@@ -930,15 +1034,15 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
     for (int i = 0; i < b.n; ++i)        // whole images of whole rows
       if (b.p[i].conv_img <= 0 || b.p[i].conv_img % b.p[i].conv_w || b.p[i].M % b.p[i].conv_img ||
           (b.p[i].conv_kt != 1 && b.p[i].conv_kt != 3) || b.p[i].K != 9 * b.p[i].conv_kt * b.p[i].conv_cin) return -1;
-    if (tile == 1256256) launch_t<256, 256, 2, 4, 64, 2, 0, true, 3>(s, b);
+    if (tile == 1256256) launch_t<256, 256, 2, 4, 64, 2, 0, true, 4>(s, b);
     else if (tile == 30128128) launch_t<128, 128, 2, 2, 64, 4, 0, true, 2>(s, b);
     else { tile = 128128; launch_t<128, 128, 2, 2, 64, 2, 0, true, 2>(s, b); }
     return tile;
   }
   switch (tile) {
     case 256256: launch_t<256, 256, 2, 2, 64, 2, 0, false, 2>(s, b); break;
-    case 1256256: launch_t<256, 256, 2, 4, 64, 2, 0, false, 3>(s, b); break;
-    case 1320256: launch_t<320, 256, 2, 4, 64, 2, 0, false, 3>(s, b); break;
+    case 1256256: launch_t<256, 256, 2, 4, 64, 2, 0, false, 4>(s, b); break;
+    case 1320256: launch_t<320, 256, 2, 4, 64, 2, 0, false, 4>(s, b); break;
     case 10256256: launch_t<256, 256, 2, 2, 32, 4, 0, false, 2>(s, b); break;
     case 11256256: launch_t<256, 256, 2, 4, 32, 4, 0, false, 2>(s, b); break;
     case 20256256: launch_t<256, 256, 2, 2, 32, 5, 0, false, 2>(s, b); break;
@@ -951,7 +1055,7 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
     case 30064128: launch_t<64, 128, 1, 4, 64, 6, 0, false, 2>(s, b); break;
     case 33128064: launch_t<128, 64, 4, 1, 64, 3, 0, false, 2>(s, b); break;
     case 31256128: launch_t<256, 128, 2, 2, 64, 3, 0, false, 2>(s, b); break;
-    case 32256128: launch_t<256, 128, 4, 2, 64, 3, 0, false, 2>(s, b); break;
+    case 32256128: launch_t<256, 128, 4, 2, 64, 3, 0, false, 5>(s, b); break;
     case 31128256: launch_t<128, 256, 2, 2, 64, 3, 0, false, 2>(s, b); break;
     case 40128128: launch_t<128, 128, 2, 2, 64, 4, 4, false, 2>(s, b); break;
     default: tile = 128128; launch_t<128, 128, 2, 2, 64, 2, 0, false, 2>(s, b); break;

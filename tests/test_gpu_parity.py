@@ -98,6 +98,28 @@ def test_gemm_against_float64_matmul(torch, B, M, N, K, variant):
         assert err.max() <= tol, (kind, err.max())
 
 
+@pytest.mark.parametrize("variant", [1256256, 1320256, 32256128])
+@pytest.mark.parametrize("M", [1, 63, 64, 80, 81, 255, 257, 319, 321])
+def test_gemm_two_group_tiles_at_their_edges(torch, B, M, variant):
+    """The 8-wave tiles whose two groups of waves alternate between reading and multiplying: K of one to
+    five slabs (fewer and more than the ring has stages, odd and even), rows around the parts in which a
+    slab of A is fetched and read (64 and 80 rows of a wave, 256 and 320 of a tile), ragged columns.
+    fp32 outputs of at most 320 products: 1e-5 of the sum of absolute products is far above 320 * 2^-24."""
+    for K, N in ((64, 264), (128, 128), (192, 100), (256, 513), (320, 256)):
+        A, W = rnd(21, "A", (M, K)), rnd(22, "W", (N, K), 0.05)
+        Wp = np.zeros(((N + 255) // 256 * 256, K), np.float32); Wp[:N] = W
+        dA, dW = to_dev_bf16(torch, A), to_dev_bf16(torch, Wp)
+        ldc = (N + 3) // 4 * 4
+        out = torch.full((M, ldc), float("nan"), dtype=torch.float32, device="cuda")
+        st = B.dit_op_gemm_variant(None, dA.data_ptr(), K, dW.data_ptr(), K, None, M, N, K, 1, out.data_ptr(), ldc, variant)
+        assert st == 0, (M, N, K)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert np.isnan(got[:, N:]).all()                  # nothing is written past the last column
+        ref, mag = A.astype(np.float64) @ W.astype(np.float64).T, np.abs(A).astype(np.float64) @ np.abs(W).astype(np.float64).T
+        assert (np.abs(got[:, :N] - ref) <= 1e-5 * mag).all(), (M, N, K)
+
+
 def test_gemm_seeded_random_shapes(torch, B):
     """Sixty seeded shapes (M 1..900, N 1..900, K a multiple of 64 up to 2048), each with a seeded
     output kind (bf16, fp32, GELU, or the gated residual with 1-5 requests whose rows change
