@@ -58,7 +58,7 @@ struct GemmProblem {
   int conv_w = 0, conv_cin = 0, conv_img = 1, conv_kt = 1;
   // convolutions with OUT_F32 / OUT_RESID_F32 only, optional: per column n, the sum and the sum
   // of squares of the stored values over the rows of each (tile row, wave row) pair:
-  // stats[(tile_row * 2 + wave_row)][N][2], rows of a pair = tile height / 2 (gemm_stats_rows)
+  // stats[tile_row * wave_rows + wave_row][N][2], rows of a pair = tile height / wave_rows (gemm_stats_rows)
   float* stats = nullptr;
   int tiles_m, tiles_n, tile_start;                        // filled by the launcher
 };
@@ -71,7 +71,9 @@ struct GemmBatch {
 
 // Launches up to 3 independent problems in one grid.  Returns the tile shape used (BM*1000+BN).
 int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile = 0);
-inline int gemm_stats_rows(int tile_code) { return (tile_code % 1000000) / 1000 / 2; }   // rows per stats chunk
+inline int gemm_stats_rows(int tile_code) {     // rows per stats chunk: two wave rows per tile, four in the 8-wave 256x128 one
+  return tile_code == 32256128 ? 64 : (tile_code % 1000000) / 1000 / 2;
+}
 
 // ---- attention ----------------------------------------------------------------------
 // One block of q_per_tile queries of one segment.  parts == 0: against all keys of the segment.  parts > 0:

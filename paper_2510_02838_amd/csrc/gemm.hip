@@ -985,7 +985,16 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
     int max_n = 0;
     for (int i = 0; i < b.n; ++i)
       if (b.p[i].M > 0 && b.p[i].N > max_n) max_n = b.p[i].N;
-    if (max_n <= 128) tile = 128128;       // half or more of a 256-wide tile would be padding
+    // half or more of a 256-wide tile would be padding; convolutions take the 8-wave 256x128 tile from one round on
+    if (max_n <= 128) {
+      long long t21 = 0;
+      bool all_conv = b.n > 0;
+      for (int i = 0; i < b.n; ++i) {
+        all_conv = all_conv && b.p[i].conv_w > 0;
+        if (b.p[i].M > 0) t21 += (b.p[i].M + 255) / 256;
+      }
+      tile = all_conv && t21 >= 256 ? 32256128 : 128128;
+    }
   }
   if (!tile) {
     long long t256 = 0;
@@ -1035,6 +1044,7 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
       if (b.p[i].conv_img <= 0 || b.p[i].conv_img % b.p[i].conv_w || b.p[i].M % b.p[i].conv_img ||
           (b.p[i].conv_kt != 1 && b.p[i].conv_kt != 3) || b.p[i].K != 9 * b.p[i].conv_kt * b.p[i].conv_cin) return -1;
     if (tile == 1256256) launch_t<256, 256, 2, 4, 64, 2, 0, true, 4>(s, b);
+    else if (tile == 32256128) launch_t<256, 128, 4, 2, 64, 3, 0, true, 5>(s, b);
     else if (tile == 30128128) launch_t<128, 128, 2, 2, 64, 4, 0, true, 2>(s, b);
     else { tile = 128128; launch_t<128, 128, 2, 2, 64, 2, 0, true, 2>(s, b); }
     return tile;
