@@ -242,7 +242,7 @@ void launch_latent_update(hipStream_t s, float* x, const float* v, long long n, 
 // for a table of matrices W_j that share x: the conditioning vectors of a few (step, request) rows against
 // the timestep MLP and the modulation matrices of every block (1.4 GB of weights at hidden 1536, read once).
 // Grid (column groups, matrix).  A workgroup stages f(x) for up to MR rows in LDS once (SiLU included) and
-// owns 32 columns, 8 per wave; a lane reads 16 bytes of a weight row per pass over K and the matching two
+// owns 128 (or 32) columns, 32 (or 8) per wave; a lane reads 16 bytes of a weight row per pass over K and the matching two
 // 16-byte pieces of every staged row (even and odd pieces are kept in separate halves of the staged row, so
 // that the lanes of a wave read consecutive LDS addresses).
 // ---------------------------------------------------------------------------------------
@@ -250,39 +250,52 @@ __device__ __forceinline__ float silu_f(float x) { return x / (1.f + __expf(-x))
 
 template <int MR>
 __global__ __launch_bounds__(256) void skinny_kernel(const float* __restrict__ x, int ldx, const SkinnyMat* __restrict__ mats,
-                                                     float* __restrict__ y, int ldy, int M, int K, int silu_in) {
+                                                     float* __restrict__ y, int ldy, int M, int K, int silu_in, int cpw) {
   extern __shared__ __attribute__((aligned(16))) float xs[];          // [MR][K]
   const SkinnyMat mt = mats[blockIdx.y];
-  if ((int)blockIdx.x * 32 >= mt.N) return;
+  if ((int)blockIdx.x * 4 * cpw >= mt.N) return;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n0 = blockIdx.x * 32 + wave * 8;
+  const int n0 = ((int)blockIdx.x * 4 + wave) * cpw;                   // the wave's cpw columns
   const int KH = K >> 1;                                               // floats in the half that holds the even pieces
+  const int nk = (K + 511) >> 9;
+  const int ncol = mt.N - n0 < cpw ? mt.N - n0 : cpw;                  // (may be negative: a wave past the matrix only stages)
+  // four columns at a time: each staged piece is read once for four weight rows
+  auto load_w = [&](int c, int kt, uint4 (&w)[4]) {
+    const int k = kt * 512 + lane * 8, kc = k < K ? k : K - 8;         // (lanes past K read the last piece and do not use it)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n = n0 + c + j;
+      w[j] = *(const uint4*)(mt.W + (size_t)(n < mt.N ? n : mt.N - 1) * mt.ldw + kc);
+    }
+  };
   for (int m0 = 0; m0 < M; m0 += MR) {
     const int rows = M - m0 < MR ? M - m0 : MR;
+    uint4 wn[4];
+    load_w(0, 0, wn);                                                  // the first weights travel while the rows are staged
     __syncthreads();
-    for (int idx = threadIdx.x * 4; idx < rows * K; idx += 1024) {
-      const int r = idx / K, k = idx - r * K, q = k >> 2;
-      float4 v = *(const float4*)(x + (size_t)(m0 + r) * ldx + k);
-      if (silu_in) { v.x = silu_f(v.x); v.y = silu_f(v.y); v.z = silu_f(v.z); v.w = silu_f(v.w); }
-      *(float4*)(xs + r * K + (q & 1) * KH + (q >> 1) * 4) = v;
-    }
+    for (int r = 0; r < rows; ++r)
+      for (int k = threadIdx.x * 4; k < K; k += 1024) {
+        const int q = k >> 2;
+        float4 v = *(const float4*)(x + (size_t)(m0 + r) * ldx + k);
+        if (silu_in) { v.x = silu_f(v.x); v.y = silu_f(v.y); v.z = silu_f(v.z); v.w = silu_f(v.w); }
+        *(float4*)(xs + r * K + (q & 1) * KH + (q >> 1) * 4) = v;
+      }
     __syncthreads();
-    // four columns at a time: each staged piece is read once for four weight rows, and a lane has four
-    // 16-byte weight loads in flight (these products run at memory latency)
-    for (int c = 0; c < 8; c += 4) {
-      if (n0 + c >= mt.N) break;
-      const bf16_t* wr[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wr[j] = mt.W + (size_t)(n0 + c + j < mt.N ? n0 + c + j : mt.N - 1) * mt.ldw;
+    for (int c = 0; c < ncol; c += 4) {
       float acc[MR][4];
 #pragma unroll
       for (int i = 0; i < MR; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-      for (int k = lane * 8; k < K; k += 512) {
+      for (int kt = 0; kt < nk; ++kt) {
         uint4 wraw[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) wraw[j] = *(const uint4*)(wr[j] + k);
+        for (int j = 0; j < 4; ++j) wraw[j] = wn[j];
+        // the next four 16-byte pieces are in flight during this product and the reduction
+        if (kt + 1 < nk) load_w(c, kt + 1, wn);
+        else if (c + 4 < ncol) load_w(c + 4, 0, wn);
+        const int k = kt * 512 + lane * 8;
+        if (k >= K) continue;
         float w[4][8];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -302,15 +315,20 @@ __global__ __launch_bounds__(256) void skinny_kernel(const float* __restrict__ x
           }
         }
       }
+      // Sum over the lanes, four columns at once: two exchanges leave lane l with column l & 3 over its group of
+      // four, four more sum the groups (seven exchanges a row instead of 24).
+      const int n = n0 + c + (lane & 3);
+      const float bias = mt.bias && n < mt.N ? mt.bias[n] : 0.f;
 #pragma unroll
       for (int i = 0; i < MR; ++i) {
         if (i < rows) {
+          const bool b0 = lane & 1, b1 = lane & 2;
+          const float p = (b0 ? acc[i][1] : acc[i][0]) + __shfl_xor(b0 ? acc[i][0] : acc[i][1], 1);
+          const float q = (b0 ? acc[i][3] : acc[i][2]) + __shfl_xor(b0 ? acc[i][2] : acc[i][3], 1);
+          float t = (b1 ? q : p) + __shfl_xor(b1 ? p : q, 2);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float t = wave_sum(acc[i][j]);
-            const int n = n0 + c + j;
-            if (lane == 0 && n < mt.N) y[(size_t)(m0 + i) * ldy + mt.out_off + n] = t + (mt.bias ? mt.bias[n] : 0.f);
-          }
+          for (int o = 4; o < 64; o <<= 1) t += __shfl_xor(t, o);
+          if (lane < 4 && n < mt.N) y[(size_t)(m0 + i) * ldy + mt.out_off + n] = t + bias;
         }
       }
     }
@@ -322,13 +340,16 @@ bool launch_skinny(hipStream_t s, const float* x, int ldx, const SkinnyMat* dev_
                    int ldy, int M, int K, int silu_in) {
   if (M == 0 || n_mats == 0 || max_n == 0) return true;
   if (K % 8 || ldx % 4 || K > 16384) return false;
-  const dim3 g((max_n + 31) / 32, n_mats), b(256);
+  // Columns per wave: 32 from four rows on, where that still leaves four workgroups per CU (every workgroup stages all rows, so more
+  // columns each divide that cost), else 8 (one row: 32 columns measure 1 % of a 256x256 step slower).
+  const int cpw = M >= 4 && (long long)((max_n + 127) / 128) * n_mats >= 1024 ? 32 : 8;
+  const dim3 g((max_n + 4 * cpw - 1) / (4 * cpw), n_mats), b(256);
   // rows staged at a time: as many as 64 KB of LDS hold (fewer rows, less LDS, more workgroups per CU)
   auto lds = [&](int mr) { return (size_t)(M < mr ? M : mr) * K * 4; };
-  if (K <= 2048) hipLaunchKernelGGL(skinny_kernel<8>, g, b, lds(8), s, x, ldx, dev_mats, y, ldy, M, K, silu_in);
-  else if (K <= 4096) hipLaunchKernelGGL(skinny_kernel<4>, g, b, lds(4), s, x, ldx, dev_mats, y, ldy, M, K, silu_in);
-  else if (K <= 8192) hipLaunchKernelGGL(skinny_kernel<2>, g, b, lds(2), s, x, ldx, dev_mats, y, ldy, M, K, silu_in);
-  else hipLaunchKernelGGL(skinny_kernel<1>, g, b, lds(1), s, x, ldx, dev_mats, y, ldy, M, K, silu_in);
+  if (K <= 2048) hipLaunchKernelGGL(skinny_kernel<8>, g, b, lds(8), s, x, ldx, dev_mats, y, ldy, M, K, silu_in, cpw);
+  else if (K <= 4096) hipLaunchKernelGGL(skinny_kernel<4>, g, b, lds(4), s, x, ldx, dev_mats, y, ldy, M, K, silu_in, cpw);
+  else if (K <= 8192) hipLaunchKernelGGL(skinny_kernel<2>, g, b, lds(2), s, x, ldx, dev_mats, y, ldy, M, K, silu_in, cpw);
+  else hipLaunchKernelGGL(skinny_kernel<1>, g, b, lds(1), s, x, ldx, dev_mats, y, ldy, M, K, silu_in, cpw);
   return true;
 }
 

@@ -98,12 +98,13 @@ def test_gemm_against_float64_matmul(torch, B, M, N, K, variant):
         assert err.max() <= tol, (kind, err.max())
 
 
-@pytest.mark.parametrize("variant", [1256256, 1320256, 32256128])
-@pytest.mark.parametrize("M", [1, 63, 64, 80, 81, 255, 257, 319, 321])
+@pytest.mark.parametrize("variant", [1256256, 1320256, 32256128, 30032128, 30064064])
+@pytest.mark.parametrize("M", [1, 31, 33, 63, 64, 80, 81, 255, 257, 319, 321])
 def test_gemm_two_group_tiles_at_their_edges(torch, B, M, variant):
     """The 8-wave tiles whose two groups of waves alternate between reading and multiplying: K of one to
     five slabs (fewer and more than the ring has stages, odd and even), rows around the parts in which a
-    slab of A is fetched and read (64 and 80 rows of a wave, 256 and 320 of a tile), ragged columns.
+    slab of A is fetched and read (64 and 80 rows of a wave, 256 and 320 of a tile), ragged columns; and the
+    two tiles for few rows.
     fp32 outputs of at most 320 products: 1e-5 of the sum of absolute products is far above 320 * 2^-24."""
     for K, N in ((64, 264), (128, 128), (192, 100), (256, 513), (320, 256)):
         A, W = rnd(21, "A", (M, K)), rnd(22, "W", (N, K), 0.05)
@@ -852,6 +853,22 @@ def test_single_token_condition_and_smallest_latent(torch):
     arch = synth.CONFIGS["tiny"]["arch"]
     case = Case(torch, arch, [(1, 2, 2, 1), (1, 2, 4, 1), (1, 4, 2, 3)], 2, std=0.06, bias_std=0.1)
     check_step(case, 0)
+
+
+@pytest.mark.parametrize("n_req", [1, 4, 9])
+def test_conditioning_products_with_32_columns_a_wave(torch, n_req):
+    """48 blocks of the 256-wide model: enough modulation matrices for the form of the small-M product in which
+    a wave owns 32 columns (from four (step, request) rows on; 9 rows are staged in two parts), and the 8-column
+    form for one row, against the float64 oracle (bounds of the per-step tests)."""
+    arch = dict(synth.CONFIGS["tiny"]["arch"], n_blocks=48)
+    reqs = [(1, 8, 8, 5 + r) for r in range(n_req)]
+    c = Case(torch, arch, reqs, 1, shifts=[1.0 + 0.2 * r for r in range(n_req)], std=0.05, bias_std=0.05)
+    xg, vg, _ = c.gpu_step()
+    xo, vo, _ = c.oracle_step()
+    for r in range(n_req):
+        assert rel_l2(vg[r], vo[r]) <= 1e-2, (r, rel_l2(vg[r], vo[r]))
+        assert max_abs(xg[r], xo[r]) <= 2e-2 * max(1.0, np.abs(xo[r]).max()), (r, max_abs(xg[r], xo[r]))
+    c.m.close()
 
 
 def test_many_step_sample_uses_matrix_core_conditioning_path(torch):
