@@ -71,12 +71,44 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
     }
 }
 
+// The same with a workgroup per row, for rows above 1024 columns: a wave that reads 4096 columns alone holds 16
+// loads a lane and starts one after the other behind a single reduction (32 rows of 4096: 12.8 us on 8 workgroups).
+template <int MAXV>
+__global__ __launch_bounds__(256) void rmsnorm_wide_kernel(const float* __restrict__ x, const float* __restrict__ gain,
+                                                           bf16_t* __restrict__ y, float* __restrict__ y32, int M, int d) {
+  __shared__ float part[4];
+  const int row = blockIdx.x, tid = threadIdx.x, n4 = d >> 2;
+  const float4* xr = (const float4*)(x + (size_t)row * d);
+  float4 v[MAXV], g[MAXV];
+  float q = 0.f;
+#pragma unroll
+  for (int i = 0; i < MAXV; ++i)
+    if (i * 256 + tid < n4) { v[i] = xr[i * 256 + tid]; g[i] = ((const float4*)gain)[i * 256 + tid]; }
+#pragma unroll
+  for (int i = 0; i < MAXV; ++i)
+    if (i * 256 + tid < n4) q += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
+  q = e_wave_sum(q);
+  if ((tid & 63) == 0) part[tid >> 6] = q;
+  __syncthreads();
+  const float r = rsqrtf(((part[0] + part[1]) + (part[2] + part[3])) / (float)d + 1e-6f);
+#pragma unroll
+  for (int i = 0; i < MAXV; ++i)
+    if (i * 256 + tid < n4) {
+      const float r0 = v[i].x * r * g[i].x, r1 = v[i].y * r * g[i].y, r2 = v[i].z * r * g[i].z, r3 = v[i].w * r * g[i].w;
+      if (y) {
+        uint2 w;
+        w.x = e_pack2(r0, r1); w.y = e_pack2(r2, r3);
+        ((uint2*)(y + (size_t)row * d))[i * 256 + tid] = w;
+      }
+      if (y32) ((float4*)(y32 + (size_t)row * d))[i * 256 + tid] = make_float4(r0, r1, r2, r3);
+    }
+}
+
 void launch_rmsnorm(hipStream_t s, const float* x, const float* gain, bf16_t* y, float* y32, int M, int d) {
   if (M == 0) return;
-  dim3 g((M + 3) / 4), b(256);
-  if (d <= 1024) hipLaunchKernelGGL(rmsnorm_kernel<4>, g, b, 0, s, x, gain, y, y32, M, d);
-  else if (d <= 4096) hipLaunchKernelGGL(rmsnorm_kernel<16>, g, b, 0, s, x, gain, y, y32, M, d);
-  else hipLaunchKernelGGL(rmsnorm_kernel<32>, g, b, 0, s, x, gain, y, y32, M, d);
+  if (d <= 1024) hipLaunchKernelGGL(rmsnorm_kernel<4>, dim3((M + 3) / 4), dim3(256), 0, s, x, gain, y, y32, M, d);
+  else if (d <= 4096) hipLaunchKernelGGL(rmsnorm_wide_kernel<4>, dim3(M), dim3(256), 0, s, x, gain, y, y32, M, d);
+  else hipLaunchKernelGGL(rmsnorm_wide_kernel<8>, dim3(M), dim3(256), 0, s, x, gain, y, y32, M, d);
 }
 
 // act = gelu_tanh(a) * b   elementwise on bf16, 8 elements per thread
