@@ -233,7 +233,7 @@ struct Fwd {
     const bool want = sums && (kind == OUT_F32 || kind == OUT_RESID_F32);   // a group norm reads `out` next
     if (want) p.stats = at<float>(L.gnp);
     const int tile = gemm({p});
-    if (want) {
+    if (want && tile != 40128128) {      // (split over K: the reduction leaves no sums, the norm takes its own)
       const int rows = gemm_stats_rows(tile);
       // chunks per image: one per wave row of a tile (a lone image may end inside a tile; with
       // several, H*W is a multiple of every chunk height)

@@ -95,7 +95,7 @@ __device__ __forceinline__ void interleave_hint() {
 #pragma unroll
   for (int i = 0; i < NR; ++i) {
     SGB(0x100, 1);      // one DS read
-    SGB(0x008, per);    // `per` MFMAs
+    if constexpr (per > 0) SGB(0x008, per);    // `per` MFMAs
   }
   if (extra > 0) SGB(0x008, extra);
 }
@@ -259,9 +259,12 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   auto acc_col = [&](int e) { return M16 ? 16 * ((e >> 2) & 1) + (lane & 15) : lane & 31; };
 
   int nk = P.K / BKT;
+  int kb_conv = 0;              // first slab of my share of a convolution (its A offset is not linear in k)
   if (MODE == 4) {              // my share of the slabs (shares differ by at most one slab)
     const int kb = split * nk / batch.splits, ke = (split + 1) * nk / batch.splits;
-    P.A += kb * BKT; P.W += kb * BKT;
+    if constexpr (CONV) kb_conv = kb;
+    else P.A += kb * BKT;
+    P.W += kb * BKT;
     nk = ke - kb;
   }
   // lanes address their tile by 32-bit byte offsets from its first row, so no operand size limit
@@ -283,8 +286,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
     const int ks = (kt < nk ? kt : nk - 1) * BKT;
     int ka = ks;             // A-side offset of the slab
     if constexpr (CONV) {    // slab = 64 channels of one tap (ky, kx): shift by ky rows and kx pixels
-      int tap = ks / P.conv_cin;
-      const int c0 = ks - tap * P.conv_cin;
+      const int kc = ks + kb_conv * BKT;
+      int tap = kc / P.conv_cin;
+      const int c0 = kc - tap * P.conv_cin;
       int kf = 0;            // 27 taps: the first index is the frame, 0 = two frames back (the stack starts two frames early)
       if (P.conv_kt == 3) { kf = tap / 9; tap -= 9 * kf; }
       const int ky = tap / 3, kx = tap - 3 * ky;
@@ -857,7 +861,17 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmBatch batc
   const int mrow = tm * BM + wm * (BM / WM) + i * 32 + 8 * g + 4 * (lane >> 5);
   const float* pc = batch.partial + (size_t)tile * batch.splits * (BM * BN) + (size_t)q * 4;
   f32x4 acc = *(const f32x4*)pc;
-  for (int s = 1; s < batch.splits; ++s) {
+  int s = 1;
+  for (; s + 3 < batch.splits; s += 4) {           // four loads in flight; added in the same order
+    f32x4 t4[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t4[u] = *(const f32x4*)(pc + (size_t)(s + u) * (BM * BN));
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] += t4[u][c];
+  }
+  for (; s < batch.splits; ++s) {
     const f32x4 t4 = *(const f32x4*)(pc + (size_t)s * (BM * BN));
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[c] += t4[c];
@@ -914,6 +928,39 @@ static void launch_t(hipStream_t s, GemmBatch& b) {
 //   30128128  128x128, k-slab 64, 4-stage ring (one workgroup per CU: for grids below 256 tiles)
 //   30128064 / 33128064  128x64 (4 waves of 32x64), 6- / 3-stage ring;  30064128  64x128 (4 waves of 64x32), 6-stage ring
 //   40128128  the same as split-K over b.splits shares of K plus the reduction kernel
+//   30032128 / 30064064  32x128 (4 waves of 32x32) and 64x64 (2 waves of 32x64), two workgroups per CU, 4- / 5-stage ring;
+//   40032128 / 40064064  the same as split-K
+// Few rows: the weights are read once whatever the tile, and what counts is how many bytes are in flight and how
+// long the chain of slabs of one workgroup is.  Tiles of 32x128 (up to 64 rows) and 64x64 take 80 KB of LDS, so
+// two workgroups share a CU and K is split over up to 512 of them.  0: not such a launch.
+static int small_m_tile(GemmBatch& b) {
+  int max_m = 0, min_nk = 1 << 30;
+  long long t32 = 0, t64 = 0, t128 = 0;
+  bool qk = false;
+  for (int i = 0; i < b.n; ++i) {
+    const GemmProblem& p = b.p[i];
+    if (p.M <= 0 || p.N <= 0) continue;
+    if (p.conv_w > 0 || (p.out_kind == OUT_QKNORM && p.qk.head_dim > 64)) return 0;
+    qk = qk || p.out_kind == OUT_QKNORM;
+    max_m = p.M > max_m ? p.M : max_m;
+    min_nk = p.K / 64 < min_nk ? p.K / 64 : min_nk;
+    t32 += (long long)((p.M + 31) / 32) * ((p.N + 127) / 128);
+    t64 += (long long)((p.M + 63) / 64) * ((p.N + 63) / 64);
+    t128 += (long long)((p.M + 127) / 128) * ((p.N + 127) / 128);
+  }
+  if (max_m == 0 || max_m > 512 || t128 > 256) return 0;
+  const bool rows32 = max_m <= 64 && !qk;       // (the q/k-norm epilogue needs waves of 64 columns, the reduction has none)
+  const long long t = rows32 ? t32 : t64;
+  if (t > 512) return 0;
+  long long sp = qk || !b.partial ? 1 : 512 / t;
+  if (sp > min_nk / 4) sp = min_nk / 4;
+  const long long cap = (long long)(b.partial_bytes / ((rows32 ? 32 * 128 : 64 * 64) * 4)) / t;
+  if (sp > cap) sp = cap;
+  if (sp < 2) return rows32 ? 30032128 : 30064064;
+  b.splits = (int)sp;
+  return rows32 ? 40032128 : 40064064;
+}
+
 int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
   // Tile choice.  The 256x256 tile (8 waves) halves the L2->LDS traffic per flop of the 128x128
   // tile and is about 25% faster per tile-flop, but one workgroup fills a CU, so its grid runs
@@ -922,8 +969,9 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
   // than a full one, lone tiles see less contention); otherwise the 128x128 tile (three
   // workgroups per CU, finer granularity).
   int tile = force_tile;
-  if (tile == 40128128 && (!b.partial || b.splits < 1)) tile = 30128128;   // no scratch: no split
-  if (tile != 40128128) b.splits = 1;
+  if (tile > 40000000 && (!b.partial || b.splits < 1)) tile -= 10000000;   // no scratch: no split
+  if (tile < 40000000) b.splits = 1;
+  if (!tile) tile = small_m_tile(b);
   if (!tile) {
     // Few tiles (small M): a lone tile's k-loop runs at memory latency per slab, so keep three
     // slabs in flight (4-stage ring, one workgroup per CU) and, when K is long enough, split it
@@ -941,7 +989,8 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
       const long long cap = (long long)(b.partial_bytes / (128 * 128 * 4)) / t128;
       if (sp > cap) sp = cap;
       bool qk = false;                       // the reduction kernel has no q/k-norm epilogue
-      for (int i = 0; i < b.n; ++i) qk = qk || b.p[i].out_kind == OUT_QKNORM || b.p[i].conv_w > 0;   // (nor the split A offsets a convolution's)
+      // (nor is a video's convolution split: its frames must not depend on how many follow them)
+      for (int i = 0; i < b.n; ++i) qk = qk || b.p[i].out_kind == OUT_QKNORM || (b.p[i].conv_w > 0 && b.p[i].conv_kt == 3);
       if (b.partial && sp >= 2 && !qk) { b.splits = (int)sp; tile = 40128128; }
       else {
         // no split (q/k-norm epilogue, or K too short): 128x64 tiles with a 6-stage ring when twice the
@@ -1033,9 +1082,9 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
   }
   // the q/k-norm epilogue exists only in the instantiations whose waves own 64 output columns
   if (qknorm && !(tile == 1256256 || tile == 1320256 || tile == 11256256 || tile == 21256256 || tile == 128128 || tile == 10128128 ||
-                  tile == 30128128 || tile == 30128064 || tile == 33128064 || tile == 256128 || tile == 31256128 || tile == 32256128))
+                  tile == 30128128 || tile == 30128064 || tile == 30064064 || tile == 33128064 || tile == 256128 || tile == 31256128 || tile == 32256128))
     return -1;
-  if (qknorm && (tile == 30128064 || tile == 33128064))      // 64 columns per workgroup: heads of 64 only
+  if (qknorm && (tile == 30128064 || tile == 33128064 || tile == 30064064))      // 64 columns per workgroup: heads of 64 only
     for (int i = 0; i < b.n; ++i)
       if (b.p[i].out_kind == OUT_QKNORM && b.p[i].qk.head_dim > 64) return -1;
   if (conv) {     // convolutions: never mixed with plain products, three tile shapes
@@ -1045,6 +1094,7 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
           (b.p[i].conv_kt != 1 && b.p[i].conv_kt != 3) || b.p[i].K != 9 * b.p[i].conv_kt * b.p[i].conv_cin) return -1;
     if (tile == 1256256) launch_t<256, 256, 2, 4, 64, 2, 0, true, 4>(s, b);
     else if (tile == 32256128) launch_t<256, 128, 4, 2, 64, 3, 0, true, 5>(s, b);
+    else if (tile == 40128128) launch_t<128, 128, 2, 2, 64, 4, 4, true, 2>(s, b);
     else if (tile == 30128128) launch_t<128, 128, 2, 2, 64, 4, 0, true, 2>(s, b);
     else { tile = 128128; launch_t<128, 128, 2, 2, 64, 2, 0, true, 2>(s, b); }
     return tile;
@@ -1063,6 +1113,10 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
     case 30128128: launch_t<128, 128, 2, 2, 64, 4, 0, false, 2>(s, b); break;
     case 30128064: launch_t<128, 64, 4, 1, 64, 6, 0, false, 2>(s, b); break;
     case 30064128: launch_t<64, 128, 1, 4, 64, 6, 0, false, 2>(s, b); break;
+    case 30032128: launch_t<32, 128, 1, 4, 64, 4, 0, false, 2>(s, b); break;
+    case 40032128: launch_t<32, 128, 1, 4, 64, 4, 4, false, 2>(s, b); break;
+    case 30064064: launch_t<64, 64, 2, 1, 64, 5, 0, false, 2>(s, b); break;
+    case 40064064: launch_t<64, 64, 2, 1, 64, 5, 4, false, 2>(s, b); break;
     case 33128064: launch_t<128, 64, 4, 1, 64, 3, 0, false, 2>(s, b); break;
     case 31256128: launch_t<256, 128, 2, 2, 64, 3, 0, false, 2>(s, b); break;
     case 32256128: launch_t<256, 128, 4, 2, 64, 3, 0, false, 5>(s, b); break;

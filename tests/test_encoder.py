@@ -102,6 +102,25 @@ def test_encoder_forward_against_oracle(torch, X, lens):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("lens", [[1], [33], [64], [65], [300, 77]])
+def test_encoder_benchmark_width_few_rows(torch, X, lens):
+    """The tiles for few rows at their edges (32-row tiles up to 64 rows, then 64x64 tiles), split over K, and the
+    norm with a workgroup per row: one layer of the benchmark width, same bounds as the other encoder tests."""
+    arch = dict(synth.ENCODERS["t5_xxl"], n_layers=1, vocab=512)
+    params, toks, m, d_tok = _case(torch, X, arch, lens, std=0.0125, bias_scale=2.0)
+    out32 = torch.full((sum(lens), arch["d_model"]), float("nan"), dtype=torch.float32, device="cuda")
+    m.forward(lens, d_tok, None, out32)
+    torch.cuda.synchronize()
+    got, ora, o = out32.cpu().numpy(), E.EncoderOracle(arch, params), 0
+    for s, L in enumerate(lens):
+        ref = ora.forward(toks[s])
+        assert np.isfinite(got[o:o + L]).all()
+        assert rel_l2(got[o:o + L], ref) <= 1e-2, (s, rel_l2(got[o:o + L], ref))
+        o += L
+    m.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("lens", [[32], [500, 7]])
 def test_encoder_benchmark_width_one_layer(torch, X, lens):
     """The T5-XXL width the stage tables are timed at (d_model 4096, 64 heads, d_ff 10240), one
