@@ -186,8 +186,8 @@ void plan(const dec_ctx* c, int n, int h, int w, Layout& L) {
   L.vt = take(rup(C0, 256) * rup(L.P0, 64) * 2);            // read as a second operand: rows up to a multiple of 256
   L.sc = take((size_t)L.P0 * L.P0 * 4);
   L.pm = take((size_t)L.P0 * rup(L.P0, 64) * 2);
-  // channel sums per chunk of 64 pixels at least (the smallest wave height of a product tile)
-  L.gnp = take(std::max(group_norm_partial_bytes((long long)L.n_out * L.Hf * L.Wf, 1024), max_x / 64 * 8 + 2 * 1024 * 8));
+  // channel sums per chunk of 64 pixels at least (the smallest wave height of a product tile; of 32 where a product is split)
+  L.gnp = take(std::max({group_norm_partial_bytes((long long)L.n_out * L.Hf * L.Wf, 1024), max_x / 64 * 8 + 2 * 1024 * 8, GEMM_SPLIT_STATS_BYTES}));
   L.gst = take(GN_STATS_BYTES);
   L.out4 = take((size_t)L.n_out * L.Hf * L.Wf * 4 * 4);
   L.partial = take(PARTIAL_BYTES);
@@ -233,7 +233,7 @@ struct Fwd {
     const bool want = sums && (kind == OUT_F32 || kind == OUT_RESID_F32);   // a group norm reads `out` next
     if (want) p.stats = at<float>(L.gnp);
     const int tile = gemm({p});
-    if (want && tile != 40128128) {      // (split over K: the reduction leaves no sums, the norm takes its own)
+    if (want) {
       const int rows = gemm_stats_rows(tile);
       // chunks per image: one per wave row of a tile (a lone image may end inside a tile; with
       // several, H*W is a multiple of every chunk height)

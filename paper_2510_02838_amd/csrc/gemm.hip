@@ -876,21 +876,36 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmBatch batc
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[c] += t4[c];
   }
-  if (n >= P.N) return;
-  const float bias = P.bias ? P.bias[n] : 0.f;
+  float cs = 0.f, cq = 0.f;               // sum and sum of squares of the values stored, this thread's rows of the column
+  if (n < P.N) {
+    const float bias = P.bias ? P.bias[n] : 0.f;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const int m = mrow + c;
-    if (m >= P.M) continue;
-    const float v = acc[c] + bias;
-    const size_t o = (size_t)m * P.ldc + n;
-    if (P.out_kind == OUT_RESID_F32) {
-      const float gt = P.gate ? P.gate[(size_t)(P.row_req ? P.row_req[m] : 0) * P.gate_stride + n] : 1.f;
-      ((float*)P.out)[o] += gt * v;
-    } else if (P.out_kind == OUT_F32) {
-      ((float*)P.out)[o] = v;
-    } else {
-      ((bf16_t*)P.out)[o] = f2bf(P.out_kind == OUT_GELU_BF16 ? gelu_tanh(v) : v);
+    for (int c = 0; c < 4; ++c) {
+      const int m = mrow + c;
+      if (m >= P.M) continue;
+      float v = acc[c] + bias;
+      const size_t o = (size_t)m * P.ldc + n;
+      if (P.out_kind == OUT_RESID_F32) {
+        const float gt = P.gate ? P.gate[(size_t)(P.row_req ? P.row_req[m] : 0) * P.gate_stride + n] : 1.f;
+        v = ((float*)P.out)[o] + gt * v;
+        ((float*)P.out)[o] = v;
+      } else if (P.out_kind == OUT_F32) {
+        ((float*)P.out)[o] = v;
+      } else {
+        ((bf16_t*)P.out)[o] = f2bf(P.out_kind == OUT_GELU_BF16 ? gelu_tanh(v) : v);
+      }
+      cs += v; cq += v * v;
+    }
+  }
+  if (P.stats) {                          // a workgroup holds one 32x32 tile: a chunk of 32 rows
+    __shared__ float red[4][32][2];
+    cs += __shfl_xor(cs, 32); cq += __shfl_xor(cq, 32);
+    if (lane < 32) { red[g][lane][0] = cs; red[g][lane][1] = cq; }
+    __syncthreads();
+    if (threadIdx.x < 32 && n < P.N) {
+      float* sp = P.stats + ((size_t)((tm * BM + wm * (BM / WM)) / 32 + i) * P.N + n) * 2;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) sp[c] = (red[0][lane][c] + red[1][lane][c]) + (red[2][lane][c] + red[3][lane][c]);
     }
   }
 }
