@@ -246,15 +246,15 @@ struct Fwd {
   }
   // first real image of the stack of bordered images of H x W x C
   bf16_t* frame(int H, int W, int C) const { return at<bf16_t>(L.img) + (kt == 3 ? (size_t)2 * (H + 2) * (W + 2) * C : 0); }
-  void zero_img(int H, int W, int C) const {       // the border must be zero; the interior is overwritten
-    if (kt == 3) launch_fill_u16(s, at<bf16_t>(L.img), (long long)2 * (H + 2) * (W + 2) * C, 0);   // the two frames before the first
-    launch_zero_border(s, frame(H, W, C), H, W, C, B);
+  // (the kernels that write a bordered image write its border too)
+  void zero_lead(int H, int W, int C) const {      // the two frames before a video's first
+    if (kt == 3) launch_fill_u16(s, at<bf16_t>(L.img), (long long)2 * (H + 2) * (W + 2) * C, 0);
   }
   // x (cin channels, in `x`) -> result (cout channels) in `y`; y == x when cin == cout
   void res(const std::string& name, float* x, float* y, int H, int W, int cin, int cout) const {
     bf16_t* img = at<bf16_t>(L.img);
     float* t = at<float>(L.t);
-    zero_img(H, W, cin);
+    zero_lead(H, W, cin);
     gn(name + ".gn1", x, frame(H, W, cin), H, W, cin, 1, 1);
     conv3(name + ".conv1", img, H, W, OUT_F32, t, cout);
     if (cin != cout) {
@@ -262,7 +262,7 @@ struct Fwd {
       gemm({prob(at<bf16_t>(L.act), cin, Wm(c, name + ".short.w"), Wld(c, name + ".short.w"), Wv(c, name + ".short.b"),
                  B * H * W, cout, cin, OUT_F32, y, cout)});
     }
-    zero_img(H, W, cout);
+    zero_lead(H, W, cout);
     gn(name + ".gn2", t, frame(H, W, cout), H, W, cout, 1, 1);
     conv3(name + ".conv2", img, H, W, OUT_RESID_F32, y, cout);
   }
@@ -509,7 +509,7 @@ dit_status dec_forward(dec_ctx* c, int n, int h, int w, const float* latent, flo
     if (l != g.n_levels - 1) {
       const int frame_up = g.temporal && l < g.t_up;       // F frames -> 2F - 1: the first once, the others twice
       if (frame_up) F.B = 2 * F.B - 1;
-      F.zero_img(2 * H, 2 * W, ch);
+      F.zero_lead(2 * H, 2 * W, ch);
       launch_upsample_pad(s, x, F.frame(2 * H, 2 * W, ch), H, W, ch, F.B, frame_up);
       H *= 2; W *= 2;
       F.conv3("up" + std::to_string(l) + ".upconv", img, H, W, OUT_F32, other, ch);
@@ -517,7 +517,7 @@ dit_status dec_forward(dec_ctx* c, int n, int h, int w, const float* latent, flo
     }
   }
   // output: GN + SiLU + conv to out_ch channels
-  F.zero_img(H, W, prev);
+  F.zero_lead(H, W, prev);
   F.gn("out.gn", x, F.frame(H, W, prev), H, W, prev, 1, 1);
   {
     const DTensor* to = find(c, "conv_out.w");

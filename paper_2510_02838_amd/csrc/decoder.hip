@@ -19,6 +19,10 @@ __device__ __forceinline__ float d_silu(float x) { return x * __builtin_amdgcn_r
 __device__ __forceinline__ long long dst_pixel(int y, int x, int W, int pad) {
   return pad ? (long long)(y + 1) * (W + 2) + (x + 1) : (long long)y * W + x;
 }
+// eight zero channels of pixel (py, px) of a bordered image, counted from its corner
+__device__ __forceinline__ void zero_piece(bf16_t* img, int py, int px, int W, int C, int c) {
+  *(uint4*)(img + ((long long)py * (W + 2) + px) * C + c) = make_uint4(0, 0, 0, 0);
+}
 }  // namespace
 
 // latents fp32 channels-first [B][C][H][W] -> bf16 bordered channels-last [B][(H+2)(W+2)][Cpad],
@@ -39,26 +43,6 @@ __global__ __launch_bounds__(256) void latent_to_image_kernel(const float* __res
 void launch_latent_to_image(hipStream_t s, const float* z, bf16_t* out, int C, int H, int W, int Cpad, int B, int frames) {
   const long long n = (long long)B * H * W * C;
   if (n) hipLaunchKernelGGL(latent_to_image_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, z, out, C, H, W, Cpad, B, frames);
-}
-
-// zero border of a bordered image [(H+2)(W+2)][C]: rows 0 and H+1, columns 0 and W+1
-__global__ __launch_bounds__(256) void zero_border_kernel(bf16_t* __restrict__ img, int H, int W, int C) {
-  img += (size_t)blockIdx.y * (H + 2) * (W + 2) * C;       // one bordered image per blockIdx.y
-  const int o8 = C >> 3;                                   // 16-byte pieces per pixel
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  const long long nb = 2LL * (W + 2) + 2LL * H;            // border pixels
-  if (i >= nb * o8) return;
-  const long long b = i / o8;
-  const int c = (int)(i % o8) * 8;
-  long long pix;
-  if (b < W + 2) pix = b;                                                   // top row
-  else if (b < 2LL * (W + 2)) pix = (long long)(H + 1) * (W + 2) + (b - (W + 2));   // bottom row
-  else { const long long r = b - 2LL * (W + 2); pix = (r / 2 + 1) * (W + 2) + ((r & 1) ? W + 1 : 0); }
-  *(uint4*)(img + pix * C + c) = make_uint4(0, 0, 0, 0);
-}
-void launch_zero_border(hipStream_t s, bf16_t* img, int H, int W, int C, int B) {
-  const long long n = (2LL * (W + 2) + 2LL * H) * (C / 8);
-  if (n && B) hipLaunchKernelGGL(zero_border_kernel, dim3((unsigned)((n + 255) / 256), B), dim3(256), 0, s, img, H, W, C);
 }
 
 // ---- group norm ---------------------------------------------------------------------------
@@ -157,6 +141,7 @@ __global__ __launch_bounds__(64) void gn_combine_kernel(const double2* __restric
 // pass 3: y = (x - mean_g) rstd_g gamma_c + beta_c, optional SiLU, bf16, bordered or plain rows.
 // One image row per blockIdx.y; a thread takes 8 consecutive channels of four consecutive pixels (gain, bias and
 // the group statistics are fetched once for the four, and the four pixels' loads are in flight together).
+// A bordered image's border is written here too: a launch of its own took 4.7 us, 28 times an image.
 __global__ __launch_bounds__(256) void gn_apply_kernel(const float* __restrict__ x, const float2* __restrict__ stats,
                                                        const float* __restrict__ gamma, const float* __restrict__ beta,
                                                        bf16_t* __restrict__ out, int W, int C, int osh, int gsh,
@@ -197,6 +182,19 @@ __global__ __launch_bounds__(256) void gn_apply_kernel(const float* __restrict__
     uint4 w;
     w.x = d_pack2(r[0], r[1]); w.y = d_pack2(r[2], r[3]); w.z = d_pack2(r[4], r[5]); w.w = d_pack2(r[6], r[7]);
     *(uint4*)(out + dst_pixel(y, x0 + k, W, pad) * C + c) = w;
+  }
+  // the zero border beside and (first and last row) above and below these pixels
+  if (!pad) return;
+  const bool first = x0 == 0, last = x0 + 4 >= W;
+  if (first) zero_piece(out, y + 1, 0, W, C, c);
+  if (last) zero_piece(out, y + 1, W + 1, W, C, c);
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    if (y != (e ? H - 1 : 0)) continue;
+    const int r = e ? H + 1 : 0;
+    for (int k = 0; k < 4 && x0 + k < W; ++k) zero_piece(out, r, x0 + k + 1, W, C, c);
+    if (first) zero_piece(out, r, 0, W, C, c);
+    if (last) zero_piece(out, r, W + 1, W, C, c);
   }
 }
 
@@ -253,6 +251,19 @@ __global__ __launch_bounds__(256) void upsample_pad_kernel(const float* __restri
 #pragma unroll
     for (int dx = 0; dx < 2; ++dx)
       *(uint4*)(out + dst_pixel(2 * y + dy, 2 * xx + dx, W2, 1) * C + c) = w;
+  // the zero border beside and (first and last row) above and below these pixels
+  const bool first = xx == 0, last = xx == W - 1;
+#pragma unroll
+  for (int dy = 0; dy < 2; ++dy) {
+    if (first) zero_piece(out, 2 * y + dy + 1, 0, W2, C, c);
+    if (last) zero_piece(out, 2 * y + dy + 1, W2 + 1, W2, C, c);
+    if (y != (dy ? H - 1 : 0)) continue;
+    const int r = dy ? 2 * H + 1 : 0;
+    zero_piece(out, r, 2 * xx + 1, W2, C, c);
+    zero_piece(out, r, 2 * xx + 2, W2, C, c);
+    if (first) zero_piece(out, r, 0, W2, C, c);
+    if (last) zero_piece(out, r, W2 + 1, W2, C, c);
+  }
 }
 void launch_upsample_pad(hipStream_t s, const float* x, bf16_t* out, int H, int W, int C, int B, int frame_up) {
   const long long n = (long long)H * W * (C / 8);

@@ -188,7 +188,6 @@ void launch_rel_bias_table(hipStream_t s, const float* table, float* bias, int H
 // latent fp32 [C][H][W] -> bf16 bordered image [(H+2)(W+2)][Cpad] (interior only; caller zero-fills)
 // frames = 0: z is [B][C][H][W]; frames = B: z is one video [C][B][H][W]
 void launch_latent_to_image(hipStream_t s, const float* z, bf16_t* out, int C, int H, int W, int Cpad, int B = 1, int frames = 0);
-void launch_zero_border(hipStream_t s, bf16_t* img, int H, int W, int C, int B = 1);   // C % 8 == 0
 // GroupNorm (eps 1e-6, affine) of the fp32 stream x [H*W][C], optional SiLU, bf16 output with
 // (pad=1) or without a one-pixel border.  C in {64,128,256,512,1024}; partial: scratch of
 // group_norm_partial_bytes; stats: scratch of GN_STATS_BYTES (groups <= 32).  ready_chunks > 0: partial already holds
