@@ -108,7 +108,7 @@ uint16_t h_f2bf(float f) {
 }
 
 struct Layout {
-  size_t map, xa, xb, t, img, act, q, k, v, vt, sc, pm, gnp, gst, out4, partial, total;
+  size_t map, xa, xb, t, img, act, q, k, v, vt, sc, pm, gnp, gnp_bytes, gst, out4, partial, total;
   int Hf, Wf, P0, P0pad;          // final image size; latent pixels and their padding to 64
   int n_out;                      // images at the output (a video's frame count grows with the frame rate)
 };
@@ -186,8 +186,9 @@ void plan(const dec_ctx* c, int n, int h, int w, Layout& L) {
   L.vt = take(rup(C0, 256) * rup(L.P0, 64) * 2);            // read as a second operand: rows up to a multiple of 256
   L.sc = take((size_t)L.P0 * L.P0 * 4);
   L.pm = take((size_t)L.P0 * rup(L.P0, 64) * 2);
-  // channel sums per chunk of 64 pixels at least (the smallest wave height of a product tile; of 32 where a product is split)
-  L.gnp = take(std::max({group_norm_partial_bytes((long long)L.n_out * L.Hf * L.Wf, 1024), max_x / 64 * 8 + 2 * 1024 * 8, GEMM_SPLIT_STATS_BYTES}));
+  // channel sums per chunk of 64 pixels at least (the smallest wave height of a product tile)
+  L.gnp_bytes = std::max(group_norm_partial_bytes((long long)L.n_out * L.Hf * L.Wf, 1024), max_x / 64 * 8 + 2 * 1024 * 8);
+  L.gnp = take(L.gnp_bytes);
   L.gst = take(GN_STATS_BYTES);
   L.out4 = take((size_t)L.n_out * L.Hf * L.Wf * 4 * 4);
   L.partial = take(PARTIAL_BYTES);
@@ -213,14 +214,14 @@ struct Fwd {
   mutable const float* stats_of = nullptr;
   mutable int stats_chunks = 0;
   template <class T> T* at(size_t off) const { return (T*)(ws + off); }
-  int gemm(std::initializer_list<GemmProblem> ps) const {
+  int gemm(std::initializer_list<GemmProblem> ps, bool may_split = true) const {
     GemmBatch b;
     b.n = 0; b.total_tiles = 0;
     for (const GemmProblem& p : ps) {
       if (p.out == stats_of) stats_of = nullptr;      // the buffer changes: its sums are stale
       b.p[b.n++] = p;
     }
-    b.partial = at<float>(L.partial); b.partial_bytes = PARTIAL_BYTES;
+    if (may_split) { b.partial = at<float>(L.partial); b.partial_bytes = PARTIAL_BYTES; }
     return launch_gemm(s, b);
   }
   // 3x3 convolution of the bordered bf16 image `img` (H x W, cin_pad channels) into fp32 rows
@@ -232,7 +233,8 @@ struct Fwd {
     p.conv_w = W; p.conv_cin = t->cin_pad; p.conv_img = H * W; p.conv_kt = kt;
     const bool want = sums && (kind == OUT_F32 || kind == OUT_RESID_F32);   // a group norm reads `out` next
     if (want) p.stats = at<float>(L.gnp);
-    const int tile = gemm({p});
+    // (a split product leaves sums per 32 rows, whole 128-row tiles: only where they fit)
+    const int tile = gemm({p}, !want || ((size_t)p.M + 127) / 128 * 4 * p.N * 8 <= L.gnp_bytes);
     if (want) {
       const int rows = gemm_stats_rows(tile);
       // chunks per image: one per wave row of a tile (a lone image may end inside a tile; with

@@ -75,7 +75,6 @@ inline int gemm_stats_rows(int tile_code) {     // rows per stats chunk: two wav
   if (tile_code == 40128128) return 32;         // 32 rows where the split-K reduction takes the sums
   return tile_code == 32256128 ? 64 : (tile_code % 1000000) / 1000 / 2;
 }
-constexpr size_t GEMM_SPLIT_STATS_BYTES = (size_t)128 * 128 * 128 / 32 * 8;   // the sums of a split convolution (at most 128 tiles)
 
 // ---- attention ----------------------------------------------------------------------
 // One block of q_per_tile queries of one segment.  parts == 0: against all keys of the segment.  parts > 0:
