@@ -201,7 +201,9 @@ dit_status dit_op_gemm(void* stream, const void* A, int lda, const void* W, int 
 /* As dit_op_gemm (out_kind 0..2 only) with the tile variant forced, for tuning sweeps:
  * BM*1000+BN in {256256, 256128, 128256, 128128}; +1000000 = 8 waves (256256 only);
  * +10000000 / +20000000 = k-slab 32 with a 4- / 5-stage LDS ring instead of k-slab 64 with
- * 2 stages (256256, 1256256, 128128); 30128128 = 128x128 with k-slab 64 and a 4-stage ring. */
+ * 2 stages (256256, 1256256, 128128); 30128128 = 128x128 with k-slab 64 and a 4-stage ring;
+ * 1320256 = 320x256 with 8 waves; 31256128 / 32256128 (4 / 8 waves) and 31128256 with a 3-stage
+ * ring; for few rows 30128064, 33128064, 30064128, 30064064 and 30032128. */
 dit_status dit_op_gemm_variant(void* stream, const void* A, int lda, const void* W, int ldw,
                                const float* bias, int M, int N, int K, int out_kind, void* out,
                                int ldc, int variant);
@@ -229,6 +231,13 @@ dit_status dit_op_gemm_splitk(void* stream, const void* A, int lda, const void* 
                               const float* bias, int M, int N, int K, int out_kind, void* out,
                               int ldc, const float* gate, int gate_stride, const int* row_req,
                               int splits, void* work, size_t work_bytes);
+
+/* dit_op_gemm_splitk with the tile forced: variant 40128128 (what dit_op_gemm_splitk takes), 40064064 or
+ * 40032128, the tiles of 128x128, 64x64 and 32x128.  work: BM*BN*4 bytes per tile and share. */
+dit_status dit_op_gemm_splitk_variant(void* stream, const void* A, int lda, const void* W, int ldw,
+                                      const float* bias, int M, int N, int K, int out_kind, void* out,
+                                      int ldc, const float* gate, int gate_stride, const int* row_req,
+                                      int splits, void* work, size_t work_bytes, int variant);
 
 /* dit_op_gemm_splitk for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same kernels and the

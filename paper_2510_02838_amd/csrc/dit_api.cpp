@@ -1248,22 +1248,32 @@ dit_status dit_op_gemm_qknorm(void* stream, const void* A, int lda, const void* 
   return hipGetLastError() == hipSuccess ? DIT_OK : DIT_EDEVICE;
 }
 
-dit_status dit_op_gemm_splitk(void* stream, const void* A, int lda, const void* W, int ldw, const float* bias, int M,
-                              int N, int K, int out_kind, void* out, int ldc, const float* gate, int gate_stride,
-                              const int* row_req, int splits, void* work, size_t work_bytes) {
+dit_status dit_op_gemm_splitk_variant(void* stream, const void* A, int lda, const void* W, int ldw, const float* bias,
+                                      int M, int N, int K, int out_kind, void* out, int ldc, const float* gate,
+                                      int gate_stride, const int* row_req, int splits, void* work, size_t work_bytes,
+                                      int variant) {
   if (!A || !W || !out || !work) return DIT_EINVAL;
+  if (variant != 40128128 && variant != 40064064 && variant != 40032128) return DIT_EINVAL;
   if (M <= 0 || N <= 0 || K <= 0 || K % 64 || lda < K || ldw < K || ldc < N) return DIT_ESHAPE;
   if (lda % 8 || ldw % 8) return DIT_ESHAPE;
   if (out_kind < 0 || out_kind > 3) return DIT_EINVAL;
   if (ldc % ((out_kind == 1 || out_kind == 3) ? 4 : 8) || ((uintptr_t)out & 15) || ((uintptr_t)work & 15)) return DIT_ESHAPE;
   if (splits < 1 || splits > K / 64) return DIT_ESHAPE;
-  const size_t tiles = (size_t)((M + 127) / 128) * ((N + 127) / 128);
-  if (work_bytes < tiles * splits * (128 * 128 * 4)) return DIT_ENOMEM;
+  const int bm = variant / 1000 % 1000, bn = variant % 1000;
+  const size_t tiles = (size_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+  if (work_bytes < tiles * splits * ((size_t)bm * bn * 4)) return DIT_ENOMEM;
   GemmBatch b; b.n = 1; b.total_tiles = 0;
   b.p[0] = mk((const bf16_t*)A, lda, (const bf16_t*)W, ldw, bias, M, N, K, out_kind, out, ldc, gate, gate_stride, row_req);
   b.splits = splits; b.partial = (float*)work; b.partial_bytes = work_bytes;
-  if (launch_gemm((hipStream_t)stream, b, 40128128) < 0) return DIT_ESHAPE;
+  if (launch_gemm((hipStream_t)stream, b, variant) < 0) return DIT_ESHAPE;
   return hipGetLastError() == hipSuccess ? DIT_OK : DIT_EDEVICE;
+}
+
+dit_status dit_op_gemm_splitk(void* stream, const void* A, int lda, const void* W, int ldw, const float* bias, int M,
+                              int N, int K, int out_kind, void* out, int ldc, const float* gate, int gate_stride,
+                              const int* row_req, int splits, void* work, size_t work_bytes) {
+  return dit_op_gemm_splitk_variant(stream, A, lda, W, ldw, bias, M, N, K, out_kind, out, ldc, gate, gate_stride, row_req,
+                                    splits, work, work_bytes, 40128128);
 }
 
 dit_status dit_op_gemm_splitk_static(void* stream, const void* A, int lda, const void* W, int ldw, const float* bias,

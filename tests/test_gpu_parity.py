@@ -67,7 +67,7 @@ def test_set_get_tensor_round_trip(torch, B):
 
 # ---------------------------------------------------------------------------------- GEMM
 @pytest.mark.parametrize("M,N,K", [(300, 384, 256), (1, 256, 64), (517, 1000, 192), (4250, 1536, 1536)])
-@pytest.mark.parametrize("variant", [0, 128128, 10128128, 30128128, 30128064, 33128064, 30064128, 256256, 1256256, 1320256, 10256256, 11256256, 20256256, 21256256,
+@pytest.mark.parametrize("variant", [0, 128128, 10128128, 30128128, 30128064, 33128064, 30064128, 30064064, 30032128, 256256, 1256256, 1320256, 10256256, 11256256, 20256256, 21256256,
                                      256128, 128256, 31256128, 32256128, 31128256])
 def test_gemm_against_float64_matmul(torch, B, M, N, K, variant):
     if M > 1000 and variant not in (0, 1256256, 1320256, 11256256, 128128, 32256128):
@@ -105,7 +105,8 @@ def test_gemm_two_group_tiles_at_their_edges(torch, B, M, variant):
     five slabs (fewer and more than the ring has stages, odd and even), rows around the parts in which a
     slab of A is fetched and read (64 and 80 rows of a wave, 256 and 320 of a tile), ragged columns; and the
     two tiles for few rows.
-    fp32 outputs of at most 320 products: 1e-5 of the sum of absolute products is far above 320 * 2^-24."""
+    fp32 outputs of at most 320 products: a chain of n additions errs by about sqrt(n) * 2^-24 of the sum of absolute
+    products (1.1e-6) and by n * 2^-24 (1.9e-5) at the very worst; the bound lies between, at 1e-5."""
     for K, N in ((64, 264), (128, 128), (192, 100), (256, 513), (320, 256)):
         A, W = rnd(21, "A", (M, K)), rnd(22, "W", (N, K), 0.05)
         Wp = np.zeros(((N + 255) // 256 * 256, K), np.float32); Wp[:N] = W
@@ -240,6 +241,56 @@ def test_gemm_split_k(torch, B, M, N, K, splits):
                                 None, 0, None, K // 64 + 1, work.data_ptr(), wb) != 0
     assert B.dit_op_gemm_splitk(None, dA.data_ptr(), K, dW.data_ptr(), K, None, M, N, K, 0, out.data_ptr(), ldc,
                                 None, 0, None, splits, work.data_ptr(), wb - 1) != 0
+
+
+@pytest.mark.parametrize("variant", [40032128, 40064064])
+@pytest.mark.parametrize("M,N,K,splits", [(1, 256, 64, 1), (31, 100, 320, 3), (33, 264, 192, 2), (64, 513, 320, 5), (65, 130, 448, 3),
+                                          (128, 1030, 640, 4), (200, 384, 1536, 6)])
+def test_gemm_split_k_tiles_for_few_rows(torch, B, M, N, K, splits, variant):
+    """The 32x128 and 64x64 tiles with K split, at the edges of a tile and past it, with ragged columns and with shares of
+    unequal length: all four epilogues against the float64 product, twice with the scratch full of NaN.
+    A chain of K + splits float32 additions errs by at most (K + splits) * 2^-24 of the sum of absolute terms; a 16-bit
+    result, eight significant bits, is rounded once more (2^-8 of it at most, and 4 * 2^-24 for the GELU's exponential, reciprocal and products)."""
+    A, W = rnd(41, "A", (M, K)), rnd(42, "W", (N, K), 0.05)
+    bias, gate = rnd(43, "b", (N,), 0.5), synth.gaussian(44, "g", 3 * N).astype(np.float32).reshape(3, N)
+    x0 = synth.gaussian(45, "x", M * N).astype(np.float32).reshape(M, N)
+    row_req = (np.arange(M) * 3 // M).astype(np.int32)
+    Wp = np.zeros(((N + 255) // 256 * 256, K), np.float32); Wp[:N] = W
+    dA, dW = to_dev_bf16(torch, A), to_dev_bf16(torch, Wp)
+    dg, db, dr = torch.from_numpy(gate).cuda(), torch.from_numpy(bias).cuda(), torch.from_numpy(row_req).cuda()
+    bm, bn = variant // 1000 % 1000, variant % 1000
+    wb = ((M + bm - 1) // bm) * ((N + bn - 1) // bn) * splits * bm * bn * 4
+    work = torch.empty(wb, dtype=torch.uint8, device="cuda")
+    prod = A.astype(np.float64) @ W.astype(np.float64).T + bias
+    mag = np.abs(A).astype(np.float64) @ np.abs(W).astype(np.float64).T + np.abs(bias)
+    err32 = (K + splits) * 2.0 ** -24
+    ldc = (N + 7) // 8 * 8
+    call = lambda out, kind, wbytes=wb, v=variant: B.dit_op_gemm_splitk_variant(
+        None, dA.data_ptr(), K, dW.data_ptr(), K, db.data_ptr(), M, N, K, kind, out.data_ptr(), ldc,
+        dg.data_ptr() if kind == 3 else None, N, dr.data_ptr() if kind == 3 else None, splits, work.data_ptr(), wbytes, v)
+    for kind in (0, 1, 2, 3):
+        outs = []
+        for rep in range(2):
+            work.fill_(0xFF)
+            out = torch.full((M, ldc), float("nan"), dtype=torch.float32 if kind in (1, 3) else torch.bfloat16, device="cuda")
+            if kind == 3:
+                out[:, :N] = torch.from_numpy(x0).cuda()
+            assert call(out, kind) == 0
+            torch.cuda.synchronize()
+            assert torch.isnan(out[:, N:]).all()           # nothing is written past the last column
+            outs.append(out[:, :N].to(torch.float32).cpu().numpy())
+        assert np.array_equal(outs[0], outs[1])
+        g = gate[row_req].astype(np.float64)
+        want = {0: prod, 1: prod, 2: O.gelu_tanh(prod), 3: x0 + g * prod}[kind]
+        bound = err32 * mag
+        if kind in (0, 2):                                 # (the GELU's slope is at most 1.13)
+            bound = 1.13 * bound + (2.0 ** -8 + 4 * 2.0 ** -24) * np.abs(want) + 2.0 ** -24 * mag
+        elif kind == 3:
+            bound = np.abs(g) * bound + 2 * 2.0 ** -24 * (np.abs(x0) + np.abs(g * prod))
+        worst = (np.abs(outs[0] - want) / bound).max()
+        assert worst <= 1, (kind, worst)
+    assert call(out, 0, wb - 1) == 3                       # too little scratch
+    assert call(out, 0, wb, 30064064) == 1                 # not a split form
 
 
 @pytest.mark.parametrize("M,d,dh,parts", [(300, 256, 64, "qkv"), (517, 512, 128, "qkv"), (70, 256, 128, "q"),
