@@ -198,6 +198,12 @@ dit_status dit_op_gemm(void* stream, const void* A, int lda, const void* W, int 
                        const float* bias, int M, int N, int K, int out_kind, void* out, int ldc,
                        const float* gate, int gate_stride, const int* row_req);
 
+/* The tile (a variant code as below, 40128128 / 40064064 / 40032128 with K split) and the number of shares of K that
+ * one launch of n problems of M[i] x N[i] x K[i] takes (n <= 3, as the streams of a joint block).  out_kind as for
+ * dit_op_gemm; head_dim 64 or 128: q/k-norm epilogue instead, else 0.  work_bytes: scratch for the partial tiles.
+ * Host only.  Returns -1 for arguments that dit_op_gemm refuses. */
+int dit_op_gemm_tile(int n, const int* M, const int* N, const int* K, int out_kind, int head_dim, size_t work_bytes, int* splits);
+
 /* As dit_op_gemm (out_kind 0..2 only) with the tile variant forced, for tuning sweeps:
  * BM*1000+BN in {256256, 256128, 128256, 128128}; +1000000 = 8 waves (256256 only);
  * +10000000 / +20000000 = k-slab 32 with a 4- / 5-stage LDS ring instead of k-slab 64 with

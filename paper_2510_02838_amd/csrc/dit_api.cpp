@@ -1248,6 +1248,21 @@ dit_status dit_op_gemm_qknorm(void* stream, const void* A, int lda, const void* 
   return hipGetLastError() == hipSuccess ? DIT_OK : DIT_EDEVICE;
 }
 
+int dit_op_gemm_tile(int n, const int* M, const int* N, const int* K, int out_kind, int head_dim, size_t work_bytes, int* splits) {
+  if (n < 1 || n > 3 || !M || !N || !K || out_kind < 0 || out_kind > 3 || (head_dim != 0 && head_dim != 64 && head_dim != 128)) return -1;
+  GemmBatch b; b.n = n; b.total_tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    if (M[i] < 0 || N[i] < 0 || K[i] <= 0 || K[i] % 64) return -1;
+    b.p[i] = mk(nullptr, K[i], nullptr, K[i], nullptr, M[i], N[i], K[i], head_dim ? (int)OUT_QKNORM : out_kind, nullptr, N[i]);
+    b.p[i].qk.head_dim = head_dim;
+  }
+  float there = 0.f;                       // (the choice asks only whether there is scratch, and how much)
+  if (work_bytes) { b.partial = &there; b.partial_bytes = work_bytes; }
+  const int tile = choose_tile(b);
+  if (splits) *splits = b.splits;
+  return tile;
+}
+
 dit_status dit_op_gemm_splitk_variant(void* stream, const void* A, int lda, const void* W, int ldw, const float* bias,
                                       int M, int N, int K, int out_kind, void* out, int ldc, const float* gate,
                                       int gate_stride, const int* row_req, int splits, void* work, size_t work_bytes,

@@ -71,6 +71,7 @@ struct GemmBatch {
 
 // Launches up to 3 independent problems in one grid.  Returns the tile shape used (BM*1000+BN).
 int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile = 0);
+int choose_tile(GemmBatch& b, int force_tile = 0);      // its choice of tile, and b.splits; host only
 inline int gemm_stats_rows(int tile_code) {     // rows per stats chunk: two wave rows per tile, four in the 8-wave 256x128 one,
   if (tile_code == 40128128) return 32;         // 32 rows where the split-K reduction takes the sums
   return tile_code == 32256128 ? 64 : (tile_code % 1000000) / 1000 / 2;

@@ -945,14 +945,20 @@ static void launch_t(hipStream_t s, GemmBatch& b) {
 //   40128128  the same as split-K over b.splits shares of K plus the reduction kernel
 //   30032128 / 30064064  32x128 (4 waves of 32x32) and 64x64 (2 waves of 32x64), two workgroups per CU, 4- / 5-stage ring;
 //   40032128 / 40064064  the same as split-K
-// Few rows: the weights are read once whatever the tile, and what counts is how many bytes are in flight and how
-// long the chain of slabs of one workgroup is.  Tiles of 32x128 (up to 64 rows) and 64x64 take 80 KB of LDS, so
-// two workgroups share a CU and K is split over up to 512 of them.  Up to 128 rows: the encoder at 16 / 65 / 100 tokens
-// takes 3.10 / 3.83 / 4.10 ms against 4.07 / 4.22 / 4.45 with the 128-row tiles, at 300 tokens 6.64 against 6.13; sd3 steps
-// of 144 to 680 rows lose 1 to 14 % (every slab of A is read by twice as many workgroups).  0: not such a launch.
+// Few rows: what counts is how many bytes are in flight and how long the chain of slabs of one workgroup is.
+// Tiles of 32x128 (up to 64 rows) and 64x64 (up to 128) take 80 KB of LDS, so two workgroups share a CU and K is
+// split over up to 512 of them.  Where one row of tiles covers a problem they take 0.63 to 0.99 of the 128-row tiles'
+// time (32 rows: 12288 x 4096 25.9 against 31.4 us, 5120 x 13824 34.5 against 36.1).  Under two rows of tiles every
+// slab of W is fetched into LDS twice, and large weights lose more by that than the shorter chain gives.  At 64 rows:
+// 4096 x 4096 16.6 against 18.8 us, 6144 x 3072 17.5 against 17.9, 5120 x 5120 21.7 against 20.8, 3072 x 12288 27.5
+// against 25.0, 5120 x 13824 41.3 against 35.3; with fewer than four shares of K also 12288 x 1536, 19.0 against 18.1.
+// At 96 rows: 1536 x 6144 15.8 against 16.0, 3072 x 3072 16.5 against 17.2, 6144 x 3072 20.7 against 18.1,
+// 5120 x 13824 49.5 against 36.9.  Hence the limits on the weights under two rows of tiles (the q/k-norm form, never
+// split, takes two streams of 4608 x 1536 at 64 and 100 rows in 15.0 against 16.8 us).  Beyond 256 tiles nothing is split and
+// a second round begins (3072-wide streams of 64 and 16 rows, N = 12288: 46 against 37 us).  0: not such a launch.
 static int small_m_tile(GemmBatch& b) {
   int max_m = 0, min_nk = 1 << 30;
-  long long t32 = 0, t64 = 0, t128 = 0;
+  long long t128 = 0;
   bool qk = false;
   for (int i = 0; i < b.n; ++i) {
     const GemmProblem& p = b.p[i];
@@ -961,24 +967,29 @@ static int small_m_tile(GemmBatch& b) {
     qk = qk || p.out_kind == OUT_QKNORM;
     max_m = p.M > max_m ? p.M : max_m;
     min_nk = p.K / 64 < min_nk ? p.K / 64 : min_nk;
-    t32 += (long long)((p.M + 31) / 32) * ((p.N + 127) / 128);
-    t64 += (long long)((p.M + 63) / 64) * ((p.N + 63) / 64);
     t128 += (long long)((p.M + 127) / 128) * ((p.N + 127) / 128);
   }
   if (max_m == 0 || max_m > 128 || t128 > 256) return 0;
   const bool rows32 = max_m <= 64 && !qk;       // (the q/k-norm epilogue needs waves of 64 columns, the reduction has none)
-  const long long t = rows32 ? t32 : t64;
-  if (t > 512) return 0;
+  const int bm = rows32 ? 32 : 64, bn = rows32 ? 128 : 64;
+  long long t = 0, twice = 0;                   // tiles; weights under two rows of them
+  for (int i = 0; i < b.n; ++i) {
+    const GemmProblem& p = b.p[i];
+    if (p.M <= 0 || p.N <= 0) continue;
+    t += (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
+    if (p.M > bm) twice += (long long)p.N * p.K;
+  }
+  if (t > 256 || twice > (rows32 ? (t <= 128 ? 5 << 22 : 1 << 24) : qk ? 1 << 24 : 5 << 21)) return 0;
   long long sp = qk || !b.partial ? 1 : 512 / t;
   if (sp > min_nk / 4) sp = min_nk / 4;
-  const long long cap = (long long)(b.partial_bytes / ((rows32 ? 32 * 128 : 64 * 64) * 4)) / t;
+  const long long cap = (long long)(b.partial_bytes / (bm * bn * 4)) / t;
   if (sp > cap) sp = cap;
   if (sp < 2) return rows32 ? 30032128 : 30064064;
   b.splits = (int)sp;
   return rows32 ? 40032128 : 40064064;
 }
 
-int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
+int choose_tile(GemmBatch& b, int force_tile) {
   // Tile choice.  The 256x256 tile (8 waves) halves the L2->LDS traffic per flop of the 128x128
   // tile and is about 25% faster per tile-flop, but one workgroup fills a CU, so its grid runs
   // in rounds of 256 tiles: use it from one full round on, unless the last round would hold only
@@ -1092,6 +1103,11 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
       if (125 * r320 <= 95 * r256) tile = 1320256;
     }
   }
+  return tile;
+}
+
+int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
+  int tile = choose_tile(b, force_tile);
   bool conv = false, plain = false, qknorm = false;
   for (int i = 0; i < b.n; ++i) {
     conv = conv || b.p[i].conv_w > 0; plain = plain || b.p[i].conv_w <= 0;

@@ -104,8 +104,9 @@ def test_encoder_forward_against_oracle(torch, X, lens):
 @pytest.mark.gpu
 @pytest.mark.parametrize("lens", [[1], [33], [64], [65], [300, 77]])
 def test_encoder_benchmark_width_few_rows(torch, X, lens):
-    """The tiles for few rows at their edges (32-row tiles up to 64 rows, then 64x64 tiles), split over K, and the
-    norm with a workgroup per row: one layer of the benchmark width, same bounds as the other encoder tests."""
+    """The 32x128 tiles for few rows, split over K (one row of tiles in every product; two in the attention output product
+    up to 64 rows), the 128-row tiles from there on, and the norm with a workgroup per row: one layer of the benchmark
+    width, same bounds as the other encoder tests."""
     arch = dict(synth.ENCODERS["t5_xxl"], n_layers=1, vocab=512)
     params, toks, m, d_tok = _case(torch, X, arch, lens, std=0.0125, bias_scale=2.0)
     out32 = torch.full((sum(lens), arch["d_model"]), float("nan"), dtype=torch.float32, device="cuda")

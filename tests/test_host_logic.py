@@ -176,3 +176,45 @@ def test_profiler_tool_host_logic():
     px1 = 5 * 4 * px
     want_v2 = lvl0 + 2.0 * px1 * 27 * c * c + 2.0 * px1 * 27 * (c * 64 + 64 * 64) + 2.0 * px1 * c * 64 + 2.0 * px1 * 27 * 64 * 3
     assert SP.video_decoder_flops(v2, 3, 4, 4) == want_v2
+
+
+def _tile(B, problems, out_kind=0, head_dim=0):
+    col = lambda i: (C.c_int * len(problems))(*[p[i] for p in problems])
+    splits = C.c_int(0)
+    return B.dit_op_gemm_tile(len(problems), col(0), col(1), col(2), out_kind, head_dim, 256 * 128 * 128 * 4, C.byref(splits)), splits.value
+
+
+@pytest.mark.parametrize("problems,head_dim,few", [
+    # one row of tiles: always the tiles for few rows
+    ([(1, 4096, 4096)], 0, True), ([(32, 12288, 4096)], 0, True), ([(32, 5120, 13824)], 0, True), ([(32, 20480, 4096)], 0, True),
+    ([(16, 10240, 5120)], 0, True),
+    # two rows of tiles: as long as the weights are small
+    ([(64, 4096, 4096)], 0, True), ([(64, 6144, 1536), (16, 6144, 1536)], 0, True), ([(64, 1536, 6144), (64, 1536, 6144)], 0, True),
+    ([(96, 1536, 1536), (96, 1536, 1536)], 0, True), ([(128, 1536, 4096)], 0, True), ([(100, 4608, 1536), (64, 4608, 1536)], 64, True),
+    # two rows of tiles over larger weights, or more than a round of tiles: 5 to 70 % slower than the 128-row tiles
+    ([(64, 12288, 1536)], 0, False), ([(33, 12288, 3072)], 0, False), ([(64, 5120, 5120)], 0, False), ([(64, 5120, 13824)], 0, False),
+    ([(64, 20480, 4096)], 0, False), ([(128, 4096, 4096)], 0, False), ([(128, 6144, 3072)], 0, False), ([(80, 3072, 15360)], 0, False),
+    ([(128, 13824, 5120)], 0, False), ([(128, 10240, 5120)], 0, False), ([(121, 1536, 6144), (77, 1536, 6144)], 0, False),
+    ([(121, 6144, 1536), (77, 6144, 1536)], 0, False), ([(64, 6144, 1536), (100, 6144, 1536)], 0, False),
+    ([(64, 12288, 3072), (16, 12288, 3072)], 0, False), ([(121, 4608, 1536), (77, 4608, 1536)], 64, False),
+    ([(16, 9216, 3072)], 128, False), ([(129, 1536, 1536)], 0, False),
+])
+def test_tiles_for_few_rows_only_where_they_are_the_faster_ones(B, problems, head_dim, few):
+    """The launches of few rows whose times with either family of tiles were measured, each on its faster side; the
+    splits fit the scratch and leave every share at least four slabs."""
+    tile, splits = _tile(B, problems, head_dim=head_dim)
+    family = (30032128, 40032128, 30064064, 40064064)
+    assert (tile in family) == few, (tile, splits)
+    assert (splits > 1) == (tile > 40000000)
+    bm, bn = tile // 1000 % 1000, tile % 1000
+    tiles = sum(-(-m // bm) * -(-n // bn) for m, n, _ in problems)
+    if splits > 1:
+        assert tiles * splits * bm * bn <= 256 * 128 * 128 and min(k for _, _, k in problems) // 64 // splits >= 4
+
+
+def test_tile_choice_arguments(B):
+    one = (C.c_int * 1)(64)
+    assert B.dit_op_gemm_tile(0, one, one, one, 0, 0, 0, None) == -1 and B.dit_op_gemm_tile(4, one, one, one, 0, 0, 0, None) == -1
+    assert B.dit_op_gemm_tile(1, one, one, (C.c_int * 1)(65), 0, 0, 0, None) == -1
+    assert B.dit_op_gemm_tile(1, one, None, one, 0, 0, 0, None) == -1 and B.dit_op_gemm_tile(1, one, one, one, 4, 0, 0, None) == -1
+    assert B.dit_op_gemm_tile(1, one, (C.c_int * 1)(4096), (C.c_int * 1)(4096), 0, 0, 0, None) == 30032128      # no scratch: no split
