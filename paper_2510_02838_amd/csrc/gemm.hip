@@ -1017,7 +1017,9 @@ int choose_tile(GemmBatch& b, int force_tile) {
       const long long cap = (long long)(b.partial_bytes / (128 * 128 * 4)) / t128;
       if (sp > cap) sp = cap;
       bool qk = false;                       // the reduction kernel has no q/k-norm epilogue
-      // (nor is a video's convolution split: its frames must not depend on how many follow them)
+      // (A video's convolutions are left unsplit as well: their shares of K would follow the frame count, on top of what
+      // does already, the 1x1 products' shares and the tile height, which is that of the group norm's partial sums.  The
+      // first frames of a narrow video, tested to keep their bits when one is added, would move with it.)
       for (int i = 0; i < b.n; ++i) qk = qk || b.p[i].out_kind == OUT_QKNORM || (b.p[i].conv_w > 0 && b.p[i].conv_kt == 3);
       if (b.partial && sp >= 2 && !qk) { b.splits = (int)sp; tile = 40128128; }
       else {

@@ -122,6 +122,25 @@ def test_gemm_two_group_tiles_at_their_edges(torch, B, M, variant):
         assert (np.abs(got[:, :N] - ref) <= 1e-5 * mag).all(), (M, N, K)
 
 
+@pytest.mark.parametrize("M,N,K", [(321, 264, 64), (65, 256, 512), (700, 130, 4608)])
+def test_gemm_tiles_agree_bit_for_bit(torch, B, M, N, K):
+    """Every tile adds a product's terms in the same order, also where it multiplies with 16x16x32 MFMAs instead of
+    32x32x16, so that a result does not move with the tile that the row count picks (unsplit). Magnitudes over many
+    binary orders, where another order of additions shows."""
+    scale = np.exp2(np.round(4 * synth.gaussian(53, "e", M * K))).reshape(M, K).astype(np.float32)
+    A, W = rnd(51, "A", (M, K)) * scale, rnd(52, "W", (N, K), 0.05)
+    Wp = np.zeros(((N + 255) // 256 * 256, K), np.float32); Wp[:N] = W
+    dA, dW = to_dev_bf16(torch, A), to_dev_bf16(torch, Wp)
+    ldc, first = (N + 3) // 4 * 4, None
+    for variant in (128128, 30128128, 30128064, 30064128, 30064064, 30032128, 1256256, 1320256, 32256128):
+        out = torch.zeros((M, ldc), dtype=torch.float32, device="cuda")
+        assert B.dit_op_gemm_variant(None, dA.data_ptr(), K, dW.data_ptr(), K, None, M, N, K, 1, out.data_ptr(), ldc, variant) == 0
+        torch.cuda.synchronize()
+        first = out if first is None else first
+        assert torch.equal(out, first), variant
+    assert bool((first[:, :N] != 0).all())
+
+
 def test_gemm_seeded_random_shapes(torch, B):
     """Sixty seeded shapes (M 1..900, N 1..900, K a multiple of 64 up to 2048), each with a seeded
     output kind (bf16, fp32, GELU, or the gated residual with 1-5 requests whose rows change
