@@ -186,7 +186,9 @@ void plan(const dec_ctx* c, int n, int h, int w, Layout& L) {
   L.vt = take(rup(C0, 256) * rup(L.P0, 64) * 2);            // read as a second operand: rows up to a multiple of 256
   L.sc = take((size_t)L.P0 * L.P0 * 4);
   L.pm = take((size_t)L.P0 * rup(L.P0, 64) * 2);
-  // channel sums per chunk of 64 pixels at least (the smallest wave height of a product tile)
+  // channel sums per chunk of 64 pixels, the smallest wave height of an unsplit product's tile.  A split product leaves
+  // them per 32 pixels: in decoders of several levels they fit beside the final image's chunks; where they do not (a
+  // single wide level beyond 256 pixels) conv3() leaves the product unsplit, and the workspace keeps its size.
   L.gnp_bytes = std::max(group_norm_partial_bytes((long long)L.n_out * L.Hf * L.Wf, 1024), max_x / 64 * 8 + 2 * 1024 * 8);
   L.gnp = take(L.gnp_bytes);
   L.gst = take(GN_STATS_BYTES);
@@ -233,7 +235,7 @@ struct Fwd {
     p.conv_w = W; p.conv_cin = t->cin_pad; p.conv_img = H * W; p.conv_kt = kt;
     const bool want = sums && (kind == OUT_F32 || kind == OUT_RESID_F32);   // a group norm reads `out` next
     if (want) p.stats = at<float>(L.gnp);
-    // (a split product leaves sums per 32 rows, whole 128-row tiles: only where they fit)
+    // (a split product leaves sums per 32 rows of whole 128-row tiles, plan() sizes the scratch for 64: only where they fit)
     const int tile = gemm({p}, !want || ((size_t)p.M + 127) / 128 * 4 * p.N * 8 <= L.gnp_bytes);
     if (want) {
       const int rows = gemm_stats_rows(tile);

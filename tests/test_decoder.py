@@ -208,6 +208,24 @@ def test_decoder_wide_configuration_against_oracle(torch, X):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("h,w", [(8, 8), (16, 16), (16, 24), (24, 32)])
+def test_decoder_with_one_wide_level_against_oracle(torch, X, h, w):
+    """One level of 512 channels: its convolutions are split over K as long as the per-32-row sums of the group norm
+    fit the scratch (8x8, and 16x16 to the byte) and not from there on (16x24, 24x32)."""
+    arch = dict(latent_ch=16, out_ch=3, channels=(512,), n_res=1)
+    params = _params(arch, seed=6)
+    z = _latent(arch, h, w)
+    m, got, taps = _run(torch, X, arch, params, z, ["mid.res0", "up0"])
+    ref_taps = {}
+    ref = D.DecoderOracle(arch, params).forward(np.transpose(z, (1, 2, 0)), ref_taps)
+    for name, tol in (("mid.res0", 1e-2), ("up0", 2e-2)):
+        r = ref_taps[name].reshape(-1, 512)
+        assert rel_l2(taps[name], r) <= tol, (name, rel_l2(taps[name], r))
+    _check_image(got, ref)
+    m.close()
+
+
+@pytest.mark.gpu
 def test_decoder_mid_attention_over_thousands_of_pixels(torch, X):
     """5184 latent pixels: the score and weighted-sum products span many tiles with a ragged last
     one, and the softmax rows take the wide register-resident path (more than 4096 columns)."""
