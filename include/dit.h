@@ -262,6 +262,17 @@ dit_status dit_op_gemm_splitk_static(void* stream, const void* A, int lda, const
                                      void* out, int ldc, const float* gate, int gate_stride,
                                      const int* row_req, int splits);
 
+/* 3x3 convolution as the Decode stage runs it: `images` channels-last bf16 images with a one-pixel border each,
+ * [(H+2)*(W+2)][cin] back to back (cin a multiple of 64, the border as it is stored); Wt: dev bf16 [cout_pad][ldw],
+ * input index (3*ky + kx)*cin + c, cout_pad a multiple of 256 rows readable; bias dev float32 [cout] or NULL.
+ * out_kind 1: float32 [images*H*W][ldc];  3: added to it.  sums (may be NULL): dev float32 [chunk][cout][2], per output
+ * column the sum and the sum of squares of the stored values over chunks of consecutive rows, their height returned
+ * in *chunk_rows; sums_bytes at least ceil(images*H*W / 256) * 8 * cout * 8.  variant: 0 (the library's choice),
+ * 128128, 30128128, 1256256, 32256128, or 40128128 with `splits` shares of K and the scratch of dit_op_gemm_splitk. */
+dit_status dit_op_conv3(void* stream, const void* img, int images, int H, int W, int cin, const void* Wt, int ldw,
+                        const float* bias, int cout, int out_kind, void* out, int ldc, float* sums, size_t sums_bytes,
+                        int variant, int splits, void* work, size_t work_bytes, int* chunk_rows);
+
 /* Flash-style attention over packed segments: softmax(Q K^T / sqrt(dh)) V per segment and
  * head, no other mask.  q: dev bf16 rows [Nq][H*dh] with row stride ldq (elements); k likewise
  * [Nk] rows; vt: dev bf16 [H][dh][ldvt], the transposed values, segment s occupying columns

@@ -1332,6 +1332,34 @@ dit_status dit_op_gemm_variant(void* stream, const void* A, int lda, const void*
   return hipGetLastError() == hipSuccess ? DIT_OK : DIT_EDEVICE;
 }
 
+dit_status dit_op_conv3(void* stream, const void* img, int images, int H, int W, int cin, const void* Wt, int ldw,
+                        const float* bias, int cout, int out_kind, void* out, int ldc, float* sums, size_t sums_bytes,
+                        int variant, int splits, void* work, size_t work_bytes, int* chunk_rows) {
+  if (!img || !Wt || !out || (sums && !chunk_rows)) return DIT_EINVAL;
+  if (variant != 0 && variant != 128128 && variant != 30128128 && variant != 1256256 && variant != 32256128 && variant != 40128128)
+    return DIT_EINVAL;
+  if (out_kind != OUT_F32 && out_kind != OUT_RESID_F32) return DIT_EINVAL;
+  if (images < 1 || H < 1 || W < 1 || cin < 64 || cin % 64 || cout < 1 || ldw < 9LL * cin || ldw % 8 || ldc < cout || ldc % 4 ||
+      ((uintptr_t)out & 15)) return DIT_ESHAPE;
+  // (32-bit byte offsets inside an image, 32-bit rows)
+  if ((H + 2LL) * (W + 2LL) * cin >= (1LL << 30) || (long long)images * H * W >= (1LL << 29)) return DIT_ESHAPE;
+  const int M = images * H * W;
+  if (sums && sums_bytes < (size_t)((M + 255) / 256) * 8 * cout * 8) return DIT_ENOMEM;
+  GemmBatch b; b.n = 1; b.total_tiles = 0;
+  b.p[0] = mk((const bf16_t*)img, cin, (const bf16_t*)Wt, ldw, bias, M, cout, 9 * cin, out_kind, out, ldc);
+  b.p[0].conv_w = W; b.p[0].conv_cin = cin; b.p[0].conv_img = H * W; b.p[0].stats = sums;
+  if (variant == 40128128) {
+    if (!work || ((uintptr_t)work & 15)) return DIT_EINVAL;
+    if (splits < 1 || splits > 9 * cin / 64) return DIT_ESHAPE;
+    if (work_bytes < (size_t)((M + 127) / 128) * ((cout + 127) / 128) * splits * (128 * 128 * 4)) return DIT_ENOMEM;
+    b.splits = splits; b.partial = (float*)work; b.partial_bytes = work_bytes;
+  }
+  const int tile = launch_gemm((hipStream_t)stream, b, variant);
+  if (tile < 0) return DIT_ESHAPE;
+  if (chunk_rows) *chunk_rows = gemm_stats_rows(tile);
+  return hipGetLastError() == hipSuccess ? DIT_OK : DIT_EDEVICE;
+}
+
 size_t dit_op_attention_work_bytes(int n_seg, const int* cu_q) {
   if (n_seg <= 0 || !cu_q) return 0;
   size_t tiles = 0;

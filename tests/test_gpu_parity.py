@@ -141,6 +141,48 @@ def test_gemm_tiles_agree_bit_for_bit(torch, B, M, N, K):
     assert bool((first[:, :N] != 0).all())
 
 
+@pytest.mark.parametrize("variant,chunk,splits", [(128128, 64, 0), (30128128, 64, 0), (1256256, 128, 0), (32256128, 64, 0),
+                                                  (40128128, 32, 4), (40128128, 32, 9)])
+@pytest.mark.parametrize("images,H,W,cin,cout", [(1, 20, 17, 64, 130), (2, 16, 16, 128, 128), (1, 40, 24, 64, 264), (1, 1, 5, 64, 64)])
+def test_convolution_and_its_column_sums(torch, B, images, H, W, cin, cout, variant, chunk, splits):
+    """3x3 convolution in every form the decoders take (tiles that end inside an image, several images, ragged columns,
+    K in shares of unequal length), overwriting and adding, against the float64 convolution: a chain of 9*cin + splits
+    float32 additions. The sums that the epilogue or the split reduction leaves for the group norm, against the
+    float64 sums of the values stored: 128 additions at most. All scratch starts as NaN."""
+    x = rnd(61, "x", (images, H + 2, W + 2, cin))
+    x[:, 0] = x[:, -1] = 0; x[:, :, 0] = x[:, :, -1] = 0
+    Wt, bias = rnd(62, "W", (cout, 9 * cin), 0.05), rnd(63, "b", (cout,), 0.5)
+    Wp = np.zeros(((cout + 255) // 256 * 256, 9 * cin), np.float32); Wp[:cout] = Wt
+    dx, dW, db = to_dev_bf16(torch, x), to_dev_bf16(torch, Wp), torch.from_numpy(bias).cuda()
+    M, ldc = images * H * W, (cout + 3) // 4 * 4
+    col = np.concatenate([x[:, ky:ky + H, kx:kx + W] for ky in range(3) for kx in range(3)], axis=3).reshape(M, 9 * cin).astype(np.float64)
+    prod, mag = col @ Wt.T.astype(np.float64) + bias, np.abs(col) @ np.abs(Wt.T).astype(np.float64) + np.abs(bias)
+    x0 = synth.gaussian(64, "r", M * cout).astype(np.float32).reshape(M, cout)
+    wb = ((M + 127) // 128) * ((cout + 127) // 128) * max(splits, 1) * 65536
+    work = torch.empty(wb, dtype=torch.uint8, device="cuda")
+    n_chunks = (M + 255) // 256 * 8
+    for kind in (1, 3):
+        work.fill_(0xFF)
+        sums = torch.full((n_chunks, cout, 2), float("nan"), dtype=torch.float32, device="cuda")
+        out = torch.full((M, ldc), float("nan"), dtype=torch.float32, device="cuda")
+        if kind == 3:
+            out[:, :cout] = torch.from_numpy(x0).cuda()
+        rows = C.c_int(0)
+        assert B.dit_op_conv3(None, dx.data_ptr(), images, H, W, cin, dW.data_ptr(), 9 * cin, db.data_ptr(), cout, kind, out.data_ptr(), ldc,
+                              sums.data_ptr(), n_chunks * cout * 8, variant, splits, work.data_ptr() if splits else None, wb, C.byref(rows)) == 0
+        torch.cuda.synchronize()
+        assert rows.value == chunk and torch.isnan(out[:, cout:]).all()
+        got, base = out[:, :cout].cpu().numpy().astype(np.float64), (x0.astype(np.float64) if kind == 3 else 0.0)
+        assert (np.abs(got - (base + prod)) <= (9 * cin + splits + 2) * 2.0 ** -24 * (np.abs(base) + mag)).all()
+        s = sums.cpu().numpy().astype(np.float64)
+        for c in range(-(-M // chunk)):
+            v = got[c * chunk:(c + 1) * chunk]
+            assert (np.abs(s[c, :, 0] - v.sum(0)) <= chunk * 2.0 ** -24 * np.abs(v).sum(0)).all(), c
+            assert (np.abs(s[c, :, 1] - (v * v).sum(0)) <= (chunk + 1) * 2.0 ** -24 * (v * v).sum(0)).all(), c
+        tail = s[-(-M // chunk):]
+        assert ((tail == 0) | np.isnan(tail)).all()        # a tile's rows past the last: nothing, or zeros
+
+
 def test_gemm_seeded_random_shapes(torch, B):
     """Sixty seeded shapes (M 1..900, N 1..900, K a multiple of 64 up to 2048), each with a seeded
     output kind (bf16, fp32, GELU, or the gated residual with 1-5 requests whose rows change

@@ -136,6 +136,9 @@ def test_calls_fail_cleanly_without_buffers(B):
     assert B.dit_denoise_step(None, 1, reqs, 256, 256, s, s, 0, None) == 1
     assert B.dit_op_gemm(None, None, 0, None, 0, None, 1, 1, 64, 0, None, 1, None, 0, None) == 1
     assert B.dit_op_gemm(None, 256, 64, 256, 64, None, 4, 4, 65, 0, 256, 4, None, 0, None) == 2
+    conv = lambda cin=64, kind=1, variant=0, sums=None, n=0: B.dit_op_conv3(None, 256, 1, 8, 8, cin, 256, 9 * cin, None, 64, kind, 256, 64,
+                                                                            sums, n, variant, 1, None, 0, None)
+    assert conv(cin=96) == 2 and conv(kind=0) == 1 and conv(variant=256256) == 1 and conv(variant=40128128) == 1 and conv(sums=256, n=1 << 20) == 1
     assert B.dit_op_attention_work_bytes(0, None) == 0
     m.close()
 
