@@ -12,9 +12,9 @@
 // 16-byte slots of a 256-byte window; the key is (row >> 1) & 7 for 128-byte rows and
 // (row >> 2) & 3 for 64-byte rows).  A wave owns a (BM/WM) x (BN/WN) sub-tile made of 32x32
 // MFMA tiles (v_mfma_f32_32x32x16_bf16: 64 lanes, A operand = 32 rows x 16 k, B operand =
-// 16 k x 32 columns, each lane supplies 8 consecutive k).  MFMA rows are rows of A (tokens),
-// MFMA columns are rows of W (output features), so the 32 lanes of a half-wave write 32
-// consecutive output features of one token.
+// 16 k x 32 columns, each lane supplies 8 consecutive k), or of 16x16 ones
+// (v_mfma_f32_16x16x32_bf16) in the two-group forms.  MFMA rows are rows of A (tokens), MFMA
+// columns are rows of W (output features).
 //
 // Pipeline.  NS-1 slabs are in flight from global memory while one is computed: measured on
 // MI355X a 64 KB slab takes about 1.4 us from issue to landing, as long as its MFMA work, so
@@ -23,8 +23,8 @@
 // kk+1 are read from LDS.  The one barrier per slab sits before the slab's last k-step: by then every
 // wave holds the slab's last fragments in registers, so the slab's stage is free for the loads of
 // slab+NS, and the next slab becomes visible, so the last k-step already prefetches the next
-// slab's first fragments.  The 8-wave tiles alternate instead: four waves multiply while the other
-// four read and load (SCHED 4 and 5 below).
+// slab's first fragments.  The 8-wave tiles with a 64-wide slab alternate instead: four waves multiply
+// while the other four read and load (SCHED 4 and 5 below).
 //
 // Several problems (for example the text and the image stream of one joint block, which
 // have different weights) are launched as one grid.  Workgroup ids are first de-interleaved
@@ -150,7 +150,7 @@ __device__ __forceinline__ void tile_coords(const GemmProblem& P, int t, int& tm
 //   5  two groups, one phase per slab (256x128 tile, 8 waves)
 //      Forms 4 and 5 multiply with v_mfma_f32_16x16x32_bf16: the same cycles per flop as 32x32x16, but these
 //      kernels keep the matrix cores 90 % busy and the board then lowers its clock to what it can feed, and per
-//      flop the 16x16 form draws less (8192^3: 768 us with 32x32x16, 705 us with 16x16x32, nothing else changed).
+//      flop the 16x16 form draws less (8192^3: 768 us with 32x32x16, 714 us with 16x16x32, nothing else changed).
 template <int BM, int BN, int WM, int WN, int BKT, int NS, int MODE, bool CONV = false, int SCHED = 2>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batch) {
   constexpr int NT = WM * WN * 64;
@@ -233,6 +233,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
 
   // accumulators: one f32x16 per 32x32 tile, or its four 16x16 quarters (row-major) in forms 4 and 5
   constexpr bool M16 = SCHED >= 4;
+  static_assert(!(M16 && MODE == 4), "the split-K store below writes the 32x32 layout");
   f32x16 acc[M16 ? 1 : TM][M16 ? 1 : TN];
   f32x4 acc4[M16 ? TM : 1][M16 ? TN : 1][4];
   if constexpr (M16) {
@@ -473,7 +474,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   // acc_at(i, j, e) is C[32i + acc_row(e)][32j + acc_col(e)] of the wave's sub-tile: a lane
   // holds one or two columns, so direct stores would be 2- or 4-byte pieces.  Each wave therefore turns
   // its sub-tile 32 rows at a time through a private LDS patch (row stride TN*128 + 32 bytes:
-  // the two half-waves, 4 rows apart, then fall into disjoint bank halves) and reads it back
+  // the two half-waves, 4 rows apart, then fall into disjoint bank halves; the 16x16 layout stores rows
+  // 0, 4, 8 and 12 at a time, and 8 rows apart is the same bank, so its stores take two passes) and reads it back
   // row-major, 4 (fp32 out) or 8 (bf16 out) consecutive columns per lane: global accesses are
   // 16 bytes per lane and whole rows of the sub-tile per instruction.
   __syncthreads();     // every wave's ring loads have landed and all fragment reads are done
@@ -991,11 +993,14 @@ static int small_m_tile(GemmBatch& b) {
 
 int choose_tile(GemmBatch& b, int force_tile) {
   // Tile choice.  The 256x256 tile (8 waves) halves the L2->LDS traffic per flop of the 128x128
-  // tile and is about 25% faster per tile-flop, but one workgroup fills a CU, so its grid runs
+  // tile and takes 0.71 to 0.74 of its time where rounds are full (8192^3 709 against 964 us,
+  // 32760 x 5120 x 5120 1177 against 1605), but one workgroup fills a CU, so its grid runs
   // in rounds of 256 tiles: use it from one full round on, unless the last round would hold only
-  // a few tiles (measured over the benchmark shapes: a partly filled last round runs faster
-  // than a full one, lone tiles see less contention); otherwise the 128x128 tile (three
-  // workgroups per CU, finer granularity).
+  // a few tiles (a partly filled last round runs faster than a full one, lone tiles see less
+  // contention; 4250 x 4608 x 1536, 306 tiles: 71.1 us against 71.6 as 1224 of 128x128); otherwise the
+  // 128x128 tile (three workgroups per CU, finer granularity).  The thresholds were set when every wave
+  // interleaved its reads and products; the two-group loop has made the 8-wave tiles 6 to 17 % faster since, and
+  // a call that they keep on the 128x128 tile is as fast as it was.
   int tile = force_tile;
   if (tile > 40000000 && (!b.partial || b.splits < 1)) tile -= 10000000;   // no scratch: no split
   if (tile < 40000000) b.splits = 1;
@@ -1047,8 +1052,8 @@ int choose_tile(GemmBatch& b, int force_tile) {
   }
   if (!tile) {
     // One round of 256x128 tiles (8 waves, 3-stage ring) when that fits the chip and K is not short:
-    // a workgroup per CU with three slabs in flight, against 1.6 128x128 workgroups per CU (measured on the
-    // 4250-row request: 7 % faster at K = 6144, 3 % at K = 1536).
+    // a workgroup per CU with two slabs in flight, against 1.6 128x128 workgroups per CU (4250 rows, N = 1536:
+    // 74 against 85 us at K = 6144, 24.1 against 27.1 at K = 1536).
     long long t21 = 0;
     int min_k = 1 << 30;
     bool plain = true;
@@ -1082,19 +1087,19 @@ int choose_tile(GemmBatch& b, int force_tile) {
     const long long rem = t256 % 256;
     tile = (t256 >= 1024 || (t256 >= 256 && (rem == 0 || rem >= 64))) ? 1256256 : 128128;
     // Below one round of 256x256 tiles: a round of them does the work of two rounds of 128x128 pairs in about
-    // 1.67 times the time of one, so the big tile wins whenever the small one needs two rounds or more of its
-    // 512 slots (216 tiles of 256x256 against 864 of 128x128 at 4608 x 3072 x 15360: 350 against 410 us).
+    // 1.42 times the time of one, so the big tile wins whenever the small one needs two rounds or more of its
+    // 512 slots (216 tiles of 256x256 against 864 of 128x128 at 4608 x 3072 x 15360: 292 against 411 us).
     if (tile == 128128 && t256 < 256) {
       long long t128 = 0;
       for (int i = 0; i < b.n; ++i)
         t128 += (long long)((b.p[i].M + 127) / 128) * ((b.p[i].N + 127) / 128);
-      if (100 * ((t128 + 511) / 512) > 167) tile = 1256256;      // (t256 < 256: one round of the big tile)
+      if (100 * ((t128 + 511) / 512) > 142) tile = 1256256;      // (t256 < 256: one round of the big tile)
     }
     // A 320-row tile when it saves rounds: the 4250-row QKV product of the 1024^2 request is 306 tiles of
-    // 256x256 (a second round for 50 tiles) but 252 of 320x256, one round of tiles 1.25 times as long (measured
-    // 56 us against 71 us with 128x128 tiles and 77 us with 256x256); 864 tiles (4 rounds) against 720 (3 rounds
-    // x 1.25) measured 5 % faster.  Per unit of work the two tiles are equally fast at K <= 5120, so the rule is
-    // rounds alone, with a margin.
+    // 256x256 (a second round for 50 tiles) but 252 of 320x256, one round of tiles 1.25 times as long (52 us
+    // against 71 us with 128x128 and with 256x256 tiles); 864 tiles (4 rounds) against 720 (3 rounds x 1.25):
+    // 252 against 267 us at 4608 x 12288 x 3072.  Per unit of work it is 3 to 12 % slower (18384 x 6144 x 1536 279
+    // against 271 us, 8192^3 797 against 709), of which the rule, rounds alone, has 5 % as its margin.
     bool any_conv = false;                  // (convolutions have no 320-row instantiation)
     for (int i = 0; i < b.n; ++i) any_conv = any_conv || b.p[i].conv_w > 0;
     if (t256 > 256 && !any_conv) {
