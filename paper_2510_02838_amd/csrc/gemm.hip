@@ -955,8 +955,9 @@ static void launch_t(hipStream_t s, GemmBatch& b) {
 // 4096 x 4096 16.6 against 18.8 us, 6144 x 3072 17.5 against 17.9, 5120 x 5120 21.7 against 20.8, 3072 x 12288 27.5
 // against 25.0, 5120 x 13824 41.3 against 35.3; with fewer than four shares of K also 12288 x 1536, 19.0 against 18.1.
 // At 96 rows: 1536 x 6144 15.8 against 16.0, 3072 x 3072 16.5 against 17.2, 6144 x 3072 20.7 against 18.1,
-// 5120 x 13824 49.5 against 36.9.  Hence the limits on the weights under two rows of tiles (the q/k-norm form, never
-// split, takes two streams of 4608 x 1536 at 64 and 100 rows in 15.0 against 16.8 us).  Beyond 256 tiles nothing is split and
+// 5120 x 13824 49.5 against 36.9.  Hence the limits on the weights under two rows of tiles: 21 million at 32x128 with at
+// least four shares (up to 128 tiles), 17 million with fewer and in the q/k-norm form, which is never split (two streams of
+// 4608 x 1536 at 64 and 100 rows 15.0 against 16.8 us), 10.5 million at 64x64.  Beyond 256 tiles nothing is split and
 // a second round begins (3072-wide streams of 64 and 16 rows, N = 12288: 46 against 37 us).  0: not such a launch.
 static int small_m_tile(GemmBatch& b) {
   int max_m = 0, min_nk = 1 << 30;
