@@ -14,7 +14,7 @@
 // MFMA tiles (v_mfma_f32_32x32x16_bf16: 64 lanes, A operand = 32 rows x 16 k, B operand =
 // 16 k x 32 columns, each lane supplies 8 consecutive k), or of 16x16 ones
 // (v_mfma_f32_16x16x32_bf16) in the two-group forms.  MFMA rows are rows of A (tokens), MFMA
-// columns are rows of W (output features).
+// columns are rows of W (output features); the two-group forms have it the other way round.
 //
 // Pipeline.  NS-1 slabs are in flight from global memory while one is computed: measured on
 // MI355X a 64 KB slab takes about 1.4 us from issue to landing, as long as its MFMA work, so
@@ -24,7 +24,7 @@
 // wave holds the slab's last fragments in registers, so the slab's stage is free for the loads of
 // slab+NS, and the next slab becomes visible, so the last k-step already prefetches the next
 // slab's first fragments.  The 8-wave tiles with a 64-wide slab alternate instead: four waves multiply
-// while the other four read and load (SCHED 4 and 5 below).
+// while the other four read and load (gemm8_kernel below).
 //
 // Several problems (for example the text and the image stream of one joint block, which
 // have different weights) are launched as one grid.  Workgroup ids are first de-interleaved
@@ -124,7 +124,8 @@ __device__ __forceinline__ void buffer_load_lds16(const void* base, lptr_t dst, 
 }
 
 // tile t of a problem -> (tile row, tile column): groups of 8 tile rows, column-major inside
-__device__ __forceinline__ void tile_coords(const GemmProblem& P, int t, int& tm, int& tn) {
+template <class PROBLEM>
+__device__ __forceinline__ void tile_coords(const PROBLEM& P, int t, int& tm, int& tn) {
   constexpr int GM = 8;
   int per = GM * P.tiles_n;
   int g = t / per, r = t - g * per;
@@ -144,14 +145,7 @@ __device__ __forceinline__ void tile_coords(const GemmProblem& P, int t, int& tm
 // from the tile's first row (for a convolution: from that row's window) and never changing, the k advance
 // in an SGPR: no vector address arithmetic in the loop and a cheaper issue than global_load_lds with
 // 64-bit lane addresses (measured +2..7 %, convolutions +2.5 %).
-// SCHED: how the loop is laid out.
-//   2  k-steps of a slab in order, the barrier after the last fragment read
-//   4  two groups of waves half a phase apart, two phases per slab (256- and 320-row tiles, 8 waves)
-//   5  two groups, one phase per slab (256x128 tile, 8 waves)
-//      Forms 4 and 5 multiply with v_mfma_f32_16x16x32_bf16: the same cycles per flop as 32x32x16, but these
-//      kernels keep the matrix cores 90 % busy and the board then lowers its clock to what it can feed, and per
-//      flop the 16x16 form draws less (8192^3: 768 us with 32x32x16, 714 us with 16x16x32, nothing else changed).
-template <int BM, int BN, int WM, int WN, int BKT, int NS, int MODE, bool CONV = false, int SCHED = 2>
+template <int BM, int BN, int WM, int WN, int BKT, int NS, int MODE, bool CONV = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batch) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
@@ -185,20 +179,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
 
-  // One load of a wave fills RPL slab rows.  Form 4 fetches A in two parts, the first 64 rows of every
-  // wave's sub-tile and the rest; row_a: first of the rows that the wave's i-th load of A fills.
-  constexpr int RPL = 64 / CPR;
-  constexpr int LAU = SCHED == 4 ? WM * 64 * CPR / NT : LA;
-  auto row_a = [&](int i) {
-    if constexpr (SCHED == 4) {
-      const bool up = i < LAU;
-      const int per = up ? 64 : TM * 32 - 64;
-      const int rr = ((up ? i : i - LAU) * (WM * WN) + wave) * RPL;
-      return rr / per * (TM * 32) + rr % per + (up ? 0 : 64);
-    } else {
-      return (i * (WM * WN) + wave) * RPL;
-    }
-  };
+  constexpr int RPL = 64 / CPR;                        // slab rows that one load of a wave fills
 
   // ---- per-thread global source offsets ------------------------------------------------
   // (element offsets from the matrix base; every operand is far below 2^31 elements)
@@ -212,7 +193,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   }
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
-    const int r = row_a(i) + lane / CPR, pc = lane % CPR, c = pc ^ swz_key<BKT>(r);
+    const int r = (i * (WM * WN) + wave) * RPL + lane / CPR, pc = lane % CPR, c = pc ^ swz_key<BKT>(r);
     int m = m0 + r; if (m >= P.M) m = P.M - 1;            // clamp: rows past M are never stored
     if constexpr (CONV) {    // top-left pixel of the 3x3 window in the stack of bordered images
       const int b = m / P.conv_img, r = m - b * P.conv_img;
@@ -231,33 +212,16 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   }
 
 
-  // accumulators: one f32x16 per 32x32 tile, or its four 16x16 quarters (row-major) in forms 4 and 5
-  constexpr bool M16 = SCHED >= 4;
-  static_assert(!(M16 && MODE == 4), "the split-K store below writes the 32x32 layout");
-  f32x16 acc[M16 ? 1 : TM][M16 ? 1 : TN];
-  f32x4 acc4[M16 ? TM : 1][M16 ? TN : 1][4];
-  if constexpr (M16) {
+  f32x16 acc[TM][TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc4[i][j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  } else {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  }
-  // element e of tile (i, j) and its place in the 32x32 tile
-  auto acc_at = [&](int i, int j, int e) -> float {
-    if constexpr (M16) return acc4[i][j][e >> 2][e & 3];
-    else return acc[i][j][e];
-  };
-  auto acc_row = [&](int e) { return M16 ? 16 * (e >> 3) + 4 * (lane >> 4) + (e & 3) : 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); };
-  auto acc_col = [&](int e) { return M16 ? 16 * ((e >> 2) & 1) + (lane & 15) : lane & 31; };
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  // place of element e in its 32x32 tile
+  auto acc_row = [&](int e) { return 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); };
+  const int acc_col = lane & 31;
 
   int nk = P.K / BKT;
   int kb_conv = 0;              // first slab of my share of a convolution (its A offset is not linear in k)
@@ -282,8 +246,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   // A load's lanes land at LDS byte row*ROWB + lane*16 of their slab (row: its first).  Slab indices
   // past the end are clamped (the copy is redundant but keeps the load count per slab fixed,
   // which the vmcnt arithmetic below relies on).
-  auto issue_a = [&](int kt, auto first, auto last) {      // loads [first, last) of slab kt of A
+  auto issue = [&](int kt) {
     unsigned char* dA = smem + (kt % NS) * STAGE;
+    unsigned char* dB = dA + OFFB;
     const int ks = (kt < nk ? kt : nk - 1) * BKT;
     int ka = ks;             // A-side offset of the slab
     if constexpr (CONV) {    // slab = 64 channels of one tap (ky, kx): shift by ky rows and kx pixels
@@ -296,19 +261,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
       ka = ((kf * (P.conv_img / P.conv_w + 2) + ky) * (P.conv_w + 2) + kx) * P.conv_cin + c0;
     }
 #pragma unroll
-    for (int i = decltype(first)::value; i < decltype(last)::value; ++i)
-      buffer_load_lds16(tileA, (lptr_t)(dA + row_a(i) * ROWB), ga[i] * 2u, ka * 2);
-  };
-  auto issue_b = [&](int kt) {
-    unsigned char* dB = smem + (kt % NS) * STAGE + OFFB;
-    const int ks = (kt < nk ? kt : nk - 1) * BKT;
+    for (int i = 0; i < LA; ++i) buffer_load_lds16(tileA, (lptr_t)(dA + (i * NT + wave * 64) * 16), ga[i] * 2u, ka * 2);
 #pragma unroll
     for (int i = 0; i < LB; ++i) buffer_load_lds16(tileW, (lptr_t)(dB + (i * NT + wave * 64) * 16), gb[i] * 2u, ks * 2);
   };
-  constexpr std::integral_constant<int, 0> A_FIRST{};
-  constexpr std::integral_constant<int, LAU> A_REST{};
-  constexpr std::integral_constant<int, LA> A_END{};
-  auto issue = [&](int kt) { issue_a(kt, A_FIRST, A_END); issue_b(kt); };
   auto load_frags = [&](const unsigned char* st, int kk, bf16x8 (&a)[TM], bf16x8 (&b)[TN]) {
     const int c = kk * 2 + half;
     const unsigned char* pa = st + abase + ((c ^ akey) << 4);
@@ -319,7 +275,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
     for (int j = 0; j < TN; ++j) b[j] = *(const bf16x8*)(pb + j * 32 * ROWB);
   };
   auto mfma_all = [&](const bf16x8 (&a)[TM], const bf16x8 (&b)[TN]) {
-    if constexpr (!M16)
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -327,98 +282,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
   };
 
-  if constexpr (M16) {
-    // Two groups of four waves (wave / 4; each has one wave on every SIMD), half a phase apart: while one group's
-    // waves do nothing but multiply, the other's read the fragments of their next product and issue loads, so
-    // the matrix cores change hands at a barrier instead of idling while a wave waits for LDS (8192^3: 839 us with
-    // each wave interleaving reads and products, matrix cores 78 % busy; 768 us this way with the same MFMA form, 91 %).
-    //
-    // A group's reads are in registers before the barrier that ends its reading half, so what it read may be
-    // overwritten by loads of either group from its next phase on.  The wait at the end of a reading half covers
-    // the group's own loads of what the NEXT phase reads; the barriers in between make them visible to the other.
-    static_assert(WM * WN == 8 && BKT == 64 && TN == 2, "two groups of four waves, 64 columns a wave");
-    constexpr int RT = TM * 2, CT = TN * 2;                     // 16-row and 16-column tiles of the sub-tile
-    constexpr int PH = SCHED == 4 ? 2 : 1, RP = RT / PH;        // phases per slab, row tiles per phase
-    constexpr int KS = BKT / 32;
-    const int l16 = lane & 15, kq = lane >> 4;
-    const int fkey = swz_key<BKT>(l16);                         // (rows 16 apart have the same key)
-    const int fa0 = (wm * (BM / WM) + l16) * ROWB, fb0 = OFFB + (wn * (BN / WN) + l16) * ROWB;
-    bf16x8 fa[KS][RP], fb[KS][CT];
-    auto read_a = [&](const unsigned char* st, int phase) {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int r = 0; r < RP; ++r)
-          fa[ks][r] = *(const bf16x8*)(st + fa0 + (((ks * 4 + kq) ^ fkey) << 4) + (phase * RP + r) * 16 * ROWB);
-    };
-    auto read_b = [&](const unsigned char* st) {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int c = 0; c < CT; ++c) fb[ks][c] = *(const bf16x8*)(st + fb0 + (((ks * 4 + kq) ^ fkey) << 4) + c * 16 * ROWB);
-    };
-    auto multiply = [&](auto phase) {
-      wg_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int r = 0; r < RP; ++r)
-#pragma unroll
-          for (int c = 0; c < CT; ++c) {
-            constexpr int r0 = decltype(phase)::value * RP;
-            f32x4& d = acc4[(r0 + r) >> 1][c >> 1][((r0 + r) & 1) * 2 + (c & 1)];
-            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[ks][r], fb[ks][c], d, 0, 0, 0);
-          }
-      __builtin_amdgcn_s_setprio(0);
-      __builtin_amdgcn_sched_barrier(0);
-      wg_barrier();
-    };
-    const bool second = wave >= WM * WN / 2;
-    if constexpr (SCHED == 4) {
-      // phase 2kt reads the upper half of A and W of slab kt and issues the rest of A of slab kt+1 (over slab kt-1,
-      // last read one phase ago); phase 2kt+1 reads the lower half of A and issues W and the first part of A of slab kt+2.
-      // Where phase 0 reads none of the rest of A (256 rows), the rest has one phase more to arrive.
-      static_assert(NS == 2 && RP * 16 >= 64, "the first part of A is read in phase 0 alone");
-      constexpr bool LATE = RP * 16 == 64;
-      issue_b(0); issue_a(0, A_FIRST, A_END);
-      issue_b(1); issue_a(1, A_FIRST, A_REST);
-      wait_vm<LB + LAU, false>();
-      wg_barrier();
-      if (second) wg_barrier();
-      for (int kt = 0; kt < nk; ++kt) {
-        const unsigned char* cur = smem + (kt & 1) * STAGE;
-        read_b(cur);
-        read_a(cur, 0);
-        issue_a(kt + 1, A_REST, A_END);
-        wait_vm<LATE ? LPS : 63, true>();      // the rest of A of slab kt (mine; without LATE slab kt is complete already)
-        multiply(std::integral_constant<int, 0>{});
-        read_a(cur, 1);
-        issue_b(kt + 2); issue_a(kt + 2, A_FIRST, A_REST);
-        wait_vm<LATE ? LPS : LB + LAU, true>();// W and the first part of A of slab kt+1 (mine; without LATE all of it)
-        multiply(std::integral_constant<int, PH - 1>{});
-      }
-    } else {
-      // phase kt reads slab kt and issues slab kt+2 into the stage that slab kt-1 left
-      static_assert(NS == 3, "three stages");
-      issue(0); issue(1);
-      wait_vm<LPS, false>();
-      wg_barrier();
-      if (second) wg_barrier();
-      int st = 0;
-      for (int kt = 0; kt < nk; ++kt) {
-        const unsigned char* cur = smem + st * STAGE;
-        read_b(cur);
-        read_a(cur, 0);
-        issue(kt + 2);
-        wait_vm<LPS, true>();                  // slab kt+1 (mine)
-        multiply(std::integral_constant<int, 0>{});
-        st = st + 1 == NS ? 0 : st + 1;
-      }
-    }
-    if (!second) wg_barrier();
-  } else {
   bf16x8 a0[TM], b0[TN], a1[TM], b1[TN];
 #pragma unroll
   for (int sidx = 0; sidx < NS; ++sidx) issue(sidx);
@@ -452,7 +315,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
     interleave_hint<TM + TN, TM * TN>();
     st_cur = st_nxt;
   }
-  }
   wait_vm<0, true>();                        // drain the redundant tail loads before LDS is released
   if (MODE == 4) {
     // float4 number q = (((wave*TM + i)*TN + j)*4 + g)*64 + lane of the chunk holds
@@ -471,11 +333,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   }
 
   // ---- epilogue ---------------------------------------------------------------------------
-  // acc_at(i, j, e) is C[32i + acc_row(e)][32j + acc_col(e)] of the wave's sub-tile: a lane
+  // acc[i][j][e] is C[32i + acc_row(e)][32j + acc_col] of the wave's sub-tile: a lane
   // holds one or two columns, so direct stores would be 2- or 4-byte pieces.  Each wave therefore turns
   // its sub-tile 32 rows at a time through a private LDS patch (row stride TN*128 + 32 bytes:
-  // the two half-waves, 4 rows apart, then fall into disjoint bank halves; the 16x16 layout stores rows
-  // 0, 4, 8 and 12 at a time, and 8 rows apart is the same bank, so its stores take two passes) and reads it back
+  // the two half-waves, 4 rows apart, then fall into disjoint bank halves) and reads it back
   // row-major, 4 (fp32 out) or 8 (bf16 out) consecutive columns per lane: global accesses are
   // 16 bytes per lane and whole rows of the sub-tile per instruction.
   __syncthreads();     // every wave's ring loads have landed and all fragment reads are done
@@ -524,7 +385,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          *(float*)(stg + acc_row(e) * RS + (j * 32 + acc_col(e)) * 4) = acc_at(i, j, e);
+          *(float*)(stg + acc_row(e) * RS + (j * 32 + acc_col) * 4) = acc[i][j][e];
       f32x4 xr[RESID ? NIT : 1], gr[RESID ? NIT : 1];
       // (tiles with 128 or more accumulator registers per lane fetch half a patch at a time)
       constexpr int GRP = (RESID && TM * TN >= 8) ? NIT / 2 : NIT;
@@ -667,7 +528,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
         for (int j = 0; j < TN; ++j)
 #pragma unroll
           for (int e = 0; e < 16; ++e)
-            *(float*)(stg + acc_row(e) * RS + (j * 32 + acc_col(e)) * 4) = acc_at(i, j, e);
+            *(float*)(stg + acc_row(e) * RS + (j * 32 + acc_col) * 4) = acc[i][j][e];
         int drows[4];
         f32x4 rc0[4], rc1[4];
         constexpr int RG = TM * TN >= 10 ? 1 : 4;     // (the 320-row tile has no registers to spare: row by row there;
@@ -752,7 +613,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          *(float*)(stg + (j * 32 + acc_col(e)) * CS + acc_row(e) * 4) = acc_at(i, j, e);
+          *(float*)(stg + (j * 32 + acc_col) * CS + acc_row(e) * 4) = acc[i][j][e];
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       const int mb = m0 + wm * (BM / WM) + i * 32;     // first row of the patch
       // whole patch in range, its 32 rows neighbours in the transposed matrix, starting at a multiple of 8:
@@ -841,6 +702,686 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   else epilogue(std::integral_constant<int, OUT_RESID_F32>{});
 }
 
+// ---- 8-wave tiles: two groups of waves, tiles in one stream ------------------------------------------------
+//
+// 256x256 and 320x256 tiles (NS = 2 stages, two phases per slab) and the 256x128 tile (3 stages, one phase).
+//
+// Loop.  Two groups of four waves (wave / 4; each has one wave on every SIMD), half a phase apart: while one group's
+// waves do nothing but multiply, the other's read the fragments of their next product and issue loads, so the matrix
+// cores change hands at a barrier instead of idling while a wave waits for LDS (8192^3: 839 us with each wave
+// interleaving reads and products, matrix cores 78 % busy; 768 us this way with the same MFMA form, 91 %).  They
+// multiply with v_mfma_f32_16x16x32_bf16: the same cycles per flop as 32x32x16, but at that load the board lowers its
+// clock to what it can feed, and per flop the 16x16 form draws less (714 us).
+//   A group's reads are in registers before the barrier that ends its reading half, so what it read may be
+// overwritten by loads of either group from its next phase on.  The wait at the end of a reading half covers
+// the group's own loads of what the NEXT phase reads; the barriers in between make them visible to the other.
+//
+// Stream.  A workgroup stays on its CU and walks over its tiles (as many apart as its XCD has workgroups); the slabs of
+// its tiles are ONE stream: behind the last slab of a tile the loads go on with the first of the next, which
+// therefore arrive under the last products and the epilogue.
+//
+// Epilogue.  The operands are swapped, W in the place of MFMA rows: a lane then holds consecutive columns of ONE row, and
+// with the rows of W fed in the order {0-3, 8-11, 16-19, 24-27}, {4-7, 12-15, ...} the two products of a pair of 16
+// columns give it 8 neighbours: bias, GELU, norm and rotary code act on whole 16-byte pieces in registers, which are
+// turned into runs of 128 bytes by 16-byte LDS accesses in a 2 KB patch per wave beside the ring.  Tiles of transposed
+// values do the same with the operands in their first order and the rows of A permuted: 8 neighbouring tokens of a column.
+//   The XOR key of a slab row takes its bits 1, 3 and 2^4, so that 16 rows fall into 16 distinct 16-byte slots in both
+// orders.
+//
+// What bounds it: the matrix cores in the loop (1.32 us a slab of 256x256x64, 1.6 PFLOP/s); a tile's fixed part, 10 us
+// with a workgroup per tile and the results turned as fp32 in 4-byte LDS stores, is a quarter of the time at K = 1536.
+// Now 8 to 8.5 us, of which tanh-GELU is 3.6 and the stores 3 (each measured by leaving it out).  Before and after:
+// 18384 x 6144 x 1536 with GELU 303 -> 292 us, 18384 x 4608 x 1536 226 -> 216, 18384 x 1536 x 6144 into the residual
+// 307 -> 297, 32760 x 5120 x 5120 1400 -> 1363, 8192^3 722 -> 709; 3x3 convolutions of a million pixels with 128
+// channels 449 -> 426.  The 320-row tile has no registers to hold the next tile's offsets and starts each tile anew.
+// Tried: two workgroups of 4 waves a CU with 256x128 tiles, to let one's epilogue run under the other's loop (8192^3 at
+// 1088 TFLOP/s); starts staggered over the CUs so that their stores do not collide (as much lost as gained);
+// non-temporal stores (0.4 % at 32760 tokens, nothing elsewhere).
+__device__ __forceinline__ int swz_key8(int r) { return ((r >> 1) & 1) | ((r >> 2) & 2) | (((r ^ (r >> 2)) & 4)); }
+
+typedef const __attribute__((address_space(4))) GemmBatch Batch;
+typedef const __attribute__((address_space(4))) GemmProblem Problem;
+typedef const __attribute__((address_space(4))) QkNorm Norm;
+
+template <int BM, int BN, int WM, int WN, int NS, bool CONV>
+__global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
+  Batch& batch = *(Batch*)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr int ROWB = 128, BKT = 64;                  // bytes of a slab row, columns of a slab
+  constexpr int RT = BM / WM / 16, CT = 4;             // 16-row and 16-column tiles of a wave
+  constexpr int PH = NS == 2 ? 2 : 1, RP = RT / PH;    // phases per slab, row tiles per phase
+  constexpr int LA = BM / 64, LB = BN / 64, LPS = LA + LB;   // loads per wave and slab
+  constexpr int LAU = NS == 2 ? WM : LA;               // ... of the first part of A: 64 rows of every wave row
+  constexpr int STAGE = (BM + BN) * ROWB, OFFB = BM * ROWB;
+  static_assert(WM * WN == 8 && BN / WN == 64 && BM % 64 == 0 && RT % PH == 0, "two groups of four waves, 64 columns a wave");
+  static_assert(NS == 3 || (NS == 2 && RP * 16 >= 64), "two stages: the first part of A is read in phase 0 alone");
+  constexpr bool STREAM = RT <= 8;                     // (320 rows: no registers to hold the next tile's offsets under the epilogue)
+  constexpr bool LATE = RP * 16 == 64;                 // phase 0 reads none of the rest of A, which has a phase more to arrive
+  extern __shared__ __attribute__((aligned(128))) unsigned char smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  unsigned char* const patch = smem + NS * STAGE + wave * 2048;
+
+  // ---- my tiles: XCD x (workgroup ids are dealt round-robin) owns a contiguous range of them -----------------
+  int t_first, t_count, t_step;
+  {
+    const int x = blockIdx.x & 7, T = batch.total_tiles, G = gridDim.x;
+    t_first = x * (T >> 3) + (x < (T & 7) ? x : (T & 7));
+    t_count = (T >> 3) + (x < (T & 7) ? 1 : 0);
+    t_step = (G >> 3) + (x < (G & 7) ? 1 : 0);
+  }
+  // The argument block is read where it lies, in the kernel's argument segment (its only argument): a copy of the
+  // problem at hand would take half of the scalar registers.
+  auto problem = [&](int bid) -> Problem& {
+    const int i = batch.n > 2 && bid >= batch.p[2].tile_start ? 2 : batch.n > 1 && bid >= batch.p[1].tile_start ? 1 : 0;
+    return batch.p[i];
+  };
+
+  // ---- the stream of slabs -----------------------------------------------------------------------------------
+  // One load of a wave fills 8 slab rows.  With two stages A is fetched in two parts, the first 64 rows of every
+  // wave row and the rest; row_a: first of the rows that the wave's i-th load of A fills.
+  auto row_a = [&](int i) {
+    if constexpr (NS == 2) {
+      const bool up = i < LAU;
+      const int per = up ? 64 : RT * 16 - 64;
+      const int rr = ((up ? i : i - LAU) * 8 + wave) * 8;
+      return rr / per * (RT * 16) + rr % per + (up ? 0 : 64);
+    } else {
+      return (i * 8 + wave) * 8;
+    }
+  };
+  uint32_t oa[LA], ob[LB];        // byte offsets of my lane's 16-byte chunk of each load, from the tile's first row
+  const bf16_t *sA, *sW;          // first rows of the tile whose slabs are fetched
+  int ld_t = blockIdx.x >> 3;     // that tile (index in my XCD's range)
+  int ks = 0, ks_n = 0, ka = 0;   // slab of it, their number, byte offset of the slab in A (in W: 128 ks)
+  int run_left = 0, rows_left = 0, run_len = 0, run_skip = 0, frame_skip = 0;   // convolutions: see advance()
+  auto aim = [&](int t) {
+    const int bid = t_first + t;
+    Problem& P = problem(bid);
+    int tm, tn;
+    tile_coords(P, bid - P.tile_start, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));                                           // (made anew for each tile: kept, these would cost registers)
+    auto window = [&](int m) {    // convolution: top-left pixel of row m's 3x3 window in the stack of bordered images
+      const int b = m / P.conv_img, r = m - b * P.conv_img;
+      const int y = r / P.conv_w, x = r - y * P.conv_w;
+      return (size_t)(b * (P.conv_img / P.conv_w + 2) + y) * (P.conv_w + 2) + x;
+    };
+    size_t pix0 = 0;
+    if constexpr (CONV) pix0 = window(m0 < P.M ? m0 : P.M - 1);
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+      const int r = row_a(i) + (ln >> 3), c = (ln & 7) ^ swz_key8(r);
+      const int m = m0 + r < P.M ? m0 + r : P.M - 1;                       // clamp: rows past M are never stored
+      if constexpr (CONV) oa[i] = (uint32_t)((window(m) - pix0) * (size_t)P.conv_cin + c * 8) * 2u;
+      else oa[i] = ((uint32_t)(m - m0) * (uint32_t)P.lda + c * 8) * 2u;    // (32-bit offsets inside a tile: no operand limit)
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+      const int r = (i * 8 + wave) * 8 + (ln >> 3), c = (ln & 7) ^ swz_key8(r);
+      ob[i] = ((uint32_t)r * (uint32_t)P.ldw + c * 8) * 2u;                // weights are padded to N_pad rows
+    }
+    sA = P.A + (CONV ? pix0 * (size_t)P.conv_cin : (size_t)m0 * P.lda);
+    sW = P.W + (size_t)n0 * P.ldw;
+    ks = 0; ks_n = P.K / BKT; ka = 0;
+    if constexpr (CONV) {
+      run_len = run_left = 3 * P.conv_cin / BKT; rows_left = 3;
+      run_skip = (P.conv_w - 1) * P.conv_cin * 2;
+      frame_skip = (P.conv_img / P.conv_w - 1) * (P.conv_w + 2) * P.conv_cin * 2;
+    }
+  };
+  // Next slab of the stream: of the same tile (a convolution's taps of one image row are neighbours in memory, 3 conv_cin
+  // columns; then the next row of the window, then the next frame) ...
+  auto next_slab = [&]() {
+    ++ks; ka += BKT * 2;
+    if constexpr (CONV)
+      if (--run_left == 0) {
+        run_left = run_len; ka += run_skip;
+        if (--rows_left == 0) { rows_left = 3; ka += frame_skip; }
+      }
+  };
+  // ... or the first of the next tile.  (Behind the very last one the same again: redundant, but it keeps the number of
+  // loads per slab fixed, which the vmcnt arithmetic relies on.)
+  auto advance = [&]() {
+    if (ks + 1 < ks_n) next_slab();
+    else if (STREAM && ld_t + t_step < t_count) {
+      ld_t += t_step;
+      aim(ld_t);
+    }
+  };
+  auto issue_a = [&](int st, auto first, auto last) {
+#pragma unroll
+    for (int i = decltype(first)::value; i < decltype(last)::value; ++i)
+      buffer_load_lds16(sA, (lptr_t)(smem + st * STAGE + row_a(i) * ROWB), oa[i], ka);
+  };
+  auto issue_b = [&](int st) {
+#pragma unroll
+    for (int i = 0; i < LB; ++i) buffer_load_lds16(sW, (lptr_t)(smem + st * STAGE + OFFB + (i * 8 + wave) * 1024), ob[i], ks * (BKT * 2));
+  };
+  constexpr std::integral_constant<int, 0> A_FIRST{};
+  constexpr std::integral_constant<int, LAU> A_REST{};
+  constexpr std::integral_constant<int, LA> A_END{};
+
+  // ---- the loop over one tile's slabs ------------------------------------------------------------------------
+  f32x4 acc[RT][CT];
+  const bool second = wave >= 4;
+  int stage = 0;                  // stage of the slab that is read next
+  // Byte offsets of this lane's fragments.  Consecutive rows: 16-row tile i starts 16 i rows on, permuted rows
+  // (8 rows for every 4 lanes): pairs of tiles 32 rows on, the odd one 4 rows on.  Odd tiles flip bit 2 of the key.
+  // VT: the first operand is A with permuted rows (tiles of transposed values), else W with permuted rows.
+  auto run = [&](auto vt_tag, int nk) {
+    constexpr bool VT = decltype(vt_tag)::value;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));                         // (made anew for each tile, as in aim())
+    const int l16 = ln & 15, kq = ln >> 4;
+    const int row_c = l16, row_p = (l16 >> 2) * 8 + (l16 & 3);
+    const int off_c = row_c * ROWB + ((kq ^ swz_key8(row_c)) << 4), off_p = row_p * ROWB + ((kq ^ swz_key8(row_p)) << 4);
+    bf16x8 fa[2][RP], fb[2][CT];
+    auto tile_off = [](bool perm, int i) { return perm ? (i >> 1) * 32 + (i & 1) * 4 : i * 16; };
+    const int a0 = wm * (RT * 16) * ROWB + (VT ? off_p : off_c), b0 = OFFB + wn * 64 * ROWB + (VT ? off_c : off_p);
+    auto read_a = [&](const unsigned char* st, auto phase) {
+      const unsigned char* p[2] = {st + a0, st + (a0 ^ 64)};
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int r = 0; r < RP; ++r) {
+          const int i = decltype(phase)::value * RP + r;
+          fa[k][r] = *(const bf16x8*)(p[k ^ (i & 1)] + tile_off(VT, i) * ROWB);
+        }
+    };
+    auto read_b = [&](const unsigned char* st) {
+      const unsigned char* p[2] = {st + b0, st + (b0 ^ 64)};
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) fb[k][c] = *(const bf16x8*)(p[k ^ (c & 1)] + tile_off(!VT, c) * ROWB);
+    };
+    auto multiply = [&](auto phase) {
+      wg_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int r = 0; r < RP; ++r)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            f32x4& d = acc[decltype(phase)::value * RP + r][c];
+            if constexpr (VT) d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[k][r], fb[k][c], d, 0, 0, 0);
+            else d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[k][c], fa[k][r], d, 0, 0, 0);
+          }
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      wg_barrier();
+    };
+    constexpr std::integral_constant<int, 0> P0{};
+    constexpr std::integral_constant<int, PH - 1> P1{};
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < CT; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // (Waits that allow for the last epilogue's stores, two slabs long, cost more by their branches than they gain.)
+    // One slab.  same: the stream's next slab is known to be of this tile, which keeps the aiming out of the loop.
+    auto slab = [&](auto same) {
+      const unsigned char* cur = smem + stage * STAGE;
+      const int nxt = stage + 1 == NS ? 0 : stage + 1;
+      if constexpr (decltype(same)::value) next_slab(); else advance();      // (here: no fragments are held)
+      read_b(cur);
+      read_a(cur, P0);
+      if constexpr (NS == 2) {
+        // Phase 0 of slab s reads the upper half of A and W; phase 1 reads the lower half of A and issues W and the first
+        // part of A of slab s+2; when it is over the rest of A follows (over that of slab s, which everybody has read).
+        wait_vm<LATE ? LPS : 63, true>();              // rest of A of slab s (mine; without LATE slab s is complete)
+        multiply(P0);
+        read_a(cur, P1);
+        issue_b(stage); issue_a(stage, A_FIRST, A_REST);
+        // W and the first part of A of slab s+1 (mine; without LATE all of it)
+        wait_vm<LATE ? LPS : LB + LAU, true>();
+        multiply(P1);
+        issue_a(stage, A_REST, A_END);
+      } else {
+        // phase s reads slab s and issues slab s+2 into the stage that slab s-1 left
+        const int free_st = nxt + 1 == NS ? 0 : nxt + 1;
+        issue_a(free_st, A_FIRST, A_END); issue_b(free_st);
+        wait_vm<LPS, true>();                          // slab s+1 (mine)
+        multiply(P0);
+      }
+      stage = nxt;
+    };
+    if (second) wg_barrier();
+    int kt = 0;
+    for (; kt < nk - 2; ++kt) slab(std::true_type{});
+    for (; kt < nk; ++kt) slab(std::false_type{});
+    if (!second) wg_barrier();
+  };
+
+  // ---- epilogues: non-VT tiles hold C[16 r + l16][32 j + 8 kq + 0..7] of the wave's sub-tile in acc[r][2 j], acc[r][2 j + 1] ----
+  // (Row addresses: a scalar base per 8 rows and one lane offset.  The scheduling barriers keep a unit's work from
+  // being hoisted over the ones before it, which costs registers.)
+  auto epilogue = [&](Problem& P, int tm, int m0, int n0, bool vt) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));                         // (lane numbers are made anew: kept through the loop they would cost registers)
+    const int l16 = ln & 15, kq = ln >> 4;
+    const int prow = ln >> 3, pchunk = ln & 7;           // my row (and the one 8 on) and 16-byte chunk when a patch is read back
+    const int mw = m0 + wm * (RT * 16), nw = n0 + wn * 64;
+    const int M = P.M, N = P.N, kind = P.out_kind;
+    const float* const bias = P.bias;
+    constexpr bool PIPE = RT <= 8;                       // a unit is turned while the one before it is stored (where registers allow)
+    auto patch_at = [&](int row, int chunk) { return patch + row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4); };
+    auto turn = [&](const u32x4& lo, const u32x4& hi, int c_lo, int c_hi, u32x4 (&out)[2]) {    // 16 rows x 128 bytes
+      *(u32x4*)patch_at(l16, c_lo) = lo;
+      *(u32x4*)patch_at(l16, c_hi) = hi;
+      asm volatile("" ::: "memory");                     // (a wave's LDS accesses are executed in order)
+      out[0] = *(const u32x4*)patch_at(prow, pchunk);
+      out[1] = *(const u32x4*)patch_at(prow + 8, pchunk);
+      asm volatile("" ::: "memory");
+    };
+    auto load_cols = [&](const float* p, float (&v)[2][8]) {   // per-column values of my 16 columns
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          const int n = nw + j * 32 + kq * 8 + c;
+          v[j][c] = p && n < N ? p[n] : 0.f;
+        }
+    };
+    auto raw = [&](int r, int j, float (&v)[8]) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) { v[c] = acc[r][2 * j][c]; v[4 + c] = acc[r][2 * j + 1][c]; }
+    };
+    // bf16 results: value(r, j, v) makes the 8 values of row tile r, columns 32 j + 8 kq ...; row_ptr(r, h): where my 8
+    // columns of row 16 r + 8 h + prow go
+    auto store_bf16 = [&](auto value, auto pack2, auto row_ptr) {
+      const bool full = nw + pchunk * 8 + 8 <= N;
+      auto make = [&](int r, u32x4 (&w)[2]) {
+        u32x4 p[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          float v[8];
+          value(r, j, v);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) p[j][c] = pack2(v[2 * c], v[2 * c + 1]);
+        }
+        turn(p[0], p[1], kq, 4 + kq, w);
+      };
+      u32x4 w[2], nx[2];
+      if (PIPE) make(0, w);
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        if (!PIPE) make(r, w);
+        else if (r + 1 < RT) make(r + 1, nx);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          char* const xp = row_ptr(r, h);
+          if (prow < M - mw - (r * 16 + h * 8)) {
+            if (full) *(u32x4*)xp = w[h];
+            else
+              for (int c = 0; c < N - nw - pchunk * 8; ++c) ((bf16_t*)xp)[c] = (bf16_t)(w[h][c >> 1] >> (16 * (c & 1)));
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < 2 && PIPE; ++h) w[h] = nx[h];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto plain_bf16 = [&](auto gelu_tag) {
+      constexpr bool GELU = decltype(gelu_tag)::value;
+      float bv[2][8];
+      load_cols(bias, bv);
+      bf16_t* const out = (bf16_t*)P.out;
+      const int ldc = P.ldc;
+      const uint32_t voff = (uint32_t)(prow * ldc + pchunk * 8) * 2u;
+      store_bf16([&](int r, int j, float (&v)[8]) {
+        raw(r, j, v);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          v[c] += bv[j][c];
+          if constexpr (GELU) v[c] = gelu_tanh(v[c]);
+        }
+      }, [](float a, float b) { return pack2bf(a, b); },
+      [&](int r, int h) { return (char*)(out + (size_t)(mw + r * 16 + h * 8) * ldc + nw) + voff; });
+    };
+    // fp32 results in units of 16 rows x 32 columns: plain, or added to what is there times the row's gate
+    auto plain_f32 = [&](auto resid_tag) {
+      constexpr bool RESID = decltype(resid_tag)::value;
+      constexpr bool STATS = CONV;
+      float bv[2][8];
+      load_cols(bias, bv);
+      const int nb = nw + pchunk * 4, ldc = P.ldc;       // my columns on the way out: nb + 32 j ... + 3
+      float* const out = (float*)P.out;
+      const uint32_t voff = (uint32_t)(prow * ldc + pchunk * 4) * 4u;
+      auto row_at = [&](int u, int h) { return (char*)(out + (size_t)(mw + (u >> 1) * 16 + h * 8) * ldc + nw + 32 * (u & 1)) + voff; };
+      auto row_in = [&](int u, int h) { return prow < M - mw - (u >> 1) * 16 - h * 8; };
+      float cs[2][4], cq[2][4];                          // convolutions: their sums and sums of squares (see GemmProblem::stats)
+      if constexpr (STATS) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) { cs[j][c] = 0.f; cq[j][c] = 0.f; }
+      }
+      // One gate vector for all rows of the wave (nearly always: a request has hundreds) is kept in registers.
+      const float* const gate = RESID && !CONV ? P.gate : nullptr;
+      const int* const rreq = P.row_req;
+      const int gstride = P.gate_stride;
+      bool one_gate = true;
+      constexpr int RQ = (RT * 16 + 63) / 64;
+      int rq[RQ];                                        // request of row 64 k + lane
+      f32x4 gv[2] = {{1.f, 1.f, 1.f, 1.f}, {1.f, 1.f, 1.f, 1.f}};
+      auto load_gate = [&](int req, int j) {
+        f32x4 g;
+        const float* gp = gate + (size_t)req * gstride + nb + 32 * j;
+        if (nb + 32 * j + 4 <= N) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) g[c] = gp[c];
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) g[c] = nb + 32 * j + c < N ? gp[c] : 0.f;
+        }
+        return g;
+      };
+      if (RESID && gate) {
+#pragma unroll
+        for (int k = 0; k < RQ; ++k) {
+          const int m = mw + k * 64 + ln;
+          rq[k] = rreq ? rreq[m < M ? m : M - 1] : 0;
+        }
+        const int req0 = __builtin_amdgcn_readfirstlane(rq[0]);
+        bool same = true;
+#pragma unroll
+        for (int k = 0; k < RQ; ++k) same = same && (rq[k] == req0 || k * 64 + ln >= RT * 16);
+        one_gate = __builtin_amdgcn_ballot_w64(!same) == 0;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) gv[j] = load_gate(req0, j);
+      }
+      // What is there is loaded AHEAD units before it is used (the compiler may not move loads across the stores).
+      constexpr int U = RT * 2;
+      f32x4 xr[RESID ? 4 : 1][2], gr[2];
+      // (rows of several requests: their gates, a unit ahead)
+      auto load_gr = [&](int u) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int i = (u >> 1) * 16 + h * 8;
+          gr[h] = load_gate(__shfl(rq[i >> 6], (i & 63) + prow), u & 1);
+        }
+      };
+      auto load_x = [&](int u, f32x4 (&x)[2]) {
+        if constexpr (RESID) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            x[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (row_in(u, h) && nb + 32 * (u & 1) + 4 <= N) x[h] = *(const f32x4*)row_at(u, h);
+          }
+        }
+      };
+      auto make = [&](int u, u32x4 (&w)[2]) {
+        union { float f[8]; u32x4 q[2]; } v;
+        raw(u >> 1, u & 1, v.f);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v.f[c] += bv[u & 1][c];
+        turn(v.q[0], v.q[1], 2 * kq, 2 * kq + 1, w);
+      };
+      auto units = [&](auto one_tag) {
+      constexpr bool ONE = decltype(one_tag)::value;
+      constexpr int AHEAD = !RESID ? 1 : ONE && PIPE ? 4 : 2;
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) load_x(u, xr[u]);
+      if (!ONE) load_gr(0);
+      u32x4 w[2], nx[2];
+      if (PIPE) make(0, w);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = u & 1, n = nb + 32 * j;
+        if (!PIPE) make(u, w);
+        else if (u + 1 < U) make(u + 1, nx);
+        // (used here on every path: a load that some path leaves pending would be waited for in the next tile's loop)
+        if constexpr (RESID) asm volatile("" :: "v"(xr[u % AHEAD][0]), "v"(xr[u % AHEAD][1]), "v"(gv[j]));
+        if constexpr (RESID && !ONE) asm volatile("" :: "v"(gr[0]), "v"(gr[1]));
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if (row_in(u, h) && n < N) {
+            f32x4 x4;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x4[c] = __uint_as_float(w[h][c]);
+            float* xp = (float*)row_at(u, h);
+            if constexpr (RESID) {
+              const f32x4 g = ONE ? gv[j] : gr[h];
+              if (n + 4 <= N) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x4[c] = xr[u % AHEAD][h][c] + g[c] * x4[c];
+              } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x4[c] = n + c < N ? xp[c] + g[c] * x4[c] : 0.f;
+              }
+            }
+            if (n + 4 <= N) *(f32x4*)xp = x4;
+            else {
+#pragma unroll
+              for (int c = 0; c < 4; ++c)
+                if (n + c < N) xp[c] = x4[c];
+            }
+            if constexpr (STATS) {
+#pragma unroll
+              for (int c = 0; c < 4; ++c) { cs[j][c] += x4[c]; cq[j][c] += x4[c] * x4[c]; }     // (columns past N are not written out)
+            }
+          }
+        }
+        if (u + AHEAD < U) load_x(u + AHEAD, xr[u % AHEAD]);
+        if (!ONE && u + 1 < U) load_gr(u + 1);
+#pragma unroll
+        for (int h = 0; h < 2 && PIPE; ++h) w[h] = nx[h];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      };
+      // (two copies: loads of a path that the compiler thinks may be left pending are waited for in the next tile's loop)
+      if (!RESID || CONV || one_gate) units(std::true_type{});
+      else units(std::false_type{});
+      if constexpr (STATS) {
+        float* const stats = P.stats;
+        if (stats) {      // partial[(tile row * WM + wm)][column][2]: rows of one wave of one tile
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+#pragma unroll
+              for (int o = 8; o < 64; o <<= 1) { cs[j][c] += __shfl_xor(cs[j][c], o); cq[j][c] += __shfl_xor(cq[j][c], o); }
+              const int n = nb + 32 * j + c;
+              if (prow == 0 && n < N) *(f32x2*)(stats + ((size_t)(tm * WM + wm) * N + n) * 2) = f32x2{cs[j][c], cq[j][c]};
+            }
+        }
+      }
+    };
+    // q/k columns of a QKV product: RMS norm per head, gain, rotary code, scale, scatter by row.  The wave's 64 columns are
+    // one head (head_dim 64) or half of one (128: the two waves of a pair exchange their sums of squares).
+    auto norm_rope = [&]() {
+      Norm& Q = P.qk;
+      const int head_dim = Q.head_dim, nq = Q.nq;
+      const bool is_k = n0 >= nq;                        // (nq is a multiple of the tile's width)
+      const int col0 = nw - (is_k ? nq : 0);             // first of the wave's columns in the q (k) range
+      // destination rows of my rows 16 r + l16 (what is loaded here arrives under the sums)
+      const int* const map = Q.dst_row;
+      int dr[RT];
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        const int m = mw + r * 16 + l16;
+        dr[r] = map ? map[m < M ? m : M - 1] : m;
+      }
+      float ss[RT];
+      {
+        float bv[2][8];
+        load_cols(bias, bv);
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          float s2 = 0.f;
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+              const float v = acc[r][2 * j + (c >> 2)][c & 3] + bv[j][c];
+              acc[r][2 * j + (c >> 2)][c & 3] = v;
+              s2 += v * v;
+            }
+          s2 += __shfl_xor(s2, 16); s2 += __shfl_xor(s2, 32);
+          ss[r] = s2;
+        }
+      }
+      if (head_dim == 128) {
+        float* mine = (float*)patch;
+        const float* other = (const float*)(smem + NS * STAGE + (wave ^ 1) * 2048);
+        if (kq == 0) {
+#pragma unroll
+          for (int r = 0; r < RT; ++r) mine[r * 16 + l16] = ss[r];
+        }
+        wait_vm<63, true>();
+        wg_barrier();
+#pragma unroll
+        for (int r = 0; r < RT; ++r) ss[r] += other[r * 16 + l16];
+        wait_vm<63, true>();
+        wg_barrier();                                    // (the patches are written again from here on)
+      }
+      const float inv_dh = 1.0f / (float)head_dim, osc = is_k ? 1.0f : Q.qscale;
+#pragma unroll
+      for (int r = 0; r < RT; ++r) ss[r] = rsqrtf(ss[r] * inv_dh + 1e-6f) * osc;
+      const int hc = (col0 & (head_dim - 1)) + kq * 8;   // my first column inside the head
+      float gv[2][8];
+      {
+        const float* gain = is_k ? Q.kgain : Q.qgain;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int c = 0; c < 8; ++c) gv[j][c] = gain[hc + j * 32 + c];
+      }
+      const float2* const rope = Q.rope;
+      const int half = head_dim >> 1;
+      // rotary pairs of row tile r, a tile ahead
+      f32x4 rc[2][2];
+      auto load_rope = [&](int r) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          f32x4 (&c)[2] = rc[j];
+          c[0] = c[1] = f32x4{1.f, 0.f, 1.f, 0.f};       // (cos, sin)
+          if (rope) {
+            const f32x4* rp = (const f32x4*)(rope + (size_t)dr[r] * half + (hc >> 1) + 16 * j);
+            c[0] = rp[0]; c[1] = rp[1];
+          }
+        }
+      };
+      load_rope(0);
+      auto value = [&](int r, int j, float (&v)[8]) {
+        const f32x4 c0 = rc[j][0], c1 = rc[j][1];
+        const float cs[8] = {c0[0], c0[1], c0[2], c0[3], c1[0], c1[1], c1[2], c1[3]};
+        raw(r, j, v);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const float a = v[2 * p] * ss[r] * gv[j][2 * p], b = v[2 * p + 1] * ss[r] * gv[j][2 * p + 1];
+          v[2 * p] = a * cs[2 * p] - b * cs[2 * p + 1];
+          v[2 * p + 1] = a * cs[2 * p + 1] + b * cs[2 * p];
+        }
+        if (j == 1 && r + 1 < RT) load_rope(r + 1);
+      };
+      const bool f16 = Q.f16 != 0;
+      bf16_t* const out = is_k ? Q.ko : Q.qo;
+      const int ldo = Q.ldo;
+      store_bf16(value, [&](float a, float b) { return f16 ? pack2h(a, b) : pack2bf(a, b); },
+                 [&](int r, int h) { return (char*)(out + (size_t)__shfl(dr[r], h * 8 + prow) * ldo + col0 + pchunk * 8); });
+    };
+    // Value columns written transposed: acc[2 i][c], acc[2 i + 1][c] hold rows 32 i + 8 kq + 0..7 of column 16 c + l16.  Units of
+    // 32 rows x 32 columns; a lane writes 8 rows of a column as one 16-byte piece (at any 2-byte offset: a request's
+    // image rows follow its text rows) when the 32 rows are neighbours in the transposed matrix, else element by element.
+    auto transposed = [&]() {
+      Norm& Q = P.qk;
+      typedef u32x4 u32x4_any __attribute__((aligned(2)));
+      const int nv0 = nw - (Q.nq + Q.nk), ldvt = Q.ldvt;
+      const int* const map = Q.vt_col;
+      bf16_t* const vt_out = Q.vt;
+      float bv[CT];
+#pragma unroll
+      for (int c = 0; c < CT; ++c) bv[c] = bias && nw + c * 16 + l16 < N ? bias[nw + c * 16 + l16] : 0.f;
+      const int fr = ln >> 2, fc = ln & 3;               // my column (and the one 16 on) and piece when a unit is read back
+      auto at = [&](int f, int chunk) { return patch + f * 64 + ((chunk ^ ((f >> 2) & 3)) << 4); };
+      const uint32_t voff = (uint32_t)(fr * ldvt + fc * 8) * 2u;
+#pragma unroll
+      for (int i = 0; i < RT / 2; ++i) {
+        const int mb = mw + i * 32;                      // first row of the unit
+        bool consec = mb + 32 <= M;
+        int cb = 0;
+        if (consec) {
+          cb = map[mb];
+          consec = map[mb + 31] == cb + 31;
+        }
+#pragma unroll
+        for (int cp = 0; cp < 2; ++cp) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int c = cp * 2 + q;
+            const f32x4 t0 = acc[2 * i][c], t1 = acc[2 * i + 1][c];
+            const u32x4 w = {pack2bf(t0[0] + bv[c], t0[1] + bv[c]), pack2bf(t0[2] + bv[c], t0[3] + bv[c]),
+                             pack2bf(t1[0] + bv[c], t1[1] + bv[c]), pack2bf(t1[2] + bv[c], t1[3] + bv[c])};
+            *(u32x4*)at(q * 16 + l16, kq) = w;
+          }
+          asm volatile("" ::: "memory");
+          u32x4 w[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) w[h] = *(const u32x4*)at(h * 16 + fr, fc);
+          asm volatile("" ::: "memory");
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int f = cp * 32 + h * 16;
+            if (fr >= N - nw - f) continue;
+            if (consec) *(u32x4_any*)((char*)(vt_out + (size_t)(nv0 + f) * ldvt + cb) + voff) = w[h];
+            else {
+              bf16_t* dst = vt_out + (size_t)(nv0 + f + fr) * ldvt;
+              for (int e = 0; e < 8; ++e)
+                if (mb + fc * 8 + e < M) dst[map[mb + fc * 8 + e]] = (bf16_t)(w[h][e >> 1] >> (16 * (e & 1)));
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    if constexpr (!CONV) {
+      if (kind == OUT_QKNORM && n0 < P.qk.nq + P.qk.nk) { norm_rope(); return; }
+      if (vt) { transposed(); return; }
+      if (kind == OUT_GELU_BF16) { plain_bf16(std::true_type{}); return; }
+      if (kind == OUT_BF16 || kind == OUT_QKNORM) { plain_bf16(std::false_type{}); return; }
+    }
+    if (kind == OUT_F32) plain_f32(std::false_type{});
+    else plain_f32(std::true_type{});
+  };
+
+  // ---- all my tiles ------------------------------------------------------------------------------------------
+  auto start = [&]() {
+    aim(ld_t);
+    issue_b(0); issue_a(0, A_FIRST, A_END);
+    advance();
+    issue_b(1); issue_a(1, A_FIRST, A_END);
+    wait_vm<LPS, false>();
+    wg_barrier();
+  };
+  if (STREAM) start();
+  for (int t = blockIdx.x >> 3; t < t_count; t += t_step) {
+    if (!STREAM) {
+      ld_t = t; stage = 0;
+      start();
+    }
+    const int bid = t_first + t;
+    Problem& P = problem(bid);
+    int tm, tn;
+    tile_coords(P, bid - P.tile_start, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const bool vt = !CONV && P.out_kind == OUT_QKNORM && P.qk.vt && n0 >= P.qk.nq + P.qk.nk;
+    if (!CONV && vt) run(std::true_type{}, P.K / BKT);
+    else run(std::false_type{}, P.K / BKT);
+    if (!STREAM) {                           // the redundant tail loads, before the stages are filled again
+      wait_vm<0, true>();
+      wg_barrier();
+    }
+    epilogue(P, tm, m0, n0, vt);
+  }
+  wait_vm<0, true>();                        // drain the redundant tail loads before LDS is released
+}
+
 // Second half of a split-K product: sums the `splits` partial tiles in fixed order (so the
 // result does not depend on which workgroup finished first) and applies the epilogue.  One
 // thread per float4 of the chunk layout written above: 4 consecutive rows of one column, the
@@ -912,20 +1453,38 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmBatch batc
   }
 }
 
-template <int BM, int BN, int WM, int WN, int BKT, int NS, int MODE = 0, bool CONV = false, int SCHED = 2>
-static void launch_t(hipStream_t s, GemmBatch& b) {
+// tiles of the whole batch, numbered through
+static int count_tiles(GemmBatch& b, int bm, int bn) {
   int total = 0;
   for (int i = 0; i < b.n; ++i) {
     GemmProblem& p = b.p[i];
-    p.tiles_m = (p.M + BM - 1) / BM;
-    p.tiles_n = (p.N + BN - 1) / BN;
+    p.tiles_m = (p.M + bm - 1) / bm;
+    p.tiles_n = (p.N + bn - 1) / bn;
     p.tile_start = total;
     total += p.tiles_m * p.tiles_n;
   }
-  b.total_tiles = total;
+  return b.total_tiles = total;
+}
+
+template <int BM, int BN, int WM, int WN, int NS, bool CONV = false>
+static void launch8_t(hipStream_t s, GemmBatch& b) {
+  const int total = count_tiles(b, BM, BN);
+  if (total == 0) return;
+  constexpr int lds = NS * (BM + BN) * 128 + 8 * 2048;      // the ring and a patch per wave
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  auto kern = gemm8_kernel<BM, BN, WM, WN, NS, CONV>;
+  static std::atomic<unsigned> seen{0};
+  if (first_use_on_device(seen))
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  hipLaunchKernelGGL(kern, dim3(total < 256 ? total : 256), dim3(512), lds, s, b);    // one workgroup per CU
+}
+
+template <int BM, int BN, int WM, int WN, int BKT, int NS, int MODE = 0, bool CONV = false>
+static void launch_t(hipStream_t s, GemmBatch& b) {
+  const int total = count_tiles(b, BM, BN);
   if (total == 0) return;
   size_t lds = (size_t)NS * (BM + BN) * BKT * 2;
-  auto kern = gemm_kernel<BM, BN, WM, WN, BKT, NS, MODE, CONV, SCHED>;
+  auto kern = gemm_kernel<BM, BN, WM, WN, BKT, NS, MODE, CONV>;
   static std::atomic<unsigned> seen{0};
   if (first_use_on_device(seen))
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1133,37 +1692,37 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
     for (int i = 0; i < b.n; ++i)        // whole images of whole rows
       if (b.p[i].conv_img <= 0 || b.p[i].conv_img % b.p[i].conv_w || b.p[i].M % b.p[i].conv_img ||
           (b.p[i].conv_kt != 1 && b.p[i].conv_kt != 3) || b.p[i].K != 9 * b.p[i].conv_kt * b.p[i].conv_cin) return -1;
-    if (tile == 1256256) launch_t<256, 256, 2, 4, 64, 2, 0, true, 4>(s, b);
-    else if (tile == 32256128) launch_t<256, 128, 4, 2, 64, 3, 0, true, 5>(s, b);
-    else if (tile == 40128128) launch_t<128, 128, 2, 2, 64, 4, 4, true, 2>(s, b);
-    else if (tile == 30128128) launch_t<128, 128, 2, 2, 64, 4, 0, true, 2>(s, b);
-    else { tile = 128128; launch_t<128, 128, 2, 2, 64, 2, 0, true, 2>(s, b); }
+    if (tile == 1256256) launch8_t<256, 256, 2, 4, 2, true>(s, b);
+    else if (tile == 32256128) launch8_t<256, 128, 4, 2, 3, true>(s, b);
+    else if (tile == 40128128) launch_t<128, 128, 2, 2, 64, 4, 4, true>(s, b);
+    else if (tile == 30128128) launch_t<128, 128, 2, 2, 64, 4, 0, true>(s, b);
+    else { tile = 128128; launch_t<128, 128, 2, 2, 64, 2, 0, true>(s, b); }
     return tile;
   }
   switch (tile) {
-    case 256256: launch_t<256, 256, 2, 2, 64, 2, 0, false, 2>(s, b); break;
-    case 1256256: launch_t<256, 256, 2, 4, 64, 2, 0, false, 4>(s, b); break;
-    case 1320256: launch_t<320, 256, 2, 4, 64, 2, 0, false, 4>(s, b); break;
-    case 10256256: launch_t<256, 256, 2, 2, 32, 4, 0, false, 2>(s, b); break;
-    case 11256256: launch_t<256, 256, 2, 4, 32, 4, 0, false, 2>(s, b); break;
-    case 20256256: launch_t<256, 256, 2, 2, 32, 5, 0, false, 2>(s, b); break;
-    case 21256256: launch_t<256, 256, 2, 4, 32, 5, 0, false, 2>(s, b); break;
-    case 256128: launch_t<256, 128, 2, 2, 64, 2, 0, false, 2>(s, b); break;
-    case 128256: launch_t<128, 256, 2, 2, 64, 2, 0, false, 2>(s, b); break;
-    case 10128128: launch_t<128, 128, 2, 2, 32, 4, 0, false, 2>(s, b); break;
-    case 30128128: launch_t<128, 128, 2, 2, 64, 4, 0, false, 2>(s, b); break;
-    case 30128064: launch_t<128, 64, 4, 1, 64, 6, 0, false, 2>(s, b); break;
-    case 30064128: launch_t<64, 128, 1, 4, 64, 6, 0, false, 2>(s, b); break;
-    case 30032128: launch_t<32, 128, 1, 4, 64, 4, 0, false, 2>(s, b); break;
-    case 40032128: launch_t<32, 128, 1, 4, 64, 4, 4, false, 2>(s, b); break;
-    case 30064064: launch_t<64, 64, 2, 1, 64, 5, 0, false, 2>(s, b); break;
-    case 40064064: launch_t<64, 64, 2, 1, 64, 5, 4, false, 2>(s, b); break;
-    case 33128064: launch_t<128, 64, 4, 1, 64, 3, 0, false, 2>(s, b); break;
-    case 31256128: launch_t<256, 128, 2, 2, 64, 3, 0, false, 2>(s, b); break;
-    case 32256128: launch_t<256, 128, 4, 2, 64, 3, 0, false, 5>(s, b); break;
-    case 31128256: launch_t<128, 256, 2, 2, 64, 3, 0, false, 2>(s, b); break;
-    case 40128128: launch_t<128, 128, 2, 2, 64, 4, 4, false, 2>(s, b); break;
-    default: tile = 128128; launch_t<128, 128, 2, 2, 64, 2, 0, false, 2>(s, b); break;
+    case 256256: launch_t<256, 256, 2, 2, 64, 2>(s, b); break;
+    case 1256256: launch8_t<256, 256, 2, 4, 2>(s, b); break;
+    case 1320256: launch8_t<320, 256, 2, 4, 2>(s, b); break;
+    case 10256256: launch_t<256, 256, 2, 2, 32, 4>(s, b); break;
+    case 11256256: launch_t<256, 256, 2, 4, 32, 4>(s, b); break;
+    case 20256256: launch_t<256, 256, 2, 2, 32, 5>(s, b); break;
+    case 21256256: launch_t<256, 256, 2, 4, 32, 5>(s, b); break;
+    case 256128: launch_t<256, 128, 2, 2, 64, 2>(s, b); break;
+    case 128256: launch_t<128, 256, 2, 2, 64, 2>(s, b); break;
+    case 10128128: launch_t<128, 128, 2, 2, 32, 4>(s, b); break;
+    case 30128128: launch_t<128, 128, 2, 2, 64, 4>(s, b); break;
+    case 30128064: launch_t<128, 64, 4, 1, 64, 6>(s, b); break;
+    case 30064128: launch_t<64, 128, 1, 4, 64, 6>(s, b); break;
+    case 30032128: launch_t<32, 128, 1, 4, 64, 4>(s, b); break;
+    case 40032128: launch_t<32, 128, 1, 4, 64, 4, 4>(s, b); break;
+    case 30064064: launch_t<64, 64, 2, 1, 64, 5>(s, b); break;
+    case 40064064: launch_t<64, 64, 2, 1, 64, 5, 4>(s, b); break;
+    case 33128064: launch_t<128, 64, 4, 1, 64, 3>(s, b); break;
+    case 31256128: launch_t<256, 128, 2, 2, 64, 3>(s, b); break;
+    case 32256128: launch8_t<256, 128, 4, 2, 3>(s, b); break;
+    case 31128256: launch_t<128, 256, 2, 2, 64, 3>(s, b); break;
+    case 40128128: launch_t<128, 128, 2, 2, 64, 4, 4>(s, b); break;
+    default: tile = 128128; launch_t<128, 128, 2, 2, 64, 2>(s, b); break;
   }
   return tile;
 }

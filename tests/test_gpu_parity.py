@@ -122,6 +122,50 @@ def test_gemm_two_group_tiles_at_their_edges(torch, B, M, variant):
         assert (np.abs(got[:, :N] - ref) <= 1e-5 * mag).all(), (M, N, K)
 
 
+@pytest.mark.parametrize("variant,M,N", [(1256256, 4200, 4200), (1320256, 5000, 4200), (32256128, 4200, 2100)])
+@pytest.mark.parametrize("K", [64, 128, 192, 448])
+def test_gemm_several_tiles_per_workgroup(torch, B, variant, M, N, K):
+    """More tiles than workgroups: the slabs of a workgroup's tiles are one stream, here with tiles of one to seven slabs
+    (of one, two tiles are under way at once), ragged in both directions; fp32, bf16 and GELU results. Every tile adds
+    in the same order, so the results are those of the 128x128 tile, which has a workgroup per tile."""
+    A, W = to_dev_bf16(torch, rnd(71, "A", (M, K))), to_dev_bf16(torch, rnd(72, "W", ((N + 255) // 256 * 256, K), 0.05))
+    ldc = (N + 7) // 8 * 8
+    for kind, dtype in ((1, torch.float32), (0, torch.bfloat16), (2, torch.bfloat16)):
+        outs = []
+        for v in (128128, variant):
+            out = torch.full((M, ldc), 7.0, dtype=dtype, device="cuda")
+            assert B.dit_op_gemm_variant(None, A.data_ptr(), K, W.data_ptr(), K, None, M, N, K, kind, out.data_ptr(), ldc, v) == 0
+            outs.append(out)
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], outs[1]), kind
+        assert bool((outs[1][:, N:] == 7).all())
+
+
+@pytest.mark.parametrize("M,N,tile", [(8192, 2560, 1256256), (4250, 1544, 32256128), (4250, 4608, 1320256)])
+@pytest.mark.parametrize("per_request", [1, 100, 5000])
+def test_gemm_gated_residual_on_the_large_tiles(torch, B, M, N, tile, per_request):
+    """x += gate[request] * (A W^T + b) through the launcher's own choice of the 8-wave tiles, with requests that change in
+    every row, inside a wave's rows, and not at all (one gate vector is then kept for the wave), ragged columns."""
+    K = 1536
+    col = lambda v: (C.c_int * 1)(v)
+    assert B.dit_op_gemm_tile(1, col(M), col(N), col(K), 3, 0, 0, None) == tile
+    Npad = (N + 255) // 256 * 256
+    A, W = to_dev_bf16(torch, rnd(73, "A", (M, K))), to_dev_bf16(torch, rnd(74, "W", (Npad, K), 0.05))
+    n_req = (M + per_request - 1) // per_request
+    req = (torch.arange(M, dtype=torch.int32) // per_request).cuda()
+    bias, gate = torch.from_numpy(rnd(75, "b", (N,), 0.5)).cuda(), torch.from_numpy(rnd(76, "g", (n_req, N))).cuda()
+    x0 = torch.from_numpy(rnd(77, "x", (M, N))).cuda()
+    out = x0.clone()
+    assert B.dit_op_gemm(None, A.data_ptr(), K, W.data_ptr(), K, bias.data_ptr(), M, N, K, 3, out.data_ptr(), N, gate.data_ptr(), N,
+                         req.data_ptr()) == 0
+    torch.cuda.synchronize()
+    Ad, Wd = A.double(), W[:N].double()
+    prod, mag = Ad @ Wd.T + bias.double(), Ad.abs() @ Wd.T.abs() + bias.double().abs()
+    g = gate.double()[req.long()]
+    bound = (K + 3) * 2.0 ** -24 * (x0.double().abs() + g.abs() * mag)
+    assert bool(((out.double() - (x0.double() + g * prod)).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("M,N,K", [(321, 264, 64), (65, 256, 512), (700, 130, 4608)])
 def test_gemm_tiles_agree_bit_for_bit(torch, B, M, N, K):
     """Every tile adds a product's terms in the same order, also where it multiplies with 16x16x32 MFMAs instead of
