@@ -19,7 +19,9 @@ inline bool first_use_on_device(std::atomic<unsigned>& mask) {
 }
 
 // ---- GEMM ---------------------------------------------------------------------------
-enum { OUT_BF16 = 0, OUT_F32 = 1, OUT_GELU_BF16 = 2, OUT_RESID_F32 = 3, OUT_QKNORM = 4 };
+enum { OUT_BF16 = 0, OUT_F32 = 1, OUT_GELU_BF16 = 2, OUT_RESID_F32 = 3, OUT_QKNORM = 4, OUT_VT = 5, OUT_GEGLU = 6 };
+// OUT_VT: bf16 results written transposed, qk.vt[n * qk.ldvt + qk.vt_col[m]]; columns of vt that no row maps to are left alone.
+// OUT_GEGLU (GemmBatch::geglu): gelu_tanh(A W^T) * (A W2^T) as bf16.  No bias in either.
 
 // OUT_QKNORM (only in the tile variants whose waves own 64 output columns): output columns [0, nq) are
 // queries and [nq, nq+nk) keys: per head RMS norm (eps
@@ -43,6 +45,7 @@ struct QkNorm {
 struct GemmProblem {
   const bf16_t* A; int lda;     // [M][lda] activations
   const bf16_t* W; int ldw;     // [N_pad][ldw] weights, out-major
+  const bf16_t* W2 = nullptr;   // OUT_GEGLU: the second matrix, same shape; N counts the columns of both
   const float* bias;            // [N] or null
   int M, N, K;
   int out_kind; void* out; int ldc;
@@ -64,6 +67,9 @@ struct GemmProblem {
 };
 struct GemmBatch {
   int n; int total_tiles; GemmProblem p[3];
+  // two problems of one A and one shape, p[0] the gate and p[1] the values: only gelu_tanh(C0) * C1 is stored, as bf16 to
+  // p[0].out (both kinds OUT_BF16, no bias)
+  int geglu = 0;
   int splits = 1;                // split-K shares (chosen by the launcher)
   float* partial = nullptr;      // device scratch for split-K partial tiles, or null (no split-K)
   size_t partial_bytes = 0;
@@ -180,7 +186,6 @@ void launch_copy_rows_f32(hipStream_t s, const float* src, const int* src_row, f
 void launch_embed_gather(hipStream_t s, const int* tokens, const float* table, float* x, int M, int d, int vocab);
 // y = x / sqrt(mean(x^2) + 1e-6) * gain; y (bf16) and y32 (fp32) are each optional; d % 256 == 0
 void launch_rmsnorm(hipStream_t s, const float* x, const float* gain, bf16_t* y, float* y32, int M, int d);
-void launch_geglu(hipStream_t s, const bf16_t* a, const bf16_t* b, bf16_t* out, long long n);   // n % 8 == 0
 // bias[h][delta + L - 1] = table[bucket(delta)][h] for delta in (-L, L); table fp32 [32][H]
 void launch_rel_bias_table(hipStream_t s, const float* table, float* bias, int H, int L);
 

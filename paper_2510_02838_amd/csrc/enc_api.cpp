@@ -96,9 +96,9 @@ uint16_t h_f2bf(float f) {
 }
 
 struct Layout {
-  size_t meta, x, h, q, k, v, vt, o, a, b, act, bias, partial, total;
+  size_t meta, x, h, q, k, vt, o, act, bias, partial, total;
   // offsets inside meta
-  size_t o_cu, o_vt_off, o_src_of_col, o_tiles;
+  size_t o_cu, o_vt_off, o_vt_col, o_tiles;
   int M, cols_pad, L, n_tiles;
 };
 
@@ -116,15 +116,13 @@ bool lens_ok(int n_seq, const int* lens) {
 void plan(const enc_ctx* c, int n_seq, const int* lens, Layout& L, std::vector<unsigned char>* meta) {
   const enc_config& g = c->cfg;
   const size_t d = g.d_model, inner = (size_t)g.n_heads * g.head_dim, dff = g.d_ff;
-  std::vector<int> cu(1, 0), vt_off, src;
+  std::vector<int> cu(1, 0), vt_off, vt_col;     // vt_col: column of the transposed values for each token
   std::vector<AttnTile> tiles;
   int col = 0, longest = 0;
   for (int s = 0; s < n_seq; ++s) {
     vt_off.push_back(col);
-    for (int t = 0; t < lens[s]; ++t) src.push_back(cu.back() + t);
-    const int pad = (int)rup(lens[s], 64);
-    for (int t = lens[s]; t < pad; ++t) src.push_back(-1);
-    col += pad;
+    for (int t = 0; t < lens[s]; ++t) vt_col.push_back(col + t);
+    col += (int)rup(lens[s], 64);
     for (int q0 = 0; q0 < lens[s]; q0 += 128) tiles.push_back(AttnTile{s, q0});
     longest = std::max(longest, lens[s]);
     cu.push_back(cu.back() + lens[s]);
@@ -140,7 +138,7 @@ void plan(const enc_ctx* c, int n_seq, const int* lens, Layout& L, std::vector<u
   };
   L.o_cu = put(cu.data(), cu.size() * 4);
   L.o_vt_off = put(vt_off.data(), vt_off.size() * 4);
-  L.o_src_of_col = put(src.data(), src.size() * 4);
+  L.o_vt_col = put(vt_col.data(), vt_col.size() * 4);
   L.o_tiles = put(tiles.data(), tiles.size() * sizeof(AttnTile));
   const size_t meta_bytes = rup(mo, 256);
   if (meta) meta->resize(meta_bytes);
@@ -150,10 +148,10 @@ void plan(const enc_ctx* c, int n_seq, const int* lens, Layout& L, std::vector<u
   L.meta = take(meta_bytes);
   L.x = take(M * d * 4);
   L.h = take(M * d * 2);
-  L.q = take(M * inner * 2); L.k = take(M * inner * 2); L.v = take(M * inner * 2);
+  L.q = take(M * inner * 2); L.k = take(M * inner * 2);
   L.vt = take(inner * (size_t)col * 2);
   L.o = take(M * inner * 2);
-  L.a = take(M * dff * 2); L.b = take(M * dff * 2); L.act = take(M * dff * 2);
+  L.act = take(M * dff * 2);
   L.bias = take((size_t)g.n_heads * (2 * (size_t)longest - 1) * 4);
   L.partial = take(PARTIAL_BYTES);
   L.total = o;
@@ -167,9 +165,9 @@ GemmProblem prob(const bf16_t* A, int lda, const bf16_t* W, int ldw, int M, int 
   p.qk = QkNorm{};
   return p;
 }
-void gemm(enc_ctx* c, float* partial, std::initializer_list<GemmProblem> ps) {
+void gemm(enc_ctx* c, float* partial, std::initializer_list<GemmProblem> ps, bool geglu = false) {
   GemmBatch b;
-  b.n = 0; b.total_tiles = 0;
+  b.n = 0; b.total_tiles = 0; b.geglu = geglu;
   for (const GemmProblem& p : ps) b.p[b.n++] = p;
   b.partial = partial; b.partial_bytes = PARTIAL_BYTES;
   launch_gemm(c->stream, b);
@@ -346,26 +344,30 @@ dit_status enc_forward(enc_ctx* c, int n_seq, const int* lens, const int* tokens
   const int M = L.M, d = g.d_model, H = g.n_heads, dh = g.head_dim, inner = H * dh, dff = g.d_ff;
   float* x = (float*)(ws + L.x);
   bf16_t* h = (bf16_t*)(ws + L.h);
-  bf16_t* q = (bf16_t*)(ws + L.q); bf16_t* k = (bf16_t*)(ws + L.k); bf16_t* v = (bf16_t*)(ws + L.v);
+  bf16_t* q = (bf16_t*)(ws + L.q); bf16_t* k = (bf16_t*)(ws + L.k);
   bf16_t* vt = (bf16_t*)(ws + L.vt); bf16_t* o = (bf16_t*)(ws + L.o);
-  bf16_t* a = (bf16_t*)(ws + L.a); bf16_t* b = (bf16_t*)(ws + L.b); bf16_t* act = (bf16_t*)(ws + L.act);
+  bf16_t* act = (bf16_t*)(ws + L.act);
   float* bias = (float*)(ws + L.bias);
   float* partial = (float*)(ws + L.partial);
   const int* cu = (const int*)(ws + L.meta + L.o_cu);
   const int* vt_off = (const int*)(ws + L.meta + L.o_vt_off);
-  const int* src_of_col = (const int*)(ws + L.meta + L.o_src_of_col);
+  const int* vt_col = (const int*)(ws + L.meta + L.o_vt_col);
   const AttnTile* tiles = (const AttnTile*)(ws + L.meta + L.o_tiles);
 
   launch_embed_gather(s, tokens, Wv(c, "embed"), x, M, d, g.vocab);
   launch_rel_bias_table(s, Wv(c, "rel_bias"), bias, H, L.L);
+  // (pad columns of the transposed values: no product writes them)
+  launch_fill_u16(s, vt, (long long)inner * L.cols_pad, 0);
   for (int l = 0; l < g.n_layers; ++l) {
     const std::string p = "l" + std::to_string(l);
     launch_rmsnorm(s, x, Wv(c, p + ".ln1.g"), h, nullptr, M, d);
     ETAP(p + ".ln1", h, (size_t)M * d * 2);
+    // the values go out transposed, head by head, as the attention reads them
+    GemmProblem pv = prob(h, d, Wm(c, p + ".v.w"), Wld(c, p + ".v.w"), M, inner, d, OUT_VT, nullptr, 0);
+    pv.qk.nq = pv.qk.nk = 0; pv.qk.vt = vt; pv.qk.ldvt = L.cols_pad; pv.qk.vt_col = vt_col;
     gemm(c, partial, {prob(h, d, Wm(c, p + ".q.w"), Wld(c, p + ".q.w"), M, inner, d, OUT_BF16, q, inner),
                       prob(h, d, Wm(c, p + ".k.w"), Wld(c, p + ".k.w"), M, inner, d, OUT_BF16, k, inner),
-                      prob(h, d, Wm(c, p + ".v.w"), Wld(c, p + ".v.w"), M, inner, d, OUT_BF16, v, inner)});
-    launch_v_transpose(s, v, inner, 0, H, dh, src_of_col, L.cols_pad, vt, L.cols_pad);
+                      pv});
     AttnArgs at;
     at.q = q; at.ldq = inner; at.k = k; at.ldk = inner; at.vt = vt; at.ldvt = L.cols_pad; at.o = o; at.ldo = inner;
     at.n_heads = H; at.head_dim = dh; at.cu_q = cu; at.cu_k = cu; at.vt_off = vt_off;
@@ -377,9 +379,8 @@ dit_status enc_forward(enc_ctx* c, int n_seq, const int* lens, const int* tokens
     gemm(c, partial, {prob(o, inner, Wm(c, p + ".o.w"), Wld(c, p + ".o.w"), M, d, inner, OUT_RESID_F32, x, d)});
     ETAP(p + ".x_attn", x, (size_t)M * d * 4);
     launch_rmsnorm(s, x, Wv(c, p + ".ln2.g"), h, nullptr, M, d);
-    gemm(c, partial, {prob(h, d, Wm(c, p + ".wi0.w"), Wld(c, p + ".wi0.w"), M, dff, d, OUT_BF16, a, dff),
-                      prob(h, d, Wm(c, p + ".wi1.w"), Wld(c, p + ".wi1.w"), M, dff, d, OUT_BF16, b, dff)});
-    launch_geglu(s, a, b, act, (long long)M * dff);
+    gemm(c, partial, {prob(h, d, Wm(c, p + ".wi0.w"), Wld(c, p + ".wi0.w"), M, dff, d, OUT_BF16, act, dff),
+                      prob(h, d, Wm(c, p + ".wi1.w"), Wld(c, p + ".wi1.w"), M, dff, d, OUT_BF16, act, dff)}, true);
     ETAP(p + ".act", act, (size_t)M * dff * 2);
     gemm(c, partial, {prob(act, dff, Wm(c, p + ".wo.w"), Wld(c, p + ".wo.w"), M, d, dff, OUT_RESID_F32, x, d)});
     ETAP(p + ".x_out", x, (size_t)M * d * 4);

@@ -1,5 +1,5 @@
 // Row-wise kernels of the Encode stage (T5-v1.1-style text encoder): embedding lookup, RMS
-// norm, the gated-GELU product and the relative-position bias table.  The matrix products and
+// norm and the relative-position bias table.  The matrix products and
 // the attention of the stage run in gemm.hip / attention.hip.
 #include "dit_internal.h"
 
@@ -11,7 +11,6 @@ __device__ __forceinline__ uint16_t e_f2bf(float f) {
   u += 0x7FFFu + ((u >> 16) & 1u);
   return (uint16_t)(u >> 16);
 }
-__device__ __forceinline__ float e_bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ __forceinline__ uint32_t e_pack2(float a, float b) { return (uint32_t)e_f2bf(a) | ((uint32_t)e_f2bf(b) << 16); }
 __device__ __forceinline__ float e_wave_sum(float v) {
 #pragma unroll
@@ -109,36 +108,6 @@ void launch_rmsnorm(hipStream_t s, const float* x, const float* gain, bf16_t* y,
   if (d <= 1024) hipLaunchKernelGGL(rmsnorm_kernel<4>, dim3((M + 3) / 4), dim3(256), 0, s, x, gain, y, y32, M, d);
   else if (d <= 4096) hipLaunchKernelGGL(rmsnorm_wide_kernel<4>, dim3(M), dim3(256), 0, s, x, gain, y, y32, M, d);
   else hipLaunchKernelGGL(rmsnorm_wide_kernel<8>, dim3(M), dim3(256), 0, s, x, gain, y, y32, M, d);
-}
-
-// act = gelu_tanh(a) * b   elementwise on bf16, 8 elements per thread
-__global__ __launch_bounds__(256) void geglu_kernel(const bf16_t* __restrict__ a, const bf16_t* __restrict__ b,
-                                                    bf16_t* __restrict__ out, long long n8) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n8) return;
-  const uint4 ra = ((const uint4*)a)[i], rb = ((const uint4*)b)[i];
-  const uint32_t wa[4] = {ra.x, ra.y, ra.z, ra.w}, wb[4] = {rb.x, rb.y, rb.z, rb.w};
-  uint32_t wo[4];
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    float r[2];
-#pragma unroll
-    for (int hlf = 0; hlf < 2; ++hlf) {
-      const float x = e_bf2f((uint16_t)(hlf ? wa[p] >> 16 : wa[p] & 0xFFFF));
-      const float y = e_bf2f((uint16_t)(hlf ? wb[p] >> 16 : wb[p] & 0xFFFF));
-      // 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)), u = sqrt(2/pi) (x + 0.044715 x^3)
-      const float t = x * (0.7978845608028654f + 0.035677408136300125f * x * x);
-      r[hlf] = x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-2.8853900817779268f * t)) * y;
-    }
-    wo[p] = e_pack2(r[0], r[1]);
-  }
-  ((uint4*)out)[i] = make_uint4(wo[0], wo[1], wo[2], wo[3]);
-}
-
-void launch_geglu(hipStream_t s, const bf16_t* a, const bf16_t* b, bf16_t* out, long long n) {
-  if (n == 0) return;
-  const long long n8 = n / 8;                                   // n is a multiple of 8 (row length is)
-  hipLaunchKernelGGL(geglu_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, a, b, out, n8);
 }
 
 // bias[h][delta + L - 1] = table[bucket(delta)][h], delta = key position - query position in

@@ -208,7 +208,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
 #pragma unroll
   for (int i = 0; i < LB; ++i) {
     const int r = (i * (WM * WN) + wave) * RPL + lane / CPR, pc = lane % CPR, c = pc ^ swz_key<BKT>(r);
-    gb[i] = (uint32_t)r * (uint32_t)P.ldw + c * 8; // weights are padded to N_pad rows
+    const int rw = !CONV && MODE == 0 && P.out_kind == OUT_GEGLU ? (r >> 6) * 32 + (r & 31) : r;
+    gb[i] = (uint32_t)rw * (uint32_t)P.ldw + c * 8; // weights are padded to N_pad rows
   }
 
 
@@ -234,7 +235,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   }
   // lanes address their tile by 32-bit byte offsets from its first row, so no operand size limit
   const bf16_t* const tileA = CONV ? P.A + conv_pix0 * (size_t)P.conv_cin : P.A + (size_t)m0 * P.lda;
-  const bf16_t* const tileW = P.W + (size_t)n0 * P.ldw;
+  // a gated pair: every 64 columns of the tile are 32 of the gate and the same 32 of the values
+  const bool pair = !CONV && MODE == 0 && P.out_kind == OUT_GEGLU;
+  const bf16_t* const tileW = P.W + (size_t)(pair ? n0 >> 1 : n0) * P.ldw;
+  const bf16_t* const tileW2 = pair ? P.W2 + (size_t)(n0 >> 1) * P.ldw : tileW;
   const int half = lane >> 5;
   // LDS byte offsets of this lane's fragment rows (the chunk index is XORed in per k-step;
   // the key is the same for rows 32 apart)
@@ -263,7 +267,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
 #pragma unroll
     for (int i = 0; i < LA; ++i) buffer_load_lds16(tileA, (lptr_t)(dA + (i * NT + wave * 64) * 16), ga[i] * 2u, ka * 2);
 #pragma unroll
-    for (int i = 0; i < LB; ++i) buffer_load_lds16(tileW, (lptr_t)(dB + (i * NT + wave * 64) * 16), gb[i] * 2u, ks * 2);
+    for (int i = 0; i < LB; ++i)      // (a load's rows lie in one half of their 64)
+      buffer_load_lds16(((i * (WM * WN) + wave) * RPL >> 5) & 1 ? tileW2 : tileW, (lptr_t)(dB + (i * NT + wave * 64) * 16), gb[i] * 2u, ks * 2);
   };
   auto load_frags = [&](const unsigned char* st, int kk, bf16x8 (&a)[TM], bf16x8 (&b)[TN]) {
     const int c = kk * 2 + half;
@@ -691,7 +696,47 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
     }
    }
   };
-  if (P.out_kind == OUT_QKNORM) {
+  // gated pair: the wave's 64 columns are 32 of the gate, then the same 32 of the values
+  auto epilogue_pair = [&]() {
+    if constexpr (BN / WN == 64) {
+      const int lr = lane >> 2, lc = (lane & 3) * 8;
+      const int n = (n0 >> 1) + wn * 32 + lc, n_end = P.N >> 1;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            *(float*)(stg + acc_row(e) * RS + (j * 32 + acc_col) * 4) = acc[i][j][e];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+          const int row = it * 16 + lr, m = m0 + wm * (BM / WM) + i * 32 + row;
+          float v[8];
+#pragma unroll
+          for (int c4 = 0; c4 < 2; ++c4) {
+            const f32x4 g = *(const f32x4*)(stg + row * RS + (lc + 4 * c4) * 4), u = *(const f32x4*)(stg + row * RS + (32 + lc + 4 * c4) * 4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[4 * c4 + c] = gelu_tanh(g[c]) * u[c];
+          }
+          if (m >= P.M || n >= n_end) continue;
+          bf16_t* xp = (bf16_t*)P.out + (size_t)m * P.ldc + n;
+          if (n + 8 <= n_end) {
+            u32x4 w;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) w[c] = pack2bf(v[2 * c], v[2 * c + 1]);
+            *(u32x4*)xp = w;
+          } else {
+            for (int c = 0; c < n_end - n; ++c) xp[c] = f2bf(v[c]);
+          }
+        }
+        asm volatile("" ::: "memory");
+      }
+    }
+  };
+  if (P.out_kind == OUT_GEGLU) { if constexpr (!CONV) epilogue_pair(); }
+  else if (P.out_kind == OUT_VT) { if constexpr (!CONV) epilogue_vt(); }
+  else if (P.out_kind == OUT_QKNORM) {
     if (n0 < P.qk.nq + P.qk.nk) epilogue_qk();
     else if (P.qk.vt) epilogue_vt();
     else epilogue(std::integral_constant<int, OUT_BF16>{});
@@ -802,6 +847,7 @@ __global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
     int tm, tn;
     tile_coords(P, bid - P.tile_start, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
+    const bool pair = !CONV && P.out_kind == OUT_GEGLU;                      // every 64 columns: 32 of the gate, the same 32 of the values
     int ln = lane;
     asm volatile("" : "+v"(ln));                                           // (made anew for each tile: kept, these would cost registers)
     auto window = [&](int m) {    // convolution: top-left pixel of row m's 3x3 window in the stack of bordered images
@@ -821,10 +867,11 @@ __global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
       const int r = (i * 8 + wave) * 8 + (ln >> 3), c = (ln & 7) ^ swz_key8(r);
-      ob[i] = ((uint32_t)r * (uint32_t)P.ldw + c * 8) * 2u;                // weights are padded to N_pad rows
+      const int rw = pair ? (r >> 6) * 32 + (r & 31) : r;
+      ob[i] = ((uint32_t)rw * (uint32_t)P.ldw + c * 8) * 2u;               // weights are padded to N_pad rows
     }
     sA = P.A + (CONV ? pix0 * (size_t)P.conv_cin : (size_t)m0 * P.lda);
-    sW = P.W + (size_t)n0 * P.ldw;
+    sW = (pair && (wave & 4) ? P.W2 : P.W) + (size_t)(pair ? n0 >> 1 : n0) * P.ldw;   // (waves 4-7 load the upper half of each 64 rows)
     ks = 0; ks_n = P.K / BKT; ka = 0;
     if constexpr (CONV) {
       run_len = run_left = 3 * P.conv_cin / BKT; rows_left = 3;
@@ -1340,7 +1387,46 @@ __global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
         }
       }
     };
+    // gated pair: the wave's 64 columns are 32 of the gate (acc[.][0, 1]) and the same 32 of the values (acc[.][2, 3])
+    auto gated = [&]() {
+      const int n_end = N >> 1, nw2 = nw >> 1;
+      bf16_t* const out = (bf16_t*)P.out;
+      const int ldc = P.ldc, fr = ln >> 2, fc = ln & 3;  // my row (and the one 16 on) and piece when 32 rows are read back
+      auto at = [&](int f, int chunk) { return patch + f * 64 + ((chunk ^ ((f >> 2) & 3)) << 4); };
+      const bool full = nw2 + fc * 8 + 8 <= n_end;
+      const uint32_t voff = (uint32_t)(fr * ldc + fc * 8) * 2u;
+#pragma unroll
+      for (int i = 0; i < RT / 2; ++i) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int r = 2 * i + q;
+          float v[8], u[8];
+          raw(r, 0, v); raw(r, 1, u);
+          u32x4 w;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) w[c] = pack2bf(gelu_tanh(v[2 * c]) * u[2 * c], gelu_tanh(v[2 * c + 1]) * u[2 * c + 1]);
+          *(u32x4*)at(q * 16 + l16, kq) = w;
+        }
+        asm volatile("" ::: "memory");
+        u32x4 w[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) w[h] = *(const u32x4*)at(h * 16 + fr, fc);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int k = i * 32 + h * 16;
+          char* const xp = (char*)(out + (size_t)(mw + k) * ldc + nw2) + voff;
+          if (fr < M - mw - k) {
+            if (full) *(u32x4*)xp = w[h];
+            else
+              for (int c = 0; c < n_end - nw2 - fc * 8; ++c) ((bf16_t*)xp)[c] = (bf16_t)(w[h][c >> 1] >> (16 * (c & 1)));
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
     if constexpr (!CONV) {
+      if (kind == OUT_GEGLU) { gated(); return; }
       if (kind == OUT_QKNORM && n0 < P.qk.nq + P.qk.nk) { norm_rope(); return; }
       if (vt) { transposed(); return; }
       if (kind == OUT_GELU_BF16) { plain_bf16(std::true_type{}); return; }
@@ -1370,7 +1456,7 @@ __global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
     int tm, tn;
     tile_coords(P, bid - P.tile_start, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
-    const bool vt = !CONV && P.out_kind == OUT_QKNORM && P.qk.vt && n0 >= P.qk.nq + P.qk.nk;
+    const bool vt = !CONV && (P.out_kind == OUT_VT || (P.out_kind == OUT_QKNORM && P.qk.vt && n0 >= P.qk.nq + P.qk.nk));
     if (!CONV && vt) run(std::true_type{}, P.K / BKT);
     else run(std::false_type{}, P.K / BKT);
     if (!STREAM) {                           // the redundant tail loads, before the stages are filled again
@@ -1386,6 +1472,8 @@ __global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
 // result does not depend on which workgroup finished first) and applies the epilogue.  One
 // thread per float4 of the chunk layout written above: 4 consecutive rows of one column, the
 // 32 lanes of a half-wave on 32 consecutive columns.
+//   A gated pair's reduction covers the tiles of the gate and adds up both; OUT_VT: 4 rows of a column are 4 neighbours
+// of a row of the transposed matrix.
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmBatch batch) {
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
@@ -1402,22 +1490,47 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmBatch batc
   const int wm = wave / WN, wn = wave % WN;
   const int n = tn * BN + wn * (BN / WN) + j * 32 + (lane & 31);
   const int mrow = tm * BM + wm * (BM / WM) + i * 32 + 8 * g + 4 * (lane >> 5);
-  const float* pc = batch.partial + (size_t)tile * batch.splits * (BM * BN) + (size_t)q * 4;
-  f32x4 acc = *(const f32x4*)pc;
-  int s = 1;
-  for (; s + 3 < batch.splits; s += 4) {           // four loads in flight; added in the same order
-    f32x4 t4[4];
+  auto sum = [&](int t) {
+    const float* pc = batch.partial + (size_t)t * batch.splits * (BM * BN) + (size_t)q * 4;
+    f32x4 acc = *(const f32x4*)pc;
+    int s = 1;
+    for (; s + 3 < batch.splits; s += 4) {           // four loads in flight; added in the same order
+      f32x4 t4[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) t4[u] = *(const f32x4*)(pc + (size_t)(s + u) * (BM * BN));
+      for (int u = 0; u < 4; ++u) t4[u] = *(const f32x4*)(pc + (size_t)(s + u) * (BM * BN));
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc[c] += t4[u][c];
+        for (int c = 0; c < 4; ++c) acc[c] += t4[u][c];
+    }
+    for (; s < batch.splits; ++s) {
+      const f32x4 t4 = *(const f32x4*)(pc + (size_t)s * (BM * BN));
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] += t4[c];
+    }
+    return acc;
+  };
+  f32x4 acc = sum(tile);
+  if (batch.geglu) {
+    const f32x4 up = sum(tile + batch.p[1].tile_start);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = gelu_tanh(acc[c]) * up[c];
   }
-  for (; s < batch.splits; ++s) {
-    const f32x4 t4 = *(const f32x4*)(pc + (size_t)s * (BM * BN));
+  if (P.out_kind == OUT_VT) {
+    if (n >= P.N) return;
+    const float bias = P.bias ? P.bias[n] : 0.f;
+    bf16_t* dst = P.qk.vt + (size_t)n * P.qk.ldvt;
+    int col[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[c] += t4[c];
+    for (int c = 0; c < 4; ++c) col[c] = mrow + c < P.M ? P.qk.vt_col[mrow + c] : -1;
+    if (col[3] == col[0] + 3 && col[1] == col[0] + 1 && col[2] == col[0] + 2 && col[0] >= 0 && (col[0] & 3) == 0) {
+      *(uint2*)(dst + col[0]) = make_uint2(pack2bf(acc[0] + bias, acc[1] + bias), pack2bf(acc[2] + bias, acc[3] + bias));
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (col[c] >= 0) dst[col[c]] = f2bf(acc[c] + bias);
+    }
+    return;
   }
   float cs = 0.f, cq = 0.f;               // sum and sum of squares of the values stored, this thread's rows of the column
   if (n < P.N) {
@@ -1490,7 +1603,7 @@ static void launch_t(hipStream_t s, GemmBatch& b) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (MODE == 4) {
     hipLaunchKernelGGL(kern, dim3(total * b.splits), dim3(WM * WN * 64), lds, s, b);
-    hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, WM, WN>), dim3(total * (BM * BN / 1024)), dim3(256), 0, s, b);
+    hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, WM, WN>), dim3((b.geglu ? total / 2 : total) * (BM * BN / 1024)), dim3(256), 0, s, b);
   } else {
     hipLaunchKernelGGL(kern, dim3(total), dim3(WM * WN * 64), lds, s, b);
   }
@@ -1675,6 +1788,16 @@ int choose_tile(GemmBatch& b, int force_tile) {
 
 int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
   int tile = choose_tile(b, force_tile);
+  bool narrow = false;                  // epilogues that need waves of 64 columns (the split reduction has its own)
+  for (int i = 0; i < b.n; ++i) narrow = narrow || b.p[i].out_kind == OUT_VT;
+  if ((narrow || b.geglu) && (tile == 30064128 || tile == 30032128)) tile = 30128128;
+  if (b.geglu && tile < 40000000) {     // unsplit: one problem whose tiles hold both products of their columns
+    if (b.n != 2 || b.p[0].A != b.p[1].A || b.p[0].M != b.p[1].M || b.p[0].N != b.p[1].N || b.p[0].ldw != b.p[1].ldw) return -1;
+    b.p[0].W2 = b.p[1].W;
+    b.p[0].N *= 2;
+    b.p[0].out_kind = OUT_GEGLU;
+    b.n = 1;
+  }
   bool conv = false, plain = false, qknorm = false;
   for (int i = 0; i < b.n; ++i) {
     conv = conv || b.p[i].conv_w > 0; plain = plain || b.p[i].conv_w <= 0;

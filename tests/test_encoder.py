@@ -180,6 +180,33 @@ def test_encoder_intermediates_and_batch_independence(torch, X):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("lens", [[31], [33, 61], [77, 130, 125], [77, 200, 33, 131, 97, 500, 51], [500, 431, 351, 287, 255, 201, 163, 127, 97, 77, 77, 64, 51, 43, 33, 31]])
+def test_encoder_benchmark_widths_over_the_tiles(torch, X, lens):
+    """One layer of the benchmark widths, from the split tiles for few rows to the 8-wave tiles, with prompts of odd length
+    (the transposed values of a product's rows then start anywhere, break inside a tile and leave pad columns between
+    the prompts): prompts of up to 130 tokens against the oracle."""
+    arch = dict(synth.ENCODERS["t5_xxl"], n_layers=1, vocab=1024)
+    m = X.Encoder(arch)
+    m.ensure_workspace(lens)
+    m.workspace.fill_(0xFF)                              # NaN in whatever is read without having been written
+    m.init_weights(3, 0.008)
+    shapes = E.param_shapes(arch)
+    params = {n: m.get_tensor(n, shapes[n][0]) for n in shapes}
+    toks = synth.make_tokens(lens, arch["vocab"])
+    out = torch.empty((sum(lens), arch["d_model"]), dtype=torch.float32, device="cuda")
+    m.forward(lens, torch.from_numpy(np.concatenate(toks)).cuda(), None, out)
+    torch.cuda.synchronize()
+    got, ora, at = out.cpu().numpy(), E.EncoderOracle(arch, params), 0
+    assert np.isfinite(got).all()
+    for n, t in zip(lens, toks):
+        if n <= 130:
+            ref = ora.forward(t)
+            assert rel_l2(got[at:at + n], ref) <= 1e-2, (n, rel_l2(got[at:at + n], ref))
+        at += n
+    m.close()
+
+
+@pytest.mark.gpu
 def test_encoder_device_init_matches_host_generator_and_feeds_the_denoiser(torch, X):
     """Weights from the device generator equal the host recipe bit for bit; the bf16 output has
     the layout the denoising step takes as its condition."""
