@@ -479,7 +479,8 @@ GemmProblem with_vt(GemmProblem p, bf16_t* vt, int ldvt, const int* vt_col) {
   p.qk.vt = vt; p.qk.ldvt = ldvt; p.qk.vt_col = vt_col;
   return p;
 }
-void run_gemm(dit_ctx* c, std::initializer_list<GemmProblem> ps) {
+// Returns whether the layer norms that the problems ask for (GemmProblem::ln_y) are done.
+bool run_gemm(dit_ctx* c, std::initializer_list<GemmProblem> ps) {
   GemmBatch b;
   b.n = 0; b.total_tiles = 0;
   double flop = 0, bytes = 0;
@@ -489,10 +490,16 @@ void run_gemm(dit_ctx* c, std::initializer_list<GemmProblem> ps) {
     flop += 2.0 * p.M * p.N * p.K;
     bytes += 2.0 * ((double)p.M * p.K + (double)p.N * p.K) + (double)p.M * p.N * (p.out_kind == OUT_RESID_F32 ? 8 : p.out_kind == OUT_F32 ? 4 : 2);
   }
-  if (!b.n) return;
+  if (!b.n) return false;
   b.partial = c->gemm_partial; b.partial_bytes = c->gemm_partial ? GEMM_PARTIAL_BYTES : 0;
   Scope sc(c, DIT_PROF_GEMM, flop, bytes);
   if (launch_gemm(c->stream, b) < 0) c->launch_refused = true;     // shape outside the kernels' limits: reported by the call
+  return b.ln_done != 0;
+}
+// the residual product `p` with the layer norm that follows it (shift and scale of its modulation, output y)
+GemmProblem with_ln(GemmProblem p, bf16_t* y, const float* shift, const float* scale) {
+  p.ln_y = y; p.ln_shift = shift; p.ln_scale = scale;
+  return p;
 }
 
 dit_status do_tap(dit_ctx* c, const std::string& name, const void* src, int rows, int cols, int elem, int ld) {
@@ -562,7 +569,9 @@ void run_attention(dit_ctx* c, const Run& R, const bf16_t* q, int ldq, const bf1
 }
 
 // joint two-stream block (families J and F-double)
-dit_status joint_block(dit_ctx* c, const Run& R, const std::string& p, const float* mod, int mod_off) {
+// normed: its first layer norm is done already.  last: no block of this kind follows (else its first norm may be done here,
+// and `normed` is set).
+dit_status joint_block(dit_ctx* c, const Run& R, const std::string& p, const float* mod, int mod_off, bool last, bool& normed) {
   const dit_config& g = c->cfg;
   const Plan& P = R.P; const WsLayout& L = R.L;
   const int d = g.hidden, dff = g.mlp_hidden, Nt = P.Nt, Ni = P.Ni, Ns = P.Ns, MC = L.MC;
@@ -576,7 +585,7 @@ dit_status joint_block(dit_ctx* c, const Run& R, const std::string& p, const flo
   const std::string pt = p + ".txt", pi = p + ".img";
   const float* mt = mod + mod_off;           // text stream: 6d
   const float* mi = mod + mod_off + 6 * d;   // image stream: 6d
-  {
+  if (!normed) {
     Scope sc(c, DIT_PROF_LNMOD, 0, 6.0 * Ns * d);
     launch_ln_modulate(c->stream, x, h, Ns, d, mt, mt + d, MC, rreq, nullptr, nullptr, nullptr, Nt, mi, mi + d);
   }
@@ -605,24 +614,34 @@ dit_status joint_block(dit_ctx* c, const Run& R, const std::string& p, const flo
                 (const AttnTile*)(R.ws + L.meta + P.o_tiles), (int)P.tiles.size(), R.ip(P.o_j2s), P.attn_flop,
                 gmax(c, pt + ".qnorm.g", pi + ".qnorm.g"), gmax(c, pt + ".knorm.g", pi + ".knorm.g"), nullptr, true);
   TAP(p + ".attn", o, Ns, d, 2, d);   // stream order: text rows, then image rows
-  run_gemm(c, {mk(o, d, Wm(c, pt + ".proj.w"), Wld(c, pt + ".proj.w"), Wv(c, pt + ".proj.b"), Nt, d, d, OUT_RESID_F32, x, d, mt + 2 * d, MC, rreq),
-               mk(o + (size_t)Nt * d, d, Wm(c, pi + ".proj.w"), Wld(c, pi + ".proj.w"), Wv(c, pi + ".proj.b"), Ni, d, d, OUT_RESID_F32, x + (size_t)Nt * d, d, mi + 2 * d, MC, rreq + Nt)});
+  GemmProblem pp_t = mk(o, d, Wm(c, pt + ".proj.w"), Wld(c, pt + ".proj.w"), Wv(c, pt + ".proj.b"), Nt, d, d, OUT_RESID_F32, x, d, mt + 2 * d, MC, rreq);
+  GemmProblem pp_i = mk(o + (size_t)Nt * d, d, Wm(c, pi + ".proj.w"), Wld(c, pi + ".proj.w"), Wv(c, pi + ".proj.b"), Ni, d, d, OUT_RESID_F32, x + (size_t)Nt * d, d, mi + 2 * d, MC, rreq + Nt);
+  if (fuse) {
+    pp_t = with_ln(pp_t, h, mt + 3 * d, mt + 4 * d);
+    pp_i = with_ln(pp_i, h + (size_t)Nt * d, mi + 3 * d, mi + 4 * d);
+  }
+  normed = run_gemm(c, {pp_t, pp_i});
   TAP(pt + ".x_attn", x, Nt, d, 4, d); TAP(pi + ".x_attn", x + (size_t)Nt * d, Ni, d, 4, d);
-  {
+  if (!normed) {
     Scope sc(c, DIT_PROF_LNMOD, 0, 6.0 * Ns * d);
     launch_ln_modulate(c->stream, x, h, Ns, d, mt + 3 * d, mt + 4 * d, MC, rreq, nullptr, nullptr, nullptr, Nt, mi + 3 * d, mi + 4 * d);
   }
   run_gemm(c, {mk(h, d, Wm(c, pt + ".mlp1.w"), Wld(c, pt + ".mlp1.w"), Wv(c, pt + ".mlp1.b"), Nt, dff, d, OUT_GELU_BF16, act, dff),
                mk(h + (size_t)Nt * d, d, Wm(c, pi + ".mlp1.w"), Wld(c, pi + ".mlp1.w"), Wv(c, pi + ".mlp1.b"), Ni, dff, d, OUT_GELU_BF16, act + (size_t)Nt * dff, dff)});
   TAP(pt + ".mlp_act", act, Nt, dff, 2, dff); TAP(pi + ".mlp_act", act + (size_t)Nt * dff, Ni, dff, 2, dff);
-  run_gemm(c, {mk(act, dff, Wm(c, pt + ".mlp2.w"), Wld(c, pt + ".mlp2.w"), Wv(c, pt + ".mlp2.b"), Nt, d, dff, OUT_RESID_F32, x, d, mt + 5 * d, MC, rreq),
-               mk(act + (size_t)Nt * dff, dff, Wm(c, pi + ".mlp2.w"), Wld(c, pi + ".mlp2.w"), Wv(c, pi + ".mlp2.b"), Ni, d, dff, OUT_RESID_F32, x + (size_t)Nt * d, d, mi + 5 * d, MC, rreq + Nt)});
+  GemmProblem pm_t = mk(act, dff, Wm(c, pt + ".mlp2.w"), Wld(c, pt + ".mlp2.w"), Wv(c, pt + ".mlp2.b"), Nt, d, dff, OUT_RESID_F32, x, d, mt + 5 * d, MC, rreq);
+  GemmProblem pm_i = mk(act + (size_t)Nt * dff, dff, Wm(c, pi + ".mlp2.w"), Wld(c, pi + ".mlp2.w"), Wv(c, pi + ".mlp2.b"), Ni, d, dff, OUT_RESID_F32, x + (size_t)Nt * d, d, mi + 5 * d, MC, rreq + Nt);
+  if (fuse && !last) {                        // the next block's modulation lies 12 d on
+    pm_t = with_ln(pm_t, h, mt + 12 * d, mt + 13 * d);
+    pm_i = with_ln(pm_i, h + (size_t)Nt * d, mi + 12 * d, mi + 13 * d);
+  }
+  normed = run_gemm(c, {pm_t, pm_i});
   TAP(pt + ".x_out", x, Nt, d, 4, d); TAP(pi + ".x_out", x + (size_t)Nt * d, Ni, d, 4, d);
   return DIT_OK;
 }
 
 // single-stream block of family F on the joint-ordered residual xj
-dit_status single_block(dit_ctx* c, const Run& R, const std::string& p, const float* mod, int mod_off) {
+dit_status single_block(dit_ctx* c, const Run& R, const std::string& p, const float* mod, int mod_off, bool last, bool& normed) {
   const dit_config& g = c->cfg;
   const Plan& P = R.P; const WsLayout& L = R.L;
   const int d = g.hidden, dff = g.mlp_hidden, Nj = P.Nj, MC = L.MC, wide = d + dff;
@@ -633,7 +652,7 @@ dit_status single_block(dit_ctx* c, const Run& R, const std::string& p, const fl
   const int* rreq = R.ip(P.o_row_req_j);
   const float2* rope = (g.rope_axes[0] + g.rope_axes[1] + g.rope_axes[2]) > 0 ? R.at<float2>(L.rope) : nullptr;
   const float* m = mod + mod_off;
-  {
+  if (!normed) {
     Scope sc(c, DIT_PROF_LNMOD, 0, 6.0 * Nj * d);
     launch_ln_modulate(c->stream, xj, h, Nj, d, m, m + d, MC, rreq, nullptr, nullptr);
   }
@@ -654,7 +673,9 @@ dit_status single_block(dit_ctx* c, const Run& R, const std::string& p, const fl
                 (const AttnTile*)(R.ws + L.meta + P.o_tiles), (int)P.tiles.size(), nullptr, P.attn_flop,
                 gmax(c, p + ".qnorm.g"), gmax(c, p + ".knorm.g"), nullptr, true);
   TAP(p + ".attn", cat, Nj, d, 2, wide);
-  run_gemm(c, {mk(cat, wide, Wm(c, p + ".lin2.w"), Wld(c, p + ".lin2.w"), Wv(c, p + ".lin2.b"), Nj, d, wide, OUT_RESID_F32, xj, d, m + 2 * d, MC, rreq)});
+  GemmProblem po = mk(cat, wide, Wm(c, p + ".lin2.w"), Wld(c, p + ".lin2.w"), Wv(c, p + ".lin2.b"), Nj, d, wide, OUT_RESID_F32, xj, d, m + 2 * d, MC, rreq);
+  if (fuse && !last) po = with_ln(po, h, m + 3 * d, m + 4 * d);      // the next block's modulation lies 3 d on
+  normed = run_gemm(c, {po});
   TAP(p + ".x_out", xj, Nj, d, 4, d);
   return DIT_OK;
 }
@@ -929,15 +950,16 @@ dit_status run_sample(dit_ctx* c, int n_req, const dit_req* reqs, float* latents
     int off = 0;
     if (g.family == DIT_FAMILY_J || g.family == DIT_FAMILY_F) {
       const char* pre = g.family == DIT_FAMILY_J ? "blk" : "dbl";
+      bool normed = false;
       for (int l = 0; l < g.n_blocks; ++l, off += 12 * d) {
         snprintf(nb, sizeof nb, "%s%d", pre, l);
-        if ((st = joint_block(c, R, nb, mstep, off)) != DIT_OK) return st;
+        if ((st = joint_block(c, R, nb, mstep, off, l + 1 == g.n_blocks, normed)) != DIT_OK) return st;
       }
       if (g.n_single > 0) {
         { Scope sc(c, DIT_PROF_OTHER, 0, 0); launch_copy_rows_f32(s, x, nullptr, R.at<float>(L.xj), R.ip(P.o_s2j), P.Ns, d); }
         for (int l = 0; l < g.n_single; ++l, off += 3 * d) {
           snprintf(nb, sizeof nb, "sgl%d", l);
-          if ((st = single_block(c, R, nb, mstep, off)) != DIT_OK) return st;
+          if ((st = single_block(c, R, nb, mstep, off, l + 1 == g.n_single, normed)) != DIT_OK) return st;
         }
         { Scope sc(c, DIT_PROF_OTHER, 0, 0); launch_copy_rows_f32(s, R.at<float>(L.xj), R.ip(P.o_s2j), x, nullptr, P.Ns, d); }
       }

@@ -51,6 +51,9 @@ struct GemmProblem {
   int out_kind; void* out; int ldc;
   const float* gate; int gate_stride; const int* row_req;  // OUT_RESID_F32 only
   QkNorm qk;                                               // OUT_QKNORM only
+  // OUT_RESID_F32 only, optional: a layer norm of the finished rows follows, modulated by (1 + ln_scale) and ln_shift (of the
+  // row's request, gate_stride apart), to ln_y [M][N] as bf16.  A hint: GemmBatch::ln_done says whether it was done.
+  bf16_t* ln_y = nullptr; const float* ln_shift = nullptr; const float* ln_scale = nullptr;
   // 3x3 convolution as a product (conv_w > 0): A is a stack of channels-last bf16 images with a
   // one-pixel zero border each, [B][(H+2)*(conv_w+2)][conv_cin]; conv_img = H*conv_w pixels per
   // image; row m of the product is pixel (r / conv_w, r % conv_w) of image m / conv_img,
@@ -70,6 +73,7 @@ struct GemmBatch {
   // two problems of one A and one shape, p[0] the gate and p[1] the values: only gelu_tanh(C0) * C1 is stored, as bf16 to
   // p[0].out (both kinds OUT_BF16, no bias)
   int geglu = 0;
+  int ln_done = 0;               // set by the launcher: the layer norms of all problems (GemmProblem::ln_y) are done
   int splits = 1;                // split-K shares (chosen by the launcher)
   float* partial = nullptr;      // device scratch for split-K partial tiles, or null (no split-K)
   size_t partial_bytes = 0;

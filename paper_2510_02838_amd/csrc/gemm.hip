@@ -1566,6 +1566,117 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmBatch batc
   }
 }
 
+// The reduction of a residual product with the layer norm that follows it: a workgroup takes four whole rows (of each
+// partial tile's float4s, four rows of a column), 512 columns at a time, writes the residual rows and, from registers,
+// their modulated norm.  What counts here is the number of launches: apart, the reduction of 410 rows of 1536 columns in 5
+// shares takes 7.5 us and the norm 5, both at the latency of a launch; together 2.6 us less.
+template <int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(512) void splitk_reduce_ln_kernel(const GemmBatch batch) {
+  constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+  constexpr int MAXP = 3;                          // up to 1536 columns
+  __shared__ float red[2][8][4];
+  int row4 = blockIdx.x;                           // my four rows: 4 row4 ... of the problem
+  GemmProblem P = batch.p[0];
+  if (batch.n > 1 && row4 >= (P.M + 3) / 4) { row4 -= (P.M + 3) / 4; P = batch.p[1]; }
+  const int tid = threadIdx.x, wv = tid >> 6;
+  const int m0 = row4 * 4, d = P.N;
+  const int tm = m0 / BM, r = m0 % BM;
+  const int i = r % (BM / WM) / 32, g = (r & 31) >> 3, half = (r >> 2) & 1, wm = r / (BM / WM);
+  const int first = tm & ~7, gsz = P.tiles_m - first < 8 ? P.tiles_m - first : 8;
+  const int tile0 = P.tile_start + first * P.tiles_n + (tm - first);      // (tile_coords() backwards; + tn * gsz)
+  int mr[4];
+  const float* gp[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    mr[c] = m0 + c < P.M ? m0 + c : P.M - 1;       // rows past the end repeat the last one and are not stored
+    const size_t req = (size_t)(P.row_req ? P.row_req[mr[c]] : 0) * P.gate_stride;
+    gp[c] = P.gate ? P.gate + req : nullptr;
+  }
+  float x[MAXP][4], s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int p = 0; p < MAXP; ++p) {
+    const int n = p * 512 + tid;
+    if (n >= d) { x[p][0] = x[p][1] = x[p][2] = x[p][3] = 0.f; continue; }
+    const int tn = n / BN, cc = n % BN, wn = cc / (BN / WN), j = cc % (BN / WN) / 32;
+    const int q = ((((wm * WN + wn) * TM + i) * TN + j) * 4 + g) * 64 + half * 32 + (cc & 31);
+    const float* pc = batch.partial + (size_t)(tile0 + tn * gsz) * batch.splits * (BM * BN) + (size_t)q * 4;
+    const float bias = P.bias ? P.bias[n] : 0.f;
+    float x0[4], gt[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      x0[c] = ((const float*)P.out)[(size_t)mr[c] * P.ldc + n];
+      gt[c] = gp[c] ? gp[c][n] : 1.f;
+    }
+    f32x4 acc = *(const f32x4*)pc;                 // (the order of splitk_reduce_kernel)
+    int k = 1;
+    for (; k + 3 < batch.splits; k += 4) {
+      f32x4 t4[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t4[u] = *(const f32x4*)(pc + (size_t)(k + u) * (BM * BN));
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] += t4[u][c];
+    }
+    for (; k < batch.splits; ++k) {
+      const f32x4 t4 = *(const f32x4*)(pc + (size_t)k * (BM * BN));
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] += t4[c];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      x[p][c] = x0[c] + gt[c] * (acc[c] + bias);
+      s[c] += x[p][c];
+    }
+  }
+  auto block_sum = [&](float (&v)[4], float (&buf)[8][4]) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) v[c] += __shfl_xor(v[c], o);
+    if ((tid & 63) == 0) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) buf[wv][c] = v[c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      v[c] = 0.f;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) v[c] += buf[w][c];
+    }
+  };
+  block_sum(s, red[0]);
+  float qs[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) s[c] /= (float)d;
+#pragma unroll
+  for (int p = 0; p < MAXP; ++p) {
+    const int n = p * 512 + tid;
+    if (n >= d) continue;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (m0 + c < P.M) ((float*)P.out)[(size_t)mr[c] * P.ldc + n] = x[p][c];
+      x[p][c] -= s[c];
+      qs[c] += x[p][c] * x[p][c];
+    }
+  }
+  block_sum(qs, red[1]);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) qs[c] = rsqrtf(qs[c] / (float)d + 1e-6f);
+#pragma unroll
+  for (int p = 0; p < MAXP; ++p) {
+    const int n = p * 512 + tid;
+    if (n >= d) continue;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (m0 + c >= P.M) continue;
+      const size_t mo = (size_t)(P.row_req ? P.row_req[mr[c]] : 0) * P.gate_stride + n;
+      P.ln_y[(size_t)mr[c] * d + n] = f2bf(x[p][c] * qs[c] * (1.f + P.ln_scale[mo]) + P.ln_shift[mo]);
+    }
+  }
+}
+
 // tiles of the whole batch, numbered through
 static int count_tiles(GemmBatch& b, int bm, int bn) {
   int total = 0;
@@ -1603,7 +1714,20 @@ static void launch_t(hipStream_t s, GemmBatch& b) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (MODE == 4) {
     hipLaunchKernelGGL(kern, dim3(total * b.splits), dim3(WM * WN * 64), lds, s, b);
-    hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, WM, WN>), dim3((b.geglu ? total / 2 : total) * (BM * BN / 1024)), dim3(256), 0, s, b);
+    // The norm that follows as well, from 96 workgroups of four rows on and up to 1536 columns: there it takes 2 % off a step (eight
+    // blocks of 1536 columns: 410 rows 1122 -> 1101 us, 700 rows 1209 -> 1184, 1178 rows 1542 -> 1513).  Below that too few
+    // workgroups read the partial sums (80 rows 817 -> 826 us, 272 rows 974 -> 976), and with 3072 columns a workgroup
+    // reads twice as many (256 rows 1278 -> 1295 us, 640 rows 1633 -> 1632).
+    bool ln = !b.geglu && b.n <= 2;
+    int rows = 0;
+    for (int i = 0; i < b.n; ++i) {
+      ln = ln && b.p[i].ln_y && b.p[i].out_kind == OUT_RESID_F32 && b.p[i].N <= 1536;
+      rows += (b.p[i].M + 3) / 4;
+    }
+    ln = ln && rows >= 96;
+    b.ln_done = ln;
+    if (ln) hipLaunchKernelGGL((splitk_reduce_ln_kernel<BM, BN, WM, WN>), dim3(rows), dim3(512), 0, s, b);
+    else hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, WM, WN>), dim3((b.geglu ? total / 2 : total) * (BM * BN / 1024)), dim3(256), 0, s, b);
   } else {
     hipLaunchKernelGGL(kern, dim3(total), dim3(WM * WN * 64), lds, s, b);
   }
@@ -1615,7 +1739,7 @@ static void launch_t(hipStream_t s, GemmBatch& b) {
 //             (default: k-slab 64, 2 stages)
 //   31256128 / 32256128 / 31128256  256x128 (4 waves / 8 waves) and 128x256 with a 3-stage ring
 //   30128128  128x128, k-slab 64, 4-stage ring (one workgroup per CU: for grids below 256 tiles)
-//   30128064 / 33128064  128x64 (4 waves of 32x64), 6- / 3-stage ring;  30064128  64x128 (4 waves of 64x32), 6-stage ring
+//   30128064 / 33128064  128x64 (4 waves of 32x64), 6- / 3-stage ring;  30064128 / 32064128  64x128 (4 waves of 64x32 / 32x64), 6-stage ring
 //   40128128  the same as split-K over b.splits shares of K plus the reduction kernel
 //   30032128 / 30064064  32x128 (4 waves of 32x32) and 64x64 (2 waves of 32x64), two workgroups per CU, 4- / 5-stage ring;
 //   40032128 / 40064064  the same as split-K
@@ -1711,14 +1835,16 @@ int choose_tile(GemmBatch& b, int force_tile) {
         for (int i = 0; i < b.n; ++i)
           narrow_ok = narrow_ok && b.p[i].conv_w <= 0 && !(b.p[i].out_kind == OUT_QKNORM && b.p[i].qk.head_dim > 64);
         tile = (t64 <= 256 && narrow_ok) ? 30128064 : 30128128;
-        if (tile == 30128128 && !qk) {          // ... or 64-row tiles when that gives more workgroups in one round
+        if (tile == 30128128) {
+          // ... or 64-row tiles when that gives more workgroups in one round, with the q/k norm in waves of 32 x 64: two
+          // streams of 256 and 154 rows, N = 4608: 252 workgroups instead of 144, a step of eight blocks 1101 -> 1058 us
           long long t6 = 0;
           bool plain = true;
           for (int i = 0; i < b.n; ++i) {
             if (b.p[i].M > 0 && b.p[i].N > 0) t6 += (long long)((b.p[i].M + 63) / 64) * ((b.p[i].N + 127) / 128);
             plain = plain && b.p[i].conv_w <= 0;
           }
-          if (plain && t6 <= 256 && t6 > t128) tile = 30064128;
+          if (plain && t6 <= 256 && t6 > t128) tile = qk ? 32064128 : 30064128;
         }
       }
     }
@@ -1787,10 +1913,12 @@ int choose_tile(GemmBatch& b, int force_tile) {
 }
 
 int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
+  b.ln_done = 0;
   int tile = choose_tile(b, force_tile);
   bool narrow = false;                  // epilogues that need waves of 64 columns (the split reduction has its own)
   for (int i = 0; i < b.n; ++i) narrow = narrow || b.p[i].out_kind == OUT_VT;
-  if ((narrow || b.geglu) && (tile == 30064128 || tile == 30032128)) tile = 30128128;
+  if ((narrow || b.geglu) && tile == 30064128) tile = 32064128;
+  if ((narrow || b.geglu) && tile == 30032128) tile = 30128128;
   if (b.geglu && tile < 40000000) {     // unsplit: one problem whose tiles hold both products of their columns
     if (b.n != 2 || b.p[0].A != b.p[1].A || b.p[0].M != b.p[1].M || b.p[0].N != b.p[1].N || b.p[0].ldw != b.p[1].ldw) return -1;
     b.p[0].W2 = b.p[1].W;
@@ -1805,7 +1933,7 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
   }
   // the q/k-norm epilogue exists only in the instantiations whose waves own 64 output columns
   if (qknorm && !(tile == 1256256 || tile == 1320256 || tile == 11256256 || tile == 21256256 || tile == 128128 || tile == 10128128 ||
-                  tile == 30128128 || tile == 30128064 || tile == 30064064 || tile == 33128064 || tile == 256128 || tile == 31256128 || tile == 32256128))
+                  tile == 30128128 || tile == 30128064 || tile == 32064128 || tile == 30064064 || tile == 33128064 || tile == 256128 || tile == 31256128 || tile == 32256128))
     return -1;
   if (qknorm && (tile == 30128064 || tile == 33128064 || tile == 30064064))      // 64 columns per workgroup: heads of 64 only
     for (int i = 0; i < b.n; ++i)
@@ -1836,6 +1964,7 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
     case 30128128: launch_t<128, 128, 2, 2, 64, 4>(s, b); break;
     case 30128064: launch_t<128, 64, 4, 1, 64, 6>(s, b); break;
     case 30064128: launch_t<64, 128, 1, 4, 64, 6>(s, b); break;
+    case 32064128: launch_t<64, 128, 2, 2, 64, 6>(s, b); break;
     case 30032128: launch_t<32, 128, 1, 4, 64, 4>(s, b); break;
     case 40032128: launch_t<32, 128, 1, 4, 64, 4, 4>(s, b); break;
     case 30064064: launch_t<64, 64, 2, 1, 64, 5>(s, b); break;

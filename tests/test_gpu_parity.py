@@ -1048,3 +1048,36 @@ def test_many_step_sample_uses_matrix_core_conditioning_path(torch):
         assert max_abs(fg[r], steps[r]) < 5e-3
         assert rel_l2(fg[r], fo[r]) <= FINAL_REL_L2
         assert rel_l2(fg[r], fo[r]) <= 1.5 * rel_l2(steps[r], fo[r]) + 1e-3
+
+
+@pytest.mark.parametrize("model,single,reqs", [
+    ("sd3", 0, [(1, 32, 32, 154)]), ("sd3", 0, [(1, 32, 32, 77), (1, 40, 24, 155), (1, 16, 24, 33)]), ("sd3", 0, [(1, 64, 48, 301)]),
+    ("sd3", 0, [(1, 40, 36, 22)]), ("flux", 1, [(1, 16, 16, 100)]), ("flux", 1, [(1, 32, 24, 77), (1, 16, 16, 33)])])
+def test_few_rows_fused_against_separate_kernels(torch, B, model, single, reqs):
+    """Steps of some hundred rows, whose split residual products do the layer norm that follows them and whose q/k product
+    takes 64-row tiles, against the same steps with a capture point registered, where norms, rotary code and transposition
+    are kernels of their own; requests that change inside the norm's groups of four rows and inside a tile.  Two
+    evaluations with other roundings on the way: the tolerances of the models' single calls."""
+    arch = dict(synth.CONFIGS[model]["arch"], n_blocks=2, n_single=single)
+    m = B.DiT(arch)
+    m.ensure_workspace(reqs, 1)
+    m.workspace.fill_(0xFF)                              # NaN in whatever is read without having been written
+    m.init_weights(5, 0.02)
+    n = sum(arch["latent_ch"] * f * h * w for f, h, w, _ in reqs)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    noise = torch.randn(n, generator=gen, device="cuda")
+    cond = torch.randn((sum(r[3] for r in reqs), arch["cond_dim"]), generator=gen, device="cuda").to(torch.bfloat16)
+    sig = np.array([[0.9, 0.8]] * len(reqs), dtype=np.float32)
+    outs = []
+    for tapped in (False, True):
+        if tapped:
+            rows = sum(h * w // 4 for _, h, w, _ in reqs)
+            m.set_tap("x_img0", torch.empty((rows, arch["hidden"]), dtype=torch.float32, device="cuda"))
+        x, v = noise.clone(), torch.empty_like(noise)
+        m.denoise_step(reqs, x, cond, sig[:, 0].copy(), sig[:, 1].copy(), 0, v)
+        torch.cuda.synchronize()
+        outs.append(v)
+    assert bool(torch.isfinite(outs[0]).all())
+    rel = float((outs[0] - outs[1]).norm() / outs[1].norm())
+    assert rel <= {"sd3": 2e-3, "flux": 1.5e-2}[model], rel
+    m.close()
