@@ -244,9 +244,9 @@ struct Fwd {
       stats_of = out; stats_chunks = B == 1 ? (H * W + 2 * rows - 1) / (2 * rows) * 2 : H * W / rows;
     }
   }
-  void gn(const std::string& name, const float* x, bf16_t* out, int H, int W, int C, int silu, int pad) const {
+  void gn(const std::string& name, const float* x, bf16_t* out, int H, int W, int C, int silu, int pad, bf16_t* raw = nullptr) const {
     launch_group_norm(s, x, Wv(c, name + ".g"), Wv(c, name + ".b"), out, at<float>(L.gnp), at<float2>(L.gst), H, W, C,
-                      GROUPS, silu, pad, x == stats_of ? stats_chunks : 0, B);
+                      GROUPS, silu, pad, x == stats_of ? stats_chunks : 0, B, raw);
   }
   // first real image of the stack of bordered images of H x W x C
   bf16_t* frame(int H, int W, int C) const { return at<bf16_t>(L.img) + (kt == 3 ? (size_t)2 * (H + 2) * (W + 2) * C : 0); }
@@ -259,10 +259,9 @@ struct Fwd {
     bf16_t* img = at<bf16_t>(L.img);
     float* t = at<float>(L.t);
     zero_lead(H, W, cin);
-    gn(name + ".gn1", x, frame(H, W, cin), H, W, cin, 1, 1);
+    gn(name + ".gn1", x, frame(H, W, cin), H, W, cin, 1, 1, cin != cout ? at<bf16_t>(L.act) : nullptr);   // (and x as bf16 for the shortcut)
     conv3(name + ".conv1", img, H, W, OUT_F32, t, cout);
     if (cin != cout) {
-      launch_cast_bf16(s, x, at<bf16_t>(L.act), (long long)B * H * W * cin);
       gemm({prob(at<bf16_t>(L.act), cin, Wm(c, name + ".short.w"), Wld(c, name + ".short.w"), Wv(c, name + ".short.b"),
                  B * H * W, cout, cin, OUT_F32, y, cout)});
     }

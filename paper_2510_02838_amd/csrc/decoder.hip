@@ -46,22 +46,22 @@ void launch_latent_to_image(hipStream_t s, const float* z, bf16_t* out, int C, i
 }
 
 // ---- group norm ---------------------------------------------------------------------------
-// pass 1: per chunk of GN_CHUNK pixels, per channel: sum and sum of squares.  A thread owns 4
+// pass 1: per chunk of `chunk` pixels (GN_CHUNK, fewer in small images), per channel: sum and sum of squares.  A thread owns 4
 // consecutive channels and strides over the chunk's pixels; threads that share channels combine
 // through LDS in a fixed order.  partial: [chunks][C][2].  C is a power of two in 64..1024.
 constexpr int GN_CHUNK = 256;
 __global__ __launch_bounds__(256) void gn_partial_kernel(const float* __restrict__ x, float* __restrict__ partial,
-                                                         long long P, int C, int qsh) {
+                                                         long long P, int C, int qsh, int chunk) {
   extern __shared__ float red[];                // [pix_par][C][2]
   const int qpc = C >> 2;                       // channel quads per pixel = 1 << qsh
   const int tid = threadIdx.x;
   const int quad = tid & (qpc - 1), lane_pix = tid >> qsh, pix_par = 256 >> qsh;
-  const long long p0 = (long long)blockIdx.x * GN_CHUNK;
+  const long long p0 = (long long)blockIdx.x * chunk;
   float s[4] = {0, 0, 0, 0}, q[4] = {0, 0, 0, 0};
   const float4* xp = (const float4*)(x + p0 * C) + quad;
-  if (p0 + GN_CHUNK <= P) {
-    // whole chunk: four independent loads in flight per thread
-    for (int pp = lane_pix; pp < GN_CHUNK; pp += 4 * pix_par) {
+  if (p0 + chunk <= P) {
+    // whole chunk: four independent loads in flight per thread (chunk is a multiple of 4 pix_par, 64 at most)
+    for (int pp = lane_pix; pp < chunk; pp += 4 * pix_par) {
       float4 v[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) v[u] = xp[(size_t)(pp + u * pix_par) * qpc];
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void gn_partial_kernel(const float* __restrict
       }
     }
   } else {
-    for (int pp = lane_pix; pp < GN_CHUNK && p0 + pp < P; pp += pix_par) {
+    for (int pp = lane_pix; pp < chunk && p0 + pp < P; pp += pix_par) {
       const float4 v = xp[(size_t)pp * qpc];
       s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
       q[0] += v.x * v.x; q[1] += v.y * v.y; q[2] += v.z * v.z; q[3] += v.w * v.w;
@@ -95,9 +95,12 @@ __global__ __launch_bounds__(256) void gn_partial_kernel(const float* __restrict
 // in fixed order in float64.  With one share per group the workgroup writes stats[g] = (mean,
 // 1/sqrt(var + eps)) itself; with several it leaves (sum, sum of squares) in part[g][share] for
 // gn_combine_kernel (many chunks: 32 workgroups alone would take longer than the apply pass).
+// The 2 cpg floats that a chunk has for the group are neighbours: cpg / 2 threads take them as float4s (two channels), four
+// chunks in flight (the launches of a 1024x1024 decode that are not shared out: 6.2 us on average; with a thread per chunk,
+// 8-byte loads and the tree in LDS 9.8).
 __global__ __launch_bounds__(256) void gn_finalize_kernel(const float* __restrict__ partial, float2* __restrict__ stats,
                                                           double2* __restrict__ part, int chunks, int C, int groups, long long P) {
-  __shared__ double rs[256], rq[256];
+  __shared__ double2 red[4];
   const int g = blockIdx.x, cpg = C / groups, tid = threadIdx.x;
   const int shares = gridDim.y, sh = blockIdx.y;
   const int img = blockIdx.z;                    // chunks, P: per image; an image's chunks are consecutive
@@ -105,22 +108,32 @@ __global__ __launch_bounds__(256) void gn_finalize_kernel(const float* __restric
   stats += img * groups;
   part += img * groups * shares;
   const int c0 = (int)((long long)chunks * sh / shares), c1 = (int)((long long)chunks * (sh + 1) / shares);
+  const int tpc = cpg >> 1, sub = tid % tpc, par = 256 / tpc;       // threads per chunk (1 to 16), chunks side by side
+  const float4* pp = (const float4*)(partial + (size_t)g * cpg * 2) + sub;
+  const size_t row = (size_t)C >> 1;             // float4s per chunk
   double a = 0.0, b = 0.0;
-  for (int ch = c0 + tid; ch < c1; ch += 256)
-    for (int c = 0; c < cpg; ++c) {
-      const float* pp = partial + ((size_t)ch * C + g * cpg + c) * 2;
-      a += (double)pp[0]; b += (double)pp[1];
-    }
-  rs[tid] = a; rq[tid] = b;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (tid < o) { rs[tid] += rs[tid + o]; rq[tid] += rq[tid + o]; }
-    __syncthreads();
+  int ch = c0 + tid / tpc;
+  for (; ch + 3 * par < c1; ch += 4 * par) {
+    float4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = pp[(size_t)(ch + u * par) * row];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) { a += (double)v[u].x + (double)v[u].z; b += (double)v[u].y + (double)v[u].w; }
   }
+  for (; ch < c1; ch += par) {
+    const float4 v = pp[(size_t)ch * row];
+    a += (double)v.x + (double)v.z; b += (double)v.y + (double)v.w;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { a += __shfl_xor(a, o); b += __shfl_xor(b, o); }
+  if ((tid & 63) == 0) red[tid >> 6] = make_double2(a, b);
+  __syncthreads();
   if (tid == 0) {
-    if (shares > 1) { part[g * shares + sh] = make_double2(rs[0], rq[0]); return; }
-    const double n = (double)P * cpg, mean = rs[0] / n;
-    double var = rq[0] / n - mean * mean;
+    a = (red[0].x + red[1].x) + (red[2].x + red[3].x);
+    b = (red[0].y + red[1].y) + (red[2].y + red[3].y);
+    if (shares > 1) { part[g * shares + sh] = make_double2(a, b); return; }
+    const double n = (double)P * cpg, mean = a / n;
+    double var = b / n - mean * mean;
     if (var < 0.0) var = 0.0;
     stats[g] = make_float2((float)mean, (float)(1.0 / sqrt(var + 1e-6)));
   }
@@ -141,17 +154,20 @@ __global__ __launch_bounds__(64) void gn_combine_kernel(const double2* __restric
 // pass 3: y = (x - mean_g) rstd_g gamma_c + beta_c, optional SiLU, bf16, bordered or plain rows.
 // One image row per blockIdx.y; a thread takes 8 consecutive channels of four consecutive pixels (gain, bias and
 // the group statistics are fetched once for the four, and the four pixels' loads are in flight together).
-// A bordered image's border is written here too: a launch of its own took 4.7 us, 28 times an image.
+// A bordered image's border is written here too: a launch of its own took 4.7 us, 28 times an image.  So is x itself as
+// bf16 where a 1x1 shortcut reads it next: a pass of its own read x again (a million pixels of 256 channels: 280 us,
+// here 90 us more).
 __global__ __launch_bounds__(256) void gn_apply_kernel(const float* __restrict__ x, const float2* __restrict__ stats,
                                                        const float* __restrict__ gamma, const float* __restrict__ beta,
                                                        bf16_t* __restrict__ out, int W, int C, int osh, int gsh,
-                                                       int silu, int pad, int groups) {
+                                                       int silu, int pad, int groups, bf16_t* __restrict__ raw) {
   const int i = blockIdx.x * 256 + threadIdx.x;      // unit: 8 channels of a group of four pixels of the row
   const int opc = C >> 3;                            // = 1 << osh
   if (i >= ((W + 3) >> 2) * opc) return;
   const int H = gridDim.y, img = blockIdx.z;         // one image per blockIdx.z
   x += (size_t)img * H * W * C;
   out += (size_t)img * (pad ? (size_t)(H + 2) * (W + 2) : (size_t)H * W) * C;
+  if (raw) raw += (size_t)img * H * W * C;
   stats += img * groups;
   const int y = blockIdx.y, x0 = (i >> osh) * 4, c = (i & (opc - 1)) * 8;
   const float* xr = x + ((size_t)y * W + x0) * C + c;
@@ -174,6 +190,11 @@ __global__ __launch_bounds__(256) void gn_apply_kernel(const float* __restrict__
   for (int k = 0; k < 4; ++k) {
     if (x0 + k >= W) break;
     float r[8] = {v0[k].x, v0[k].y, v0[k].z, v0[k].w, v1[k].x, v1[k].y, v1[k].z, v1[k].w};
+    if (raw) {                                       // x itself as bf16 rows
+      uint4 w;
+      w.x = d_pack2(r[0], r[1]); w.y = d_pack2(r[2], r[3]); w.z = d_pack2(r[4], r[5]); w.w = d_pack2(r[6], r[7]);
+      *(uint4*)(raw + ((size_t)y * W + x0 + k) * C + c) = w;
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       r[j] = r[j] * sc[j] + sh[j];
@@ -204,7 +225,7 @@ __global__ __launch_bounds__(256) void gn_apply_kernel(const float* __restrict__
 // pass 1 needs H*W to be a multiple of its chunk (256 pixels).
 void launch_group_norm(hipStream_t s, const float* x, const float* gamma, const float* beta, bf16_t* out,
                        float* partial, float2* stats, int H, int W, int C, int groups, int silu, int pad,
-                       int ready_chunks, int B) {
+                       int ready_chunks, int B, bf16_t* raw) {
   const long long P = (long long)H * W;
   if (P == 0 || B == 0) return;
   int chunks = ready_chunks;
@@ -213,17 +234,20 @@ void launch_group_norm(hipStream_t s, const float* x, const float* gamma, const 
   int gsh = 0;
   while ((groups << gsh) < C) ++gsh;             // channels per group = 1 << gsh
   if (chunks <= 0) {
-    chunks = (int)((P + GN_CHUNK - 1) / GN_CHUNK);
+    // (small images: 64 pixels a workgroup, as many partial sums as a convolution leaves; 1024 pixels on 4 workgroups took 15 us)
+    const int chunk = P * B < 65536 ? 64 : GN_CHUNK;
+    chunks = (int)((P + chunk - 1) / chunk);
     const int pix_par = 256 >> (csh - 2);
-    hipLaunchKernelGGL(gn_partial_kernel, dim3(chunks * B), dim3(256), (size_t)pix_par * C * 2 * sizeof(float), s, x, partial, P * B, C, csh - 2);
+    hipLaunchKernelGGL(gn_partial_kernel, dim3(chunks * B), dim3(256), (size_t)pix_par * C * 2 * sizeof(float), s, x, partial, P * B, C, csh - 2, chunk);
   }
   // stats: [B][groups] float2, then (GN_STATS_HEAD bytes on) the [B][groups][shares] float64 pairs of the two-stage form
-  const int shares = chunks >= 4096 ? 16 : (chunks >= 1024 ? 4 : 1);
+  // (shared out from 4096 chunks on; below, the launch that combines the shares costs what they gain)
+  const int shares = chunks >= 4096 ? 16 : 1;
   double2* part = (double2*)((unsigned char*)stats + GN_STATS_HEAD);
   hipLaunchKernelGGL(gn_finalize_kernel, dim3(groups, shares, B), dim3(256), 0, s, partial, stats, part, chunks, C, groups, P);
   if (shares > 1) hipLaunchKernelGGL(gn_combine_kernel, dim3(B), dim3(64), 0, s, part, stats, shares, C / groups, groups, P);
   const int units = ((W + 3) >> 2) * (C >> 3);
-  hipLaunchKernelGGL(gn_apply_kernel, dim3((units + 255) / 256, H, B), dim3(256), 0, s, x, stats, gamma, beta, out, W, C, csh - 3, gsh, silu, pad, groups);
+  hipLaunchKernelGGL(gn_apply_kernel, dim3((units + 255) / 256, H, B), dim3(256), 0, s, x, stats, gamma, beta, out, W, C, csh - 3, gsh, silu, pad, groups, raw);
 }
 size_t group_norm_partial_bytes(long long pixels, int C) {
   return (size_t)((pixels + GN_CHUNK - 1) / GN_CHUNK) * C * 2 * sizeof(float);
@@ -268,26 +292,6 @@ __global__ __launch_bounds__(256) void upsample_pad_kernel(const float* __restri
 void launch_upsample_pad(hipStream_t s, const float* x, bf16_t* out, int H, int W, int C, int B, int frame_up) {
   const long long n = (long long)H * W * (C / 8);
   if (n && B) hipLaunchKernelGGL(upsample_pad_kernel, dim3((unsigned)((n + 255) / 256), B), dim3(256), 0, s, x, out, H, W, C, frame_up);
-}
-
-// fp32 -> bf16, 4 elements per thread (plain rows)
-// (a workgroup takes 4 x 256 float4s, a thread one of each quarter: four loads in flight per thread)
-__global__ __launch_bounds__(256) void cast_bf16_kernel(const float* __restrict__ x, bf16_t* __restrict__ out, long long n4) {
-  const long long i0 = (long long)blockIdx.x * 1024 + threadIdx.x;
-  float4 v[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (i0 + k * 256 < n4) v[k] = ((const float4*)x)[i0 + k * 256];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    if (i0 + k * 256 >= n4) break;
-    uint2 w;
-    w.x = d_pack2(v[k].x, v[k].y); w.y = d_pack2(v[k].z, v[k].w);
-    ((uint2*)out)[i0 + k * 256] = w;
-  }
-}
-void launch_cast_bf16(hipStream_t s, const float* x, bf16_t* out, long long n) {
-  if (n) hipLaunchKernelGGL(cast_bf16_kernel, dim3((unsigned)((n / 4 + 1023) / 1024)), dim3(256), 0, s, x, out, n / 4);
 }
 
 // row softmax of fp32 scores times `scale`, written as bf16 with row stride ldo; columns from n to

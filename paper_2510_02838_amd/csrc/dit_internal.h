@@ -207,11 +207,11 @@ constexpr size_t GN_STATS_HEAD = (size_t)GN_MAX_BATCH * 32 * 8;                 
 constexpr size_t GN_STATS_BYTES = GN_STATS_HEAD + (size_t)GN_MAX_BATCH * 32 * 16 * 16;   // + [B][groups][shares] double2
 void launch_group_norm(hipStream_t s, const float* x, const float* gamma, const float* beta, bf16_t* out,
                        float* partial, float2* stats, int H, int W, int C, int groups, int silu, int pad,
-                       int ready_chunks = 0, int B = 1);   // B same-size images back to back, statistics per image
+                       int ready_chunks = 0, int B = 1,    // B same-size images back to back, statistics per image
+                       bf16_t* raw = nullptr);             // optional: x itself as plain bf16 rows
 // nearest 2x upsampling of x [H*W][C] fp32 into a bf16 bordered image of size 2H x 2W
 // B output images; frame_up: output image g shows input image (g + 1) / 2 (frame-rate doubling), else image g
 void launch_upsample_pad(hipStream_t s, const float* x, bf16_t* out, int H, int W, int C, int B = 1, int frame_up = 0);
-void launch_cast_bf16(hipStream_t s, const float* x, bf16_t* out, long long n);     // n % 4 == 0
 // out[r][j] = softmax_j(sc[r][j] * scale) as bf16, j < n; columns n..ldo-1 are set to zero
 void launch_softmax_rows(hipStream_t s, const float* sc, int lds_, bf16_t* out, int ldo, int rows, int n, float scale_log2);
 // 3x3 convolution of a bordered bf16 image to OC <= 4 fp32 channels without the matrix cores;

@@ -1852,7 +1852,8 @@ int choose_tile(GemmBatch& b, int force_tile) {
   if (!tile) {
     // One round of 256x128 tiles (8 waves, 3-stage ring) when that fits the chip and K is not short:
     // a workgroup per CU with two slabs in flight, against 1.6 128x128 workgroups per CU (4250 rows, N = 1536:
-    // 74 against 85 us at K = 6144, 24.1 against 27.1 at K = 1536).
+    // 74 against 85 us at K = 6144, 24.1 against 27.1 at K = 1536; a 3x3 convolution of 16384 pixels, 512 channels:
+    // 67 against 75).
     long long t21 = 0;
     int min_k = 1 << 30;
     bool plain = true;
@@ -1860,7 +1861,7 @@ int choose_tile(GemmBatch& b, int force_tile) {
       if (b.p[i].M <= 0 || b.p[i].N <= 0) continue;
       t21 += (long long)((b.p[i].M + 255) / 256) * ((b.p[i].N + 127) / 128);
       min_k = b.p[i].K < min_k ? b.p[i].K : min_k;
-      plain = plain && b.p[i].out_kind != OUT_QKNORM && b.p[i].conv_w <= 0;
+      plain = plain && b.p[i].out_kind != OUT_QKNORM;
     }
     if (plain && t21 > 128 && t21 <= 256 && min_k >= 1536) tile = 32256128;
   }
