@@ -487,14 +487,19 @@ bool run_gemm(dit_ctx* c, std::initializer_list<GemmProblem> ps) {
   for (const GemmProblem& p : ps) {
     if (p.M <= 0 || p.N <= 0) continue;
     b.p[b.n++] = p;
-    flop += 2.0 * p.M * p.N * p.K;
-    bytes += 2.0 * ((double)p.M * p.K + (double)p.N * p.K) + (double)p.M * p.N * (p.out_kind == OUT_RESID_F32 ? 8 : p.out_kind == OUT_F32 ? 4 : 2);
+    flop += (p.A2 ? 4.0 : 2.0) * p.M * p.N * p.K;
+    bytes += 2.0 * ((p.A2 ? 2.0 : 1.0) * p.M * p.K + (double)p.N * p.K) + (double)p.M * p.N * (p.out_kind == OUT_RESID_F32 ? 8 : p.out_kind == OUT_F32 ? 4 : 2);
   }
   if (!b.n) return false;
   b.partial = c->gemm_partial; b.partial_bytes = c->gemm_partial ? GEMM_PARTIAL_BYTES : 0;
   Scope sc(c, DIT_PROF_GEMM, flop, bytes);
   if (launch_gemm(c->stream, b) < 0) c->launch_refused = true;     // shape outside the kernels' limits: reported by the call
   return b.ln_done != 0;
+}
+// the product `p` with a second term of its left operand: (A + lo) W^T
+GemmProblem with_lo(GemmProblem p, const bf16_t* lo) {
+  p.A2 = lo;
+  return p;
 }
 // the residual product `p` with the layer norm that follows it (shift and scale of its modulation, output y)
 GemmProblem with_ln(GemmProblem p, bf16_t* y, const float* shift, const float* scale) {
@@ -692,8 +697,7 @@ dit_status w_cross_kv(dit_ctx* c, const Run& R, const std::string& p, int blk) {
   const bf16_t* cproj = R.at<bf16_t>(L.cproj);
   const bf16_t* cproj_lo = cproj + (size_t)Nt * d;
   float* kv32 = R.at<float>(L.act);
-  run_gemm(c, {mk(cproj, d, Wm(c, p + ".xkv.w"), Wld(c, p + ".xkv.w"), Wv(c, p + ".xkv.b"), Nt, 2 * d, d, OUT_F32, kv32, 2 * d)});
-  run_gemm(c, {mk(cproj_lo, d, Wm(c, p + ".xkv.w"), Wld(c, p + ".xkv.w"), nullptr, Nt, 2 * d, d, OUT_RESID_F32, kv32, 2 * d)});
+  run_gemm(c, {with_lo(mk(cproj, d, Wm(c, p + ".xkv.w"), Wld(c, p + ".xkv.w"), Wv(c, p + ".xkv.b"), Nt, 2 * d, d, OUT_F32, kv32, 2 * d), cproj_lo)});
   Scope sc(c, DIT_PROF_QKNORM, 0, 12.0 * Nt * d);
   launch_cross_kv_finish(c->stream, kv32, 2 * d, Nt, g.n_heads, g.head_dim, Wv(c, p + ".xknorm.g"),
                          R.at<bf16_t>(L.xk) + (size_t)blk * Nt * d, d, R.ip(P.o_src_of_col_x), P.Nvx_pad,
@@ -893,8 +897,7 @@ dit_status run_sample(dit_ctx* c, int n_req, const dit_req* reqs, float* latents
       launch_skinny(s, vec, d, mats + 2, c->n_skinny - 2, 6 * d, mod, MC, Rr, d, 1);
     auto modv = [&](const std::string& name, int n) {
       if (big) {
-        run_gemm(c, {mk(R.at<bf16_t>(L.mhi), d, Wm(c, name + ".w"), Wld(c, name + ".w"), Wv(c, name + ".b"), Rr, n, d, OUT_F32, mod + off, MC)});
-        run_gemm(c, {mk(R.at<bf16_t>(L.mlo), d, Wm(c, name + ".w"), Wld(c, name + ".w"), nullptr, Rr, n, d, OUT_RESID_F32, mod + off, MC)});
+        run_gemm(c, {with_lo(mk(R.at<bf16_t>(L.mhi), d, Wm(c, name + ".w"), Wld(c, name + ".w"), Wv(c, name + ".b"), Rr, n, d, OUT_F32, mod + off, MC), R.at<bf16_t>(L.mlo))});
       }
       off += n;
     };
@@ -931,19 +934,16 @@ dit_status run_sample(dit_ctx* c, int n_req, const dit_req* reqs, float* latents
     // ---- embed ---------------------------------------------------------------------------
     {
       Scope sc(c, DIT_PROF_OTHER, 0, 0);
-      launch_patchify(s, latents, (const long long*)(c->ws + L.meta + P.o_lat_off), (const int4*)(c->ws + L.meta + P.o_req_dims),
-                      tok, Ni, g.latent_ch, g.patch_t, g.patch_h, g.patch_w, R.at<bf16_t>(L.patch),
-                      R.at<bf16_t>(L.patch) + (size_t)Ni * L.ldp, L.ldp);
-      if (P.has_txt_stream) launch_copy_rows_f32(s, R.at<float>(L.xt0), nullptr, x, nullptr, Nt, d);
+      launch_step_begin(s, latents, (const long long*)(c->ws + L.meta + P.o_lat_off), (const int4*)(c->ws + L.meta + P.o_req_dims),
+                        tok, Ni, g.latent_ch, g.patch_t, g.patch_h, g.patch_w, R.at<bf16_t>(L.patch),
+                        R.at<bf16_t>(L.patch) + (size_t)Ni * L.ldp, L.ldp, g.family == DIT_FAMILY_J ? x_img : nullptr,
+                        R.at<float>(L.xt0), x, P.has_txt_stream ? Nt : 0, d);
     }
     // The latent enters as two bf16 terms (hi + lo) so that the embedding sees it to ~16 bits:
     // with small weights the model output is dominated by this path and by the final layer.
-    run_gemm(c, {mk(R.at<bf16_t>(L.patch), L.ldp, Wm(c, "x_embed.w"), Wld(c, "x_embed.w"), Wv(c, "x_embed.b"), Ni, d, L.ldp, OUT_F32, x_img, d)});
-    run_gemm(c, {mk(R.at<bf16_t>(L.patch) + (size_t)Ni * L.ldp, L.ldp, Wm(c, "x_embed.w"), Wld(c, "x_embed.w"), nullptr, Ni, d, L.ldp, OUT_RESID_F32, x_img, d)});
-    if (g.family == DIT_FAMILY_J) {
-      Scope sc(c, DIT_PROF_OTHER, 0, 0);
-      launch_add_pe(s, x_img, tok, Ni, d);
-    }
+    // (family J: onto the positions)
+    run_gemm(c, {with_lo(mk(R.at<bf16_t>(L.patch), L.ldp, Wm(c, "x_embed.w"), Wld(c, "x_embed.w"), Wv(c, "x_embed.b"), Ni, d, L.ldp,
+                            g.family == DIT_FAMILY_J ? OUT_RESID_F32 : OUT_F32, x_img, d), R.at<bf16_t>(L.patch) + (size_t)Ni * L.ldp)});
     if (P.has_txt_stream) TAP("x_txt0", x, Nt, d, 4, d);
     TAP("x_img0", x_img, Ni, d, 4, d);
     // ---- blocks --------------------------------------------------------------------------
@@ -978,8 +978,7 @@ dit_status run_sample(dit_ctx* c, int n_req, const dit_req* reqs, float* latents
       launch_ln_modulate(s, x_img, h, Ni, d, mf, mf + d, MC, R.ip(P.o_row_req_s) + soff_img, nullptr, nullptr,
                          R.at<bf16_t>(L.o));     // second term in the (free) attention-output buffer
     }
-    run_gemm(c, {mk(h, d, Wm(c, "final.w"), Wld(c, "final.w"), Wv(c, "final.b"), Ni, c->pdim, d, OUT_F32, R.at<float>(L.yfin), L.ldy)});
-    run_gemm(c, {mk(R.at<bf16_t>(L.o), d, Wm(c, "final.w"), Wld(c, "final.w"), nullptr, Ni, c->pdim, d, OUT_RESID_F32, R.at<float>(L.yfin), L.ldy)});
+    run_gemm(c, {with_lo(mk(h, d, Wm(c, "final.w"), Wld(c, "final.w"), Wv(c, "final.b"), Ni, c->pdim, d, OUT_F32, R.at<float>(L.yfin), L.ldy), R.at<bf16_t>(L.o))});
     TAP("final", R.at<float>(L.yfin), Ni, c->pdim, 4, L.ldy);
     {
       Scope sc(c, DIT_PROF_UPDATE, 0, 12.0 * P.lat_total);

@@ -45,6 +45,7 @@ struct QkNorm {
 struct GemmProblem {
   const bf16_t* A; int lda;     // [M][lda] activations
   const bf16_t* W; int ldw;     // [N_pad][ldw] weights, out-major
+  const bf16_t* A2 = nullptr;   // optional second term of A, same shape: (A + A2) W^T, all of A first (no convolutions)
   const bf16_t* W2 = nullptr;   // OUT_GEGLU: the second matrix, same shape; N counts the columns of both
   const float* bias;            // [N] or null
   int M, N, K;
@@ -163,14 +164,14 @@ void launch_cross_kv_finish(hipStream_t s, const float* kv, int ld, int M, int H
                             bf16_t* k16, int ldk, const int* src_of_col, int n_cols_pad, bf16_t* vt_hi,
                             bf16_t* vt_lo, int ldvt);
 
-// patchify: latents fp32 packed -> bf16 [n_img][ldp] (columns >= pdim zero)
+// What a step begins with, in one launch: the latents' patches, fp32 packed -> two bf16 terms [n_img][ldp] (columns >= pdim
+// zero; out + out_lo = latent to ~16 bits); with pe the 2-D sin/cos positions PE(i,j) as the image rows pe [n_img][d]; and
+// the n_txt text rows txt_src -> txt_dst [n_txt][d] (either may be null / 0).
 struct TokInfo { int req; int f, i, j; };  // per image token: request and grid position
-void launch_patchify(hipStream_t s, const float* lat, const long long* lat_off_dev,
-                     const int4* req_dims_dev /* (F,H,W,unused) per req */,
-                     const TokInfo* tok, int n_img, int C, int pt, int ph, int pw,
-                     bf16_t* out, bf16_t* out_lo, int ldp);   // out + out_lo = latent to ~16 bits
-// x[m][c] += PE(i,j)[c] for family J
-void launch_add_pe(hipStream_t s, float* x, const TokInfo* tok, int n_img, int d);
+void launch_step_begin(hipStream_t s, const float* lat, const long long* lat_off_dev,
+                       const int4* req_dims_dev /* (F,H,W,unused) per req */,
+                       const TokInfo* tok, int n_img, int C, int pt, int ph, int pw,
+                       bf16_t* out, bf16_t* out_lo, int ldp, float* pe, const float* txt_src, float* txt_dst, int n_txt, int d);
 // unpatchify + update: for every latent element: v = y[token][feat]; x = a x + b v
 void launch_unpatchify_update(hipStream_t s, float* lat, float* v_out, const float* y, int ldy,
                               const long long* lat_off_dev, const int4* req_dims_dev,

@@ -436,12 +436,29 @@ void launch_timestep_features(hipStream_t s, const float* sigma_dev, float* out,
 // ---------------------------------------------------------------------------------------
 // patchify: token t of request r, feature ((c*pt+dt)*ph+dh)*pw+dw  <-  latent[c][f][y][x]
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void patchify_kernel(const float* __restrict__ lat,
-                                                       const long long* __restrict__ lat_off,
-                                                       const int4* __restrict__ req_dims,
-                                                       const TokInfo* __restrict__ tok, int n_img, int C,
-                                                       int pt, int ph, int pw, bf16_t* __restrict__ out,
-                                                       bf16_t* __restrict__ out_lo, int ldp) {
+// Three jobs by ranges of workgroups (apart, each of them is a launch of 2 to 5 us in a small step): patches, positions
+// [sin(i w), cos(i w), sin(j w), cos(j w)], w_k = 1e4^(-k/(d/4)), and the text rows.
+__global__ __launch_bounds__(256) void step_begin_kernel(const float* __restrict__ lat, const long long* __restrict__ lat_off,
+                                                         const int4* __restrict__ req_dims, const TokInfo* __restrict__ tok, int n_img,
+                                                         int C, int pt, int ph, int pw, bf16_t* __restrict__ out, bf16_t* __restrict__ out_lo,
+                                                         int ldp, float* __restrict__ pe, const float4* __restrict__ txt_src,
+                                                         float4* __restrict__ txt_dst, int n_txt, int d, unsigned wg_patch, unsigned wg_pe) {
+  if (blockIdx.x >= wg_patch + wg_pe) {
+    const long long idx = (long long)(blockIdx.x - wg_patch - wg_pe) * 256 + threadIdx.x;
+    if (idx < (long long)n_txt * (d >> 2)) txt_dst[idx] = txt_src[idx];
+    return;
+  }
+  if (blockIdx.x >= wg_patch) {
+    const long long idx = (long long)(blockIdx.x - wg_patch) * 256 + threadIdx.x;
+    if (idx >= (long long)n_img * d) return;
+    const int t = (int)(idx / d), c = (int)(idx % d);
+    const int qd = d >> 2, part = c / qd, k = c % qd;
+    const TokInfo ti = tok[t];
+    const float w = exp2f(-13.287712379549449f * (float)k / (float)qd);   // log2(1e4)
+    const float ang = (float)(part < 2 ? ti.i : ti.j) * w;
+    pe[idx] = (part & 1) ? cosf(ang) : sinf(ang);
+    return;
+  }
   const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
   if (idx >= (long long)n_img * ldp) return;
   const int t = (int)(idx / ldp), feat = (int)(idx % ldp);
@@ -460,31 +477,14 @@ __global__ __launch_bounds__(256) void patchify_kernel(const float* __restrict__
   out[idx] = hi;
   out_lo[idx] = f2bf(v - bf2f(hi));     // latent = hi + lo to about 16 mantissa bits
 }
-void launch_patchify(hipStream_t s, const float* lat, const long long* lat_off_dev, const int4* req_dims_dev,
-                     const TokInfo* tok, int n_img, int C, int pt, int ph, int pw, bf16_t* out, bf16_t* out_lo,
-                     int ldp) {
-  const long long total = (long long)n_img * ldp;
-  if (total == 0) return;
-  hipLaunchKernelGGL(patchify_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, lat, lat_off_dev,
-                     req_dims_dev, tok, n_img, C, pt, ph, pw, out, out_lo, ldp);
-}
-
-// x[t][c] += PE(i, j)[c]:  quarters [sin(i w), cos(i w), sin(j w), cos(j w)], w_k = 1e4^(-k/(d/4))
-__global__ __launch_bounds__(256) void add_pe_kernel(float* __restrict__ x, const TokInfo* __restrict__ tok,
-                                                     int n_img, int d) {
-  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (long long)n_img * d) return;
-  const int t = (int)(idx / d), c = (int)(idx % d);
-  const int qd = d >> 2, part = c / qd, k = c % qd;
-  const TokInfo ti = tok[t];
-  const float w = exp2f(-13.287712379549449f * (float)k / (float)qd);   // log2(1e4)
-  const float ang = (float)(part < 2 ? ti.i : ti.j) * w;
-  x[idx] += (part & 1) ? cosf(ang) : sinf(ang);
-}
-void launch_add_pe(hipStream_t s, float* x, const TokInfo* tok, int n_img, int d) {
-  const long long total = (long long)n_img * d;
-  if (total == 0) return;
-  hipLaunchKernelGGL(add_pe_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, x, tok, n_img, d);
+void launch_step_begin(hipStream_t s, const float* lat, const long long* lat_off_dev, const int4* req_dims_dev,
+                       const TokInfo* tok, int n_img, int C, int pt, int ph, int pw, bf16_t* out, bf16_t* out_lo, int ldp,
+                       float* pe, const float* txt_src, float* txt_dst, int n_txt, int d) {
+  auto wgs = [](long long n) { return (unsigned)((n + 255) / 256); };
+  const unsigned wp = wgs((long long)n_img * ldp), we = pe ? wgs((long long)n_img * d) : 0, wt = wgs((long long)n_txt * (d / 4));
+  if (wp + we + wt == 0) return;
+  hipLaunchKernelGGL(step_begin_kernel, dim3(wp + we + wt), dim3(256), 0, s, lat, lat_off_dev, req_dims_dev, tok, n_img, C, pt, ph, pw,
+                     out, out_lo, ldp, pe, (const float4*)txt_src, (float4*)txt_dst, n_txt, d, wp, we);
 }
 
 // ---------------------------------------------------------------------------------------

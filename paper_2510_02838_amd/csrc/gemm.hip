@@ -224,17 +224,18 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   auto acc_row = [&](int e) { return 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); };
   const int acc_col = lane & 31;
 
-  int nk = P.K / BKT;
-  int kb_conv = 0;              // first slab of my share of a convolution (its A offset is not linear in k)
+  // Slabs of the product; with a second term of A those of both, and slab nh is the first of the second term.
+  const int nh = !CONV && P.A2 ? P.K / BKT : 1 << 30;
+  int nk = (!CONV && P.A2 ? 2 : 1) * (P.K / BKT);
+  int kb = 0;                   // first slab of my share
   if (MODE == 4) {              // my share of the slabs (shares differ by at most one slab)
-    const int kb = split * nk / batch.splits, ke = (split + 1) * nk / batch.splits;
-    if constexpr (CONV) kb_conv = kb;
-    else P.A += kb * BKT;
-    P.W += kb * BKT;
+    const int ke = (split + 1) * nk / batch.splits;
+    kb = split * nk / batch.splits;
     nk = ke - kb;
   }
   // lanes address their tile by 32-bit byte offsets from its first row, so no operand size limit
   const bf16_t* const tileA = CONV ? P.A + conv_pix0 * (size_t)P.conv_cin : P.A + (size_t)m0 * P.lda;
+  const bf16_t* const tileA2 = !CONV && P.A2 ? P.A2 + (size_t)m0 * P.lda : tileA;
   // a gated pair: every 64 columns of the tile are 32 of the gate and the same 32 of the values
   const bool pair = !CONV && MODE == 0 && P.out_kind == OUT_GEGLU;
   const bf16_t* const tileW = P.W + (size_t)(pair ? n0 >> 1 : n0) * P.ldw;
@@ -253,19 +254,20 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
   auto issue = [&](int kt) {
     unsigned char* dA = smem + (kt % NS) * STAGE;
     unsigned char* dB = dA + OFFB;
-    const int ks = (kt < nk ? kt : nk - 1) * BKT;
+    const int slab = kb + (kt < nk ? kt : nk - 1);
+    const bool lo = slab >= nh;
+    const int ks = (lo ? slab - nh : slab) * BKT;
     int ka = ks;             // A-side offset of the slab
     if constexpr (CONV) {    // slab = 64 channels of one tap (ky, kx): shift by ky rows and kx pixels
-      const int kc = ks + kb_conv * BKT;
-      int tap = kc / P.conv_cin;
-      const int c0 = kc - tap * P.conv_cin;
+      int tap = ks / P.conv_cin;
+      const int c0 = ks - tap * P.conv_cin;
       int kf = 0;            // 27 taps: the first index is the frame, 0 = two frames back (the stack starts two frames early)
       if (P.conv_kt == 3) { kf = tap / 9; tap -= 9 * kf; }
       const int ky = tap / 3, kx = tap - 3 * ky;
       ka = ((kf * (P.conv_img / P.conv_w + 2) + ky) * (P.conv_w + 2) + kx) * P.conv_cin + c0;
     }
 #pragma unroll
-    for (int i = 0; i < LA; ++i) buffer_load_lds16(tileA, (lptr_t)(dA + (i * NT + wave * 64) * 16), ga[i] * 2u, ka * 2);
+    for (int i = 0; i < LA; ++i) buffer_load_lds16(lo ? tileA2 : tileA, (lptr_t)(dA + (i * NT + wave * 64) * 16), ga[i] * 2u, ka * 2);
 #pragma unroll
     for (int i = 0; i < LB; ++i)      // (a load's rows lie in one half of their 64)
       buffer_load_lds16(((i * (WM * WN) + wave) * RPL >> 5) & 1 ? tileW2 : tileW, (lptr_t)(dB + (i * NT + wave * 64) * 16), gb[i] * 2u, ks * 2);
@@ -1916,6 +1918,22 @@ int choose_tile(GemmBatch& b, int force_tile) {
 int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
   b.ln_done = 0;
   int tile = choose_tile(b, force_tile);
+  // The streams of the 8-wave tiles do not know second terms of A: there it is added by a launch of its own.
+  if (tile == 1256256 || tile == 1320256 || tile == 32256128) {
+    GemmBatch first = b, second = b;
+    second.n = 0;
+    for (int i = 0; i < b.n; ++i) {
+      if (!b.p[i].A2) continue;
+      if (b.p[i].out_kind != OUT_F32 && b.p[i].out_kind != OUT_RESID_F32) return -1;
+      first.p[i].A2 = nullptr;
+      GemmProblem& q = second.p[second.n++] = b.p[i];
+      q.A = q.A2; q.A2 = nullptr; q.bias = nullptr; q.out_kind = OUT_RESID_F32;
+    }
+    if (second.n) {
+      tile = launch_gemm(s, first, force_tile);
+      return tile < 0 ? tile : launch_gemm(s, second, force_tile);
+    }
+  }
   bool narrow = false;                  // epilogues that need waves of 64 columns (the split reduction has its own)
   for (int i = 0; i < b.n; ++i) narrow = narrow || b.p[i].out_kind == OUT_VT;
   if ((narrow || b.geglu) && tile == 30064128) tile = 32064128;
