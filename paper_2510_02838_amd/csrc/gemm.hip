@@ -1359,6 +1359,12 @@ __global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
           cb = map[mb];
           consec = map[mb + 31] == cb + 31;
         }
+        int col[8];                                      // else the columns of my piece's rows, fetched together and
+        if (!consec) {                                   // waited for here (one by one they cost a memory latency each)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) col[e] = mb + fc * 8 + e < M ? map[mb + fc * 8 + e] : -1;
+          asm volatile("" :: "v"(col[0]), "v"(col[1]), "v"(col[2]), "v"(col[3]), "v"(col[4]), "v"(col[5]), "v"(col[6]), "v"(col[7]));
+        }
 #pragma unroll
         for (int cp = 0; cp < 2; ++cp) {
 #pragma unroll
@@ -1381,8 +1387,14 @@ __global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
             if (consec) *(u32x4_any*)((char*)(vt_out + (size_t)(nv0 + f) * ldvt + cb) + voff) = w[h];
             else {
               bf16_t* dst = vt_out + (size_t)(nv0 + f + fr) * ldvt;
-              for (int e = 0; e < 8; ++e)
-                if (mb + fc * 8 + e < M) dst[map[mb + fc * 8 + e]] = (bf16_t)(w[h][e >> 1] >> (16 * (e & 1)));
+#pragma unroll
+              for (int e = 0; e < 8; e += 2) {           // (pairs where two rows are neighbours at an even column)
+                if (col[e + 1] == col[e] + 1 && (col[e] & 1) == 0) *(uint32_t*)(dst + col[e]) = w[h][e >> 1];
+                else {
+                  if (col[e] >= 0) dst[col[e]] = (bf16_t)w[h][e >> 1];
+                  if (col[e + 1] >= 0) dst[col[e + 1]] = (bf16_t)(w[h][e >> 1] >> 16);
+                }
+              }
             }
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -1470,6 +1482,27 @@ __global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
   wait_vm<0, true>();                        // drain the redundant tail loads before LDS is released
 }
 
+// The shares of one float4 of a split product, STRIDE floats apart, added in their order.  Eight loads are in flight and none
+// waits alone behind them: with four, and the rest one by one, 16 shares cost six memory latencies, with eight two (32 tokens
+// through the encoder 2985 -> 2962 us).
+template <int STRIDE>
+__device__ __forceinline__ f32x4 sum_shares(const float* pc, int splits) {
+  f32x4 acc = *(const f32x4*)pc;
+  for (int s = 1; s < splits; s += 8) {
+    f32x4 t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (s + u < splits) t[u] = *(const f32x4*)(pc + (size_t)(s + u) * STRIDE);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (s + u < splits) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] += t[u][c];
+      }
+  }
+  return acc;
+}
+
 // Second half of a split-K product: sums the `splits` partial tiles in fixed order (so the
 // result does not depend on which workgroup finished first) and applies the epilogue.  One
 // thread per float4 of the chunk layout written above: 4 consecutive rows of one column, the
@@ -1494,23 +1527,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmBatch batc
   const int mrow = tm * BM + wm * (BM / WM) + i * 32 + 8 * g + 4 * (lane >> 5);
   auto sum = [&](int t) {
     const float* pc = batch.partial + (size_t)t * batch.splits * (BM * BN) + (size_t)q * 4;
-    f32x4 acc = *(const f32x4*)pc;
-    int s = 1;
-    for (; s + 3 < batch.splits; s += 4) {           // four loads in flight; added in the same order
-      f32x4 t4[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) t4[u] = *(const f32x4*)(pc + (size_t)(s + u) * (BM * BN));
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[c] += t4[u][c];
-    }
-    for (; s < batch.splits; ++s) {
-      const f32x4 t4 = *(const f32x4*)(pc + (size_t)s * (BM * BN));
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[c] += t4[c];
-    }
-    return acc;
+    return sum_shares<BM * BN>(pc, batch.splits);
   };
   f32x4 acc = sum(tile);
   if (batch.geglu) {
@@ -1609,7 +1626,8 @@ __global__ __launch_bounds__(512) void splitk_reduce_ln_kernel(const GemmBatch b
       x0[c] = ((const float*)P.out)[(size_t)mr[c] * P.ldc + n];
       gt[c] = gp[c] ? gp[c][n] : 1.f;
     }
-    f32x4 acc = *(const f32x4*)pc;                 // (the order of splitk_reduce_kernel)
+    // (the order of sum_shares(); several columns a thread have enough loads in flight, whose conditions cost 0.6 % of a step)
+    f32x4 acc = *(const f32x4*)pc;
     int k = 1;
     for (; k + 3 < batch.splits; k += 4) {
       f32x4 t4[4];
