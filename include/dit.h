@@ -209,7 +209,7 @@ int dit_op_gemm_tile(int n, const int* M, const int* N, const int* K, int out_ki
  * +10000000 / +20000000 = k-slab 32 with a 4- / 5-stage LDS ring instead of k-slab 64 with
  * 2 stages (256256, 1256256, 128128); 30128128 = 128x128 with k-slab 64 and a 4-stage ring;
  * 1320256 = 320x256 with 8 waves; 31256128 / 32256128 (4 / 8 waves) and 31128256 with a 3-stage
- * ring; for few rows 30128064, 33128064, 30064128, 30064064 and 30032128. */
+ * ring; for few rows 30128064, 33128064, 30064128, 32064128, 30064064 and 30032128. */
 dit_status dit_op_gemm_variant(void* stream, const void* A, int lda, const void* W, int ldw,
                                const float* bias, int M, int N, int K, int out_kind, void* out,
                                int ldc, int variant);
