@@ -31,6 +31,7 @@
 // over the 8 XCDs (ids are dealt round-robin to XCDs by the hardware) so that workgroups
 // sharing an L2 work on neighbouring tiles, then mapped to tiles in groups of 8 tile rows.
 #include "dit_internal.h"
+#include "gemm_rows.h"
 #include <type_traits>
 
 namespace dit {
@@ -1252,10 +1253,7 @@ __global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
       const int* const map = Q.dst_row;
       int dr[RT];
 #pragma unroll
-      for (int r = 0; r < RT; ++r) {
-        const int m = mw + r * 16 + l16;
-        dr[r] = map ? map[m < M ? m : M - 1] : m;
-      }
+      for (int r = 0; r < RT; ++r) dr[r] = dest_row(map, mw + r * 16 + l16, M);
       float ss[RT];
       {
         float bv[2][8];

@@ -401,10 +401,13 @@ def test_gemm_split_k_tiles_for_few_rows(torch, B, M, N, K, splits, variant):
 @pytest.mark.parametrize("M,d,dh,parts", [(300, 256, 64, "qkv"), (517, 512, 128, "qkv"), (70, 256, 128, "q"),
                                           (4250, 512, 64, "qkv"), (33, 256, 64, "kv"),
                                           (4250, 1536, 64, "qkv"), (5400, 1024, 128, "qkv")])
-def test_gemm_qknorm_epilogue(torch, B, M, d, dh, parts):
+@pytest.mark.parametrize("mapped", [True, False])
+def test_gemm_qknorm_epilogue(torch, B, M, d, dh, parts, mapped):
     """QKV product with the q/k RMS norm, rotary code, scale and row scatter as its epilogue,
-    against the float64 product pushed through the oracle's norm and rotation."""
+    against the float64 product pushed through the oracle's norm and rotation.  Without a map (rows stay
+    where they are) the rotary table and the outputs end with row M - 1, inside the last tile."""
     K = 192
+    rows = M + 5 if mapped else M
     nq = d if "q" in parts else 0
     nk = d if "k" in parts else 0
     nv = d if "v" in parts else 0
@@ -413,8 +416,8 @@ def test_gemm_qknorm_epilogue(torch, B, M, d, dh, parts):
     bias = rnd(3, "b", (N,), 0.5)
     qg = synth.round_bf16(1.0 + 0.3 * synth.gaussian(4, "qg", dh)).astype(np.float32)
     kg = synth.round_bf16(1.0 + 0.3 * synth.gaussian(5, "kg", dh)).astype(np.float32)
-    perm = np.random.default_rng(6).permutation(M + 5)[:M].astype(np.int32)       # scatter into M+5 rows
-    ang = synth.gaussian(7, "ang", (M + 5) * (dh // 2)).reshape(M + 5, dh // 2) * 2.0
+    perm = (np.random.default_rng(6).permutation(rows)[:M] if mapped else np.arange(M)).astype(np.int32)   # mapped: scatter into M+5 rows
+    ang = synth.gaussian(7, "ang", rows * (dh // 2)).reshape(rows, dh // 2) * 2.0
     rope = np.stack([np.cos(ang), np.sin(ang)], axis=-1).astype(np.float32)           # [rows][dh/2][2]
     qscale = np.float32(np.log2(np.e) / np.sqrt(dh))
     npad = (N + 255) // 256 * 256
@@ -423,10 +426,10 @@ def test_gemm_qknorm_epilogue(torch, B, M, d, dh, parts):
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
     db, dqg, dkg, drope, dperm = dev(bias), dev(qg), dev(kg), dev(rope), dev(perm)
     out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
-    qo = torch.full((M + 5, d), float("nan"), dtype=torch.bfloat16, device="cuda")
-    ko = torch.full((M + 5, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    qo = torch.full((rows, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ko = torch.full((rows, d), float("nan"), dtype=torch.bfloat16, device="cuda")
     st = B.dit_op_gemm_qknorm(None, dA.data_ptr(), K, dW.data_ptr(), K, db.data_ptr(), M, N, K, out.data_ptr(), N,
-                              nq, nk, dh, dqg.data_ptr(), dkg.data_ptr(), drope.data_ptr(), dperm.data_ptr(),
+                              nq, nk, dh, dqg.data_ptr(), dkg.data_ptr(), drope.data_ptr(), dperm.data_ptr() if mapped else None,
                               qo.data_ptr(), ko.data_ptr(), d, float(qscale))
     assert st == 0
     torch.cuda.synchronize()
@@ -455,7 +458,7 @@ def test_gemm_qknorm_epilogue(torch, B, M, d, dh, parts):
         got = bf16_to_np(out)[:, nq + nk:]
         w = prod[:, nq + nk:]
         assert np.isfinite(got).all() and (np.abs(got - w) / (np.abs(w) + 1.0)).max() <= 2.0 ** -8
-    untouched = np.setdiff1d(np.arange(M + 5), perm)
+    untouched = np.setdiff1d(np.arange(rows), perm)
     assert np.isnan(bf16_to_np(qo)[untouched]).all() and np.isnan(bf16_to_np(ko)[untouched]).all()
 
 

@@ -3,6 +3,7 @@ host logic (tensor table, size queries, argument validation) behaves.  No kernel
 import ctypes as C
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -27,6 +28,30 @@ def test_library_exports_every_declared_symbol(B):
     for name in declared:
         assert hasattr(B.lib, name), f"{name} declared in dit.h but not exported"
     assert declared == set(B.EXPORTS)
+
+
+def test_rows_of_the_last_tile_stay_inside_the_rotary_table(tmp_path):
+    """The row arithmetic of the q/k-norm epilogue, compiled for the host: whatever part of the last tile (256 or 320 rows)
+    a product of M rows fills, every row that a lane reads is one of the M, with and without a map."""
+    src, exe = tmp_path / "rows.cpp", tmp_path / "rows"
+    src.write_text('''
+#include "gemm_rows.h"
+#include <vector>
+int main() {
+  for (int tile : {256, 320})
+    for (int M : {1, 15, 16, 17, 255, 256, 257, 319, 320, 321, 4250}) {
+      std::vector<int> map(M);
+      for (int m = 0; m < M; ++m) map[m] = M - 1 - m;
+      for (int m = 0; m < (M + tile - 1) / tile * tile; ++m) {
+        const int c = m < M ? m : M - 1;
+        if (dit::dest_row(nullptr, m, M) != c || dit::dest_row(map.data(), m, M) != M - 1 - c) return 1;
+      }
+    }
+  return 0;
+}
+''')
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2510_02838_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)]).returncode == 0
 
 
 @pytest.mark.parametrize("name", list(synth.CONFIGS))
