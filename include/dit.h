@@ -262,6 +262,25 @@ dit_status dit_op_gemm_splitk_static(void* stream, const void* A, int lda, const
                                      void* out, int ldc, const float* gate, int gate_stride,
                                      const int* row_req, int splits);
 
+/* Further forms of the product, as the stages run them.  variant: 0 (the library's choice, which may split K if `work`
+ * holds the partial tiles), a tile of dit_op_gemm_variant, or a split one of dit_op_gemm_splitk_variant with `splits` and
+ * its scratch (twice that for the gated pair).  DIT_ESHAPE for a tile whose waves are not 64 columns wide
+ * where the epilogue needs it (gated pair, transposed; 30064128 and 30032128 give way to one that is).
+ *   two_term: (A + A_lo) W^T, both of one shape and stride; out_kind 1 or 3 of dit_op_gemm.
+ *   geglu: bf16 of tanh-GELU(A W_gate^T) * (A W_up^T), both weights [N_pad][ld] with the same ld.
+ *   transposed: bf16 of A W^T + bias, element (m, n) to out[n*ldo + col[m]]; col: dev int32 [M], rising; columns that no row maps
+ *   to are left alone. */
+dit_status dit_op_gemm_two_term(void* stream, const void* A, const void* A_lo, int lda, const void* W, int ldw,
+                                const float* bias, int M, int N, int K, int out_kind, void* out, int ldc,
+                                const float* gate, int gate_stride, const int* row_req,
+                                int variant, int splits, void* work, size_t work_bytes);
+dit_status dit_op_gemm_geglu(void* stream, const void* A, int lda, const void* W_gate, int ld_gate,
+                             const void* W_up, int ld_up, int M, int N, int K, void* out, int ldc,
+                             int variant, int splits, void* work, size_t work_bytes);
+dit_status dit_op_gemm_transposed(void* stream, const void* A, int lda, const void* W, int ldw, const float* bias,
+                                  int M, int N, int K, void* out, int ldo, const int* col,
+                                  int variant, int splits, void* work, size_t work_bytes);
+
 /* 3x3 convolution as the Decode stage runs it: `images` channels-last bf16 images with a one-pixel border each,
  * [(H+2)*(W+2)][cin] back to back (cin a multiple of 64, the border as it is stored); Wt: dev bf16 [cout_pad][ldw],
  * input index (3*ky + kx)*cin + c, cout_pad a multiple of 256 rows readable; bias dev float32 [cout] or NULL.

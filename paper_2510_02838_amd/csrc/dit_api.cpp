@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <iterator>
 #include <cstdlib>
 #include <map>
 #include <string>
@@ -1351,6 +1352,59 @@ dit_status dit_op_gemm_variant(void* stream, const void* A, int lda, const void*
   b.p[0] = mk((const bf16_t*)A, lda, (const bf16_t*)W, ldw, bias, M, N, K, out_kind, out, ldc);
   if (launch_gemm((hipStream_t)stream, b, variant) < 0) return DIT_ESHAPE;
   return hipGetLastError() == hipSuccess ? DIT_OK : DIT_EDEVICE;
+}
+
+// One launch of products with the library's choice of tile (0, split if `work` allows) or a forced variant.
+static dit_status launch_form(void* stream, GemmBatch& b, int variant, int splits, void* work, size_t work_bytes) {
+  static const int unsplit[] = {0, 128128, 10128128, 30128128, 30128064, 33128064, 30064128, 32064128, 30064064, 30032128, 256256, 1256256, 1320256,
+                                10256256, 11256256, 20256256, 21256256, 256128, 128256, 31256128, 32256128, 31128256};
+  if ((uintptr_t)work & 15) return DIT_ESHAPE;
+  if (variant == 40128128 || variant == 40064064 || variant == 40032128) {
+    if (!work) return DIT_EINVAL;
+    if (splits < 1 || splits > b.p[0].K / 64) return DIT_ESHAPE;
+    const int bm = variant / 1000 % 1000, bn = variant % 1000;
+    size_t tiles = 0;
+    for (int i = 0; i < b.n; ++i) tiles += (size_t)((b.p[i].M + bm - 1) / bm) * ((b.p[i].N + bn - 1) / bn);
+    if (work_bytes < tiles * splits * ((size_t)bm * bn * 4)) return DIT_ENOMEM;
+    b.splits = splits;
+  } else if (std::find(std::begin(unsplit), std::end(unsplit), variant) == std::end(unsplit)) {
+    return DIT_EINVAL;
+  }
+  b.partial = (float*)work; b.partial_bytes = work ? work_bytes : 0;
+  if (launch_gemm((hipStream_t)stream, b, variant) < 0) return DIT_ESHAPE;
+  return hipGetLastError() == hipSuccess ? DIT_OK : DIT_EDEVICE;
+}
+
+dit_status dit_op_gemm_two_term(void* stream, const void* A, const void* A_lo, int lda, const void* W, int ldw, const float* bias, int M,
+                                int N, int K, int out_kind, void* out, int ldc, const float* gate, int gate_stride, const int* row_req,
+                                int variant, int splits, void* work, size_t work_bytes) {
+  if (!A || !A_lo || !W || !out) return DIT_EINVAL;
+  if (M <= 0 || N <= 0 || K <= 0 || K % 64 || lda < K || ldw < K || ldc < N || lda % 8 || ldw % 8) return DIT_ESHAPE;
+  if (out_kind != OUT_F32 && out_kind != OUT_RESID_F32) return DIT_EINVAL;
+  if (ldc % 4 || ((uintptr_t)out & 15)) return DIT_ESHAPE;
+  GemmBatch b; b.n = 1; b.total_tiles = 0;
+  b.p[0] = with_lo(mk((const bf16_t*)A, lda, (const bf16_t*)W, ldw, bias, M, N, K, out_kind, out, ldc, gate, gate_stride, row_req), (const bf16_t*)A_lo);
+  return launch_form(stream, b, variant, splits, work, work_bytes);
+}
+
+dit_status dit_op_gemm_geglu(void* stream, const void* A, int lda, const void* W_gate, int ld_gate, const void* W_up, int ld_up, int M, int N,
+                             int K, void* out, int ldc, int variant, int splits, void* work, size_t work_bytes) {
+  if (!A || !W_gate || !W_up || !out) return DIT_EINVAL;
+  if (M <= 0 || N <= 0 || K <= 0 || K % 64 || lda < K || ld_gate < K || ld_up < K || ldc < N) return DIT_ESHAPE;
+  if (lda % 8 || ld_gate % 8 || ld_up % 8 || ldc % 8 || ((uintptr_t)out & 15)) return DIT_ESHAPE;
+  GemmBatch b; b.n = 2; b.total_tiles = 0; b.geglu = 1;
+  b.p[0] = mk((const bf16_t*)A, lda, (const bf16_t*)W_gate, ld_gate, nullptr, M, N, K, OUT_BF16, out, ldc);
+  b.p[1] = mk((const bf16_t*)A, lda, (const bf16_t*)W_up, ld_up, nullptr, M, N, K, OUT_BF16, out, ldc);
+  return launch_form(stream, b, variant, splits, work, work_bytes);
+}
+
+dit_status dit_op_gemm_transposed(void* stream, const void* A, int lda, const void* W, int ldw, const float* bias, int M, int N, int K,
+                                  void* out, int ldo, const int* col, int variant, int splits, void* work, size_t work_bytes) {
+  if (!A || !W || !out || !col) return DIT_EINVAL;
+  if (M <= 0 || N <= 0 || K <= 0 || K % 64 || lda < K || ldw < K || ldo < M || lda % 8 || ldw % 8 || ldo % 8 || ((uintptr_t)out & 15)) return DIT_ESHAPE;
+  GemmBatch b; b.n = 1; b.total_tiles = 0;
+  b.p[0] = with_vt(mk((const bf16_t*)A, lda, (const bf16_t*)W, ldw, bias, M, N, K, OUT_VT, nullptr, 0), (bf16_t*)out, ldo, col);
+  return launch_form(stream, b, variant, splits, work, work_bytes);
 }
 
 dit_status dit_op_conv3(void* stream, const void* img, int images, int H, int W, int cin, const void* Wt, int ldw,

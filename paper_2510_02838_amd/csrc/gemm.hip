@@ -1950,10 +1950,20 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
       return tile < 0 ? tile : launch_gemm(s, second, force_tile);
     }
   }
-  bool narrow = false;                  // epilogues that need waves of 64 columns (the split reduction has its own)
-  for (int i = 0; i < b.n; ++i) narrow = narrow || b.p[i].out_kind == OUT_VT;
-  if ((narrow || b.geglu) && tile == 30064128) tile = 32064128;
-  if ((narrow || b.geglu) && tile == 30032128) tile = 30128128;
+  bool narrow = b.geglu && tile < 40000000;      // epilogues that need waves of 64 columns (the split reduction has its own ...
+  bool conv = false, plain = false, qknorm = false;
+  for (int i = 0; i < b.n; ++i) {
+    conv = conv || b.p[i].conv_w > 0; plain = plain || b.p[i].conv_w <= 0;
+    qknorm = qknorm || b.p[i].out_kind == OUT_QKNORM;
+    narrow = narrow || (b.p[i].out_kind == OUT_VT && tile < 40000000);
+  }
+  if (narrow && tile == 30064128) tile = 32064128;
+  if (narrow && tile == 30032128) tile = 30128128;
+  // ... but none for the q/k norm)
+  if ((qknorm || narrow) && !(tile == 1256256 || tile == 1320256 || tile == 11256256 || tile == 21256256 || tile == 128128 || tile == 10128128 ||
+                              tile == 30128128 || tile == 30128064 || tile == 32064128 || tile == 30064064 || tile == 33128064 || tile == 256128 ||
+                              tile == 31256128 || tile == 32256128))
+    return -1;
   if (b.geglu && tile < 40000000) {     // unsplit: one problem whose tiles hold both products of their columns
     if (b.n != 2 || b.p[0].A != b.p[1].A || b.p[0].M != b.p[1].M || b.p[0].N != b.p[1].N || b.p[0].ldw != b.p[1].ldw) return -1;
     b.p[0].W2 = b.p[1].W;
@@ -1961,15 +1971,6 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
     b.p[0].out_kind = OUT_GEGLU;
     b.n = 1;
   }
-  bool conv = false, plain = false, qknorm = false;
-  for (int i = 0; i < b.n; ++i) {
-    conv = conv || b.p[i].conv_w > 0; plain = plain || b.p[i].conv_w <= 0;
-    qknorm = qknorm || b.p[i].out_kind == OUT_QKNORM;
-  }
-  // the q/k-norm epilogue exists only in the instantiations whose waves own 64 output columns
-  if (qknorm && !(tile == 1256256 || tile == 1320256 || tile == 11256256 || tile == 21256256 || tile == 128128 || tile == 10128128 ||
-                  tile == 30128128 || tile == 30128064 || tile == 32064128 || tile == 30064064 || tile == 33128064 || tile == 256128 || tile == 31256128 || tile == 32256128))
-    return -1;
   if (qknorm && (tile == 30128064 || tile == 33128064 || tile == 30064064))      // 64 columns per workgroup: heads of 64 only
     for (int i = 0; i < b.n; ++i)
       if (b.p[i].out_kind == OUT_QKNORM && b.p[i].qk.head_dim > 64) return -1;

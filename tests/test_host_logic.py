@@ -168,6 +168,27 @@ def test_calls_fail_cleanly_without_buffers(B):
     m.close()
 
 
+@pytest.mark.parametrize("variant", [256256, 10256256, 20256256, 128256, 31128256])
+def test_products_refuse_tiles_that_have_not_their_epilogue(B, variant):
+    """The gated pair and the transposed form need waves of 64 columns: a tile without is refused before anything is
+    launched (its epilogue would write nothing), as for the q/k norm.  (Addresses are never dereferenced.)"""
+    assert B.dit_op_gemm_geglu(None, 256, 64, 256, 64, 256, 64, 300, 300, 64, 256, 304, variant, 0, None, 0) == 2
+    assert B.dit_op_gemm_transposed(None, 256, 64, 256, 64, None, 300, 300, 64, 256, 304, 256, variant, 0, None, 0) == 2
+
+
+def test_products_in_further_forms_check_their_arguments(B):
+    geglu = lambda ld=64, up=64, ldc=304, variant=128128, splits=0, work=None, n=0: B.dit_op_gemm_geglu(
+        None, 256, 64, 256, ld, 256, up, 300, 300, 64, 256, ldc, variant, splits, work, n)
+    assert geglu(up=128) == 2 and geglu(ldc=300) == 2 and geglu(variant=5) == 1 and geglu(variant=40128128, splits=1) == 1
+    # twice three by three tiles of 64 KB
+    assert geglu(variant=40128128, splits=1, work=256, n=18 * 65536 - 1) == 3
+    two = lambda kind=1, lo=256, variant=128128, splits=0, work=None, n=0: B.dit_op_gemm_two_term(
+        None, 256, lo, 64, 256, 64, None, 300, 300, 64, kind, 256, 300, None, 0, None, variant, splits, work, n)
+    assert two(kind=0) == 1 and two(kind=2) == 1 and two(lo=None) == 1 and two(variant=40064064, splits=2, work=256, n=1 << 30) == 2
+    tr = lambda ldo=304, col=256: B.dit_op_gemm_transposed(None, 256, 64, 256, 64, None, 300, 300, 64, 256, ldo, col, 128128, 0, None, 0)
+    assert tr(ldo=296) == 2 and tr(ldo=300) == 2 and tr(col=None) == 1
+
+
 def test_profiler_tool_host_logic():
     """The offline profiler's CPU-side pieces: the paper's 20 % batching rule (Appendix "Impact of
     Batch Size"), request-spec parsing, token counts and the decoder's product flop count."""
