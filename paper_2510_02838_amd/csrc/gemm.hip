@@ -1950,6 +1950,9 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
       return tile < 0 ? tile : launch_gemm(s, second, force_tile);
     }
   }
+  // a gated pair: two problems of one A and one shape, nothing but the product
+  if (b.geglu && (b.n != 2 || b.p[0].A != b.p[1].A || b.p[0].lda != b.p[1].lda || b.p[0].M != b.p[1].M || b.p[0].N != b.p[1].N ||
+                  b.p[0].K != b.p[1].K || b.p[0].ldw != b.p[1].ldw || b.p[0].bias || b.p[1].bias)) return -1;
   bool narrow = b.geglu && tile < 40000000;      // epilogues that need waves of 64 columns (the split reduction has its own ...
   bool conv = false, plain = false, qknorm = false;
   for (int i = 0; i < b.n; ++i) {
@@ -1965,7 +1968,6 @@ int launch_gemm(hipStream_t s, GemmBatch& b, int force_tile) {
                               tile == 31256128 || tile == 32256128))
     return -1;
   if (b.geglu && tile < 40000000) {     // unsplit: one problem whose tiles hold both products of their columns
-    if (b.n != 2 || b.p[0].A != b.p[1].A || b.p[0].M != b.p[1].M || b.p[0].N != b.p[1].N || b.p[0].ldw != b.p[1].ldw) return -1;
     b.p[0].W2 = b.p[1].W;
     b.p[0].N *= 2;
     b.p[0].out_kind = OUT_GEGLU;

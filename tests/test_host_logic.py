@@ -179,7 +179,9 @@ def test_products_refuse_tiles_that_have_not_their_epilogue(B, variant):
 def test_products_in_further_forms_check_their_arguments(B):
     geglu = lambda ld=64, up=64, ldc=304, variant=128128, splits=0, work=None, n=0: B.dit_op_gemm_geglu(
         None, 256, 64, 256, ld, 256, up, 300, 300, 64, 256, ldc, variant, splits, work, n)
-    assert geglu(up=128) == 2 and geglu(ldc=300) == 2 and geglu(variant=5) == 1 and geglu(variant=40128128, splits=1) == 1
+    # weights of different strides: unsplit, and split, where the reduction takes both for one tile grid
+    assert geglu(up=128) == 2 and geglu(up=128, variant=40128128, splits=1, work=256, n=1 << 30) == 2
+    assert geglu(ldc=300) == 2 and geglu(variant=5) == 1 and geglu(variant=40128128, splits=1) == 1
     # twice three by three tiles of 64 KB
     assert geglu(variant=40128128, splits=1, work=256, n=18 * 65536 - 1) == 3
     two = lambda kind=1, lo=256, variant=128128, splits=0, work=None, n=0: B.dit_op_gemm_two_term(
