@@ -42,6 +42,7 @@ struct dec_ctx {
   std::map<std::string, DTap> taps;
   std::vector<int> host_map;
   hipEvent_t map_done = nullptr;
+  bool launch_refused = false;     // a product of the running call was outside the GEMM's limits
 };
 
 namespace {
@@ -224,7 +225,9 @@ struct Fwd {
       b.p[b.n++] = p;
     }
     if (may_split) { b.partial = at<float>(L.partial); b.partial_bytes = PARTIAL_BYTES; }
-    return launch_gemm(s, b);
+    const int tile = launch_gemm(s, b);
+    if (tile < 0) c->launch_refused = true;           // reported by the call
+    return tile;
   }
   // 3x3 convolution of the bordered bf16 image `img` (H x W, cin_pad channels) into fp32 rows
   // (a video's stack starts with two zero frames: `img` is the stack, frame() its first real image)
@@ -237,7 +240,7 @@ struct Fwd {
     if (want) p.stats = at<float>(L.gnp);
     // (a split product leaves sums per 32 rows of whole 128-row tiles, plan() sizes the scratch for 64: only where they fit)
     const int tile = gemm({p}, !want || ((size_t)p.M + 127) / 128 * 4 * p.N * 8 <= L.gnp_bytes);
-    if (want) {
+    if (want && tile >= 0) {
       const int rows = gemm_stats_rows(tile);
       // chunks per image: one per wave row of a tile (a lone image may end inside a tile; with
       // several, H*W is a multiple of every chunk height)
@@ -443,6 +446,7 @@ dit_status dec_forward(dec_ctx* c, int n, int h, int w, const float* latent, flo
                  "1..%d images or output frames with fewer than 2^29 pixels together", n, h, w, GN_MAX_BATCH);
   const dec_config& g = c->cfg;
   DHIP(c, hipSetDevice(c->device));
+  c->launch_refused = false;
   Layout L;
   plan(c, n, h, w, L);
   if (L.total > c->ws_bytes) return dfail(c, DIT_ENOMEM, "workspace has %zu bytes, this call needs %zu", c->ws_bytes, L.total);
@@ -534,6 +538,7 @@ dit_status dec_forward(dec_ctx* c, int n, int h, int w, const float* latent, flo
       launch_compact_rows(s, F.at<float>(L.out4), 4, image, (long long)F.B * H * W, g.out_ch);
     }
   }
+  if (c->launch_refused) return dfail(c, DIT_ESHAPE, "a matrix product of this call is outside the GEMM kernels' limits");
   DHIP(c, hipGetLastError());
   return DIT_OK;
 }

@@ -990,7 +990,7 @@ dit_status run_sample(dit_ctx* c, int n_req, const dit_req* reqs, float* latents
     }
   }
   HIPCHK(c, hipGetLastError());
-  if (c->launch_refused) return fail(c, DIT_ESHAPE, "a matrix product of this call exceeds the GEMM kernels' 4 GiB operand limit");
+  if (c->launch_refused) return fail(c, DIT_ESHAPE, "a matrix product of this call is outside the GEMM kernels' limits");
   return DIT_OK;
 }
 

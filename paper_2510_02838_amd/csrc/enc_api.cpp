@@ -41,6 +41,7 @@ struct enc_ctx {
   std::map<std::string, ETap> taps;
   std::vector<unsigned char> host_meta;        // kept alive until the upload has been consumed
   hipEvent_t meta_done = nullptr;
+  bool launch_refused = false;     // a product of the running call was outside the GEMM's limits
 };
 
 namespace {
@@ -170,7 +171,7 @@ void gemm(enc_ctx* c, float* partial, std::initializer_list<GemmProblem> ps, boo
   b.n = 0; b.total_tiles = 0; b.geglu = geglu;
   for (const GemmProblem& p : ps) b.p[b.n++] = p;
   b.partial = partial; b.partial_bytes = PARTIAL_BYTES;
-  launch_gemm(c->stream, b);
+  if (launch_gemm(c->stream, b) < 0) c->launch_refused = true;     // reported by the call
 }
 
 dit_status tap(enc_ctx* c, const std::string& name, const void* src, size_t bytes) {
@@ -330,6 +331,7 @@ dit_status enc_forward(enc_ctx* c, int n_seq, const int* lens, const int* tokens
   if (!lens_ok(n_seq, lens)) return efail(c, DIT_ESHAPE, "1..4096 sequences of 1..%d tokens, at most 2^20 tokens", (int)ENC_MAX_LEN);
   const enc_config& g = c->cfg;
   EHIP(c, hipSetDevice(c->device));
+  c->launch_refused = false;
   // the previous call's host image must have been consumed before it is rebuilt
   if (c->meta_done) EHIP(c, hipEventSynchronize(c->meta_done));
   else EHIP(c, hipEventCreateWithFlags(&c->meta_done, hipEventDisableTiming));
@@ -386,6 +388,7 @@ dit_status enc_forward(enc_ctx* c, int n_seq, const int* lens, const int* tokens
     ETAP(p + ".x_out", x, (size_t)M * d * 4);
   }
   launch_rmsnorm(s, x, Wv(c, "final.g"), (bf16_t*)out_bf16, out_f32, M, d);
+  if (c->launch_refused) return efail(c, DIT_ESHAPE, "a matrix product of this call is outside the GEMM kernels' limits");
   EHIP(c, hipGetLastError());
   return DIT_OK;
 }

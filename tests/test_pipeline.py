@@ -95,3 +95,52 @@ def test_video_diffuse_decode_chain_against_the_oracle_chain():
     assert got.shape == video_ref.shape == (5, 64, 64, 3) and np.isfinite(got).all()
     assert rel_l2(got, video_ref) <= 8e-2, rel_l2(got, video_ref)
     dec.close()
+
+
+@pytest.mark.gpu
+def test_every_stage_reports_a_refused_product(tmp_path):
+    """The products' launcher refuses what its kernels cannot do, which no configuration that the stages accept asks for.
+    A child process puts a launcher that refuses everything before the library's own: each stage then has to fail
+    its call instead of returning what its buffers happened to hold."""
+    import os
+    import subprocess
+    import sys
+    src, so = tmp_path / "refuse.cpp", tmp_path / "librefuse.so"
+    src.write_text("struct ihipStream_t;\nnamespace dit { struct GemmBatch; int launch_gemm(ihipStream_t*, GemmBatch&, int) { return -1; } }\n")
+    subprocess.run(["g++", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+    child = tmp_path / "child.py"
+    child.write_text(f'''
+import ctypes
+import numpy as np
+import torch                                             # (brings the HIP runtime that the library binds to)
+ctypes.CDLL({str(so)!r}, mode=ctypes.RTLD_GLOBAL)
+import synth
+from paper_2510_02838_amd import binding as B, decoder as XD, encoder as XE
+torch.cuda.set_device(0)
+def status(f):
+    try:
+        f()
+    except B.DitError as e:
+        return e.status
+    return 0
+enc = XE.Encoder(synth.ENCODERS["t5_tiny"]); enc.ensure_workspace([9]); enc.workspace.zero_(); enc.init_weights(1, 0.05)
+out = torch.empty((9, synth.ENCODERS["t5_tiny"]["d_model"]), dtype=torch.float32, device="cuda")
+got = [status(lambda: enc.forward([9], torch.zeros(9, dtype=torch.int32, device="cuda"), None, out))]
+arch = dict(latent_ch=4, out_ch=3, channels=(128, 64), n_res=1)
+dec = XD.Decoder(arch); dec.ensure_workspace(8, 8); dec.workspace.zero_(); dec.init_weights(1, 0.05)
+img = torch.empty((16, 16, 3), dtype=torch.float32, device="cuda")
+got.append(status(lambda: dec.forward(8, 8, torch.zeros(4 * 64, device="cuda"), img)))
+cfg = synth.CONFIGS["tiny"]
+reqs, a = synth.make_requests("tiny"), cfg["arch"]
+dit = B.DiT(a); dit.ensure_workspace(reqs, 1); dit.workspace.zero_(); dit.init_weights(1, 0.05)
+_, h, w, n = reqs[0]
+x, c = torch.zeros(a["latent_ch"] * h * w, device="cuda"), torch.zeros((n, a["cond_dim"]), dtype=torch.bfloat16, device="cuda")
+one = np.ones(1, np.float32)
+got.append(status(lambda: dit.denoise_step(reqs, x, c, one, one * 0.5, 0, torch.empty_like(x))))
+torch.cuda.synchronize()
+print(got)
+assert got == [2, 2, 2], got
+''')
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, str(child)], env=dict(os.environ, PYTHONPATH=root), cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
