@@ -364,12 +364,17 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
 #pragma unroll
     for (int c = 0; c < VEC; ++c) bv[c] = (P.bias && n + c < P.N) ? P.bias[n + c] : 0.f;
     // convolutions with fp32 output: per-column sums and sums of squares of the values stored,
-    // over this wave's rows (the statistics pass of the group norm that follows)
+    // over this wave's rows (the statistics pass of the group norm that follows).  Rows 8 apart are added one after the other,
+    // then the eight sums in pairs: the order of gemm8_kernel, so that an image's statistics do not move with the tile.
     constexpr bool STATS = CONV && F32OUT;
-    float cs[STATS ? VEC : 1], cq[STATS ? VEC : 1];
+    constexpr int CLS = STATS ? 8 / RPI : 1;     // rows of this lane modulo 8
+    static_assert(!STATS || RPI == 4, "two classes of rows a lane");
+    float cs[CLS][STATS ? VEC : 1], cq[CLS][STATS ? VEC : 1];
     if constexpr (STATS) {
 #pragma unroll
-      for (int c = 0; c < VEC; ++c) { cs[c] = 0.f; cq[c] = 0.f; }
+      for (int k = 0; k < CLS; ++k)
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) { cs[k][c] = 0.f; cq[k][c] = 0.f; }
     }
     // Gated residual: the loads of an output row (request index -> gate vector, and the residual itself)
     // depend on each other and may not be moved across the stores by the compiler, so they are issued
@@ -437,7 +442,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
             *(f32x4*)xp = x4;
             if constexpr (STATS) {
 #pragma unroll
-              for (int c = 0; c < 4; ++c) { cs[c] += x4[c]; cq[c] += x4[c] * x4[c]; }
+              for (int c = 0; c < 4; ++c) { cs[it % CLS][c] += x4[c]; cq[it % CLS][c] += x4[c] * x4[c]; }
             }
           } else {
             // (ragged last columns: the request index is read here, rq[] may already hold the next patch's)
@@ -445,7 +450,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
             for (int c = 0; c < VEC && n + c < P.N; ++c) {
               const float r = xp[c] + (gp ? gp[c] : 1.f) * v[c];
               xp[c] = r;
-              if constexpr (STATS) { cs[c] += r; cq[c] += r * r; }
+              if constexpr (STATS) { cs[it % CLS][c] += r; cq[it % CLS][c] += r * r; }
             }
           }
         } else if constexpr (KIND == OUT_F32) {
@@ -458,7 +463,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
           }
           if constexpr (STATS) {
 #pragma unroll
-            for (int c = 0; c < VEC; ++c) { cs[c] += v[c]; cq[c] += v[c] * v[c]; }   // (columns past N are not written out)
+            for (int c = 0; c < VEC; ++c) { cs[it % CLS][c] += v[c]; cq[it % CLS][c] += v[c] * v[c]; }   // (columns past N are not written out)
           }
         } else {
           if constexpr (KIND == OUT_GELU_BF16) {
@@ -483,10 +488,12 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
 #pragma unroll
         for (int c = 0; c < VEC; ++c)
 #pragma unroll
-          for (int o = LPR; o < 64; o <<= 1) { cs[c] += __shfl_xor(cs[c], o); cq[c] += __shfl_xor(cq[c], o); }
+          for (int o = LPR; o < 64; o <<= 1)
+#pragma unroll
+            for (int k = 0; k < CLS; ++k) { cs[k][c] += __shfl_xor(cs[k][c], o); cq[k][c] += __shfl_xor(cq[k][c], o); }
         if (lr == 0) {
           float* sp = P.stats + ((size_t)(tm * WM + wm) * P.N + n) * 2;
-          for (int c = 0; c < VEC && n + c < P.N; ++c) { sp[2 * c] = cs[c]; sp[2 * c + 1] = cq[c]; }
+          for (int c = 0; c < VEC && n + c < P.N; ++c) { sp[2 * c] = cs[0][c] + cs[CLS - 1][c]; sp[2 * c + 1] = cq[0][c] + cq[CLS - 1][c]; }
         }
       }
     }

@@ -227,6 +227,29 @@ def test_convolution_and_its_column_sums(torch, B, images, H, W, cin, cout, vari
         assert ((tail == 0) | np.isnan(tail)).all()        # a tile's rows past the last: nothing, or zeros
 
 
+@pytest.mark.parametrize("images,H,W,cin,cout", [(1, 16, 16, 64, 128), (1, 24, 56, 64, 130), (3, 16, 32, 128, 64), (1, 9, 7, 64, 40)])
+def test_convolution_tiles_leave_the_same_column_sums(torch, B, images, H, W, cin, cout):
+    """The tiles whose sums cover 64 rows add them in one order, so that the group norm that follows does not move with the
+    tile that the number of images or frames picks: sums, sums of squares and results bit for bit."""
+    x = rnd(66, "x", (images, H + 2, W + 2, cin))
+    Wp = np.zeros(((cout + 255) // 256 * 256, 9 * cin), np.float32); Wp[:cout] = rnd(67, "W", (cout, 9 * cin), 0.05)
+    dx, dW, db = to_dev_bf16(torch, x), to_dev_bf16(torch, Wp), torch.from_numpy(rnd(68, "b", (cout,), 0.5)).cuda()
+    M, ldc, n_chunks = images * H * W, (cout + 3) // 4 * 4, (images * H * W + 255) // 256 * 8
+    x0 = torch.from_numpy(synth.gaussian(69, "r", M * ldc).astype(np.float32).reshape(M, ldc)).cuda()
+    for kind in (1, 3):
+        got = []
+        for variant in (128128, 30128128, 32256128):
+            sums, out, rows = torch.zeros((n_chunks, cout, 2), dtype=torch.float32, device="cuda"), x0.clone(), C.c_int(0)
+            assert B.dit_op_conv3(None, dx.data_ptr(), images, H, W, cin, dW.data_ptr(), 9 * cin, db.data_ptr(), cout, kind, out.data_ptr(), ldc,
+                                  sums.data_ptr(), n_chunks * cout * 8, variant, 0, None, 0, C.byref(rows)) == 0
+            torch.cuda.synchronize()
+            assert rows.value == 64
+            got.append((sums, out))
+        for sums, out in got[1:]:
+            assert torch.equal(out, got[0][1])
+            assert torch.equal(sums, got[0][0]), (kind, int((sums != got[0][0]).sum()))
+
+
 def test_gemm_seeded_random_shapes(torch, B):
     """Sixty seeded shapes (M 1..900, N 1..900, K a multiple of 64 up to 2048), each with a seeded
     output kind (bf16, fp32, GELU, or the gated residual with 1-5 requests whose rows change
