@@ -156,16 +156,18 @@ void plan(const dec_ctx* c, int n, int h, int w, Layout& L) {
   // the largest stream / image / intermediate over the levels
   // (n streams / bordered images back to back; a video's frame count grows on the way and its stacks of
   // bordered images start with two zero frames)
-  size_t max_x = 0, max_img = 0;
+  size_t max_x = 0, max_img = 0, max_norm = 0;
   int H = h, W = w;
   int prev = g.channels[0];
   size_t F = n;
   const size_t pad = g.temporal ? 2 : 0;
   max_x = std::max(max_x, F * H * W * prev);
+  auto norm = [&](int ch) { max_norm = std::max(max_norm, group_norm_partial_bytes((long long)H * W, ch, (int)F)); };
   max_img = std::max(max_img, (F + pad) * (H + 2) * (W + 2) * std::max(prev, 64));
   for (int l = 0; l < g.n_levels; ++l) {
     const int ch = g.channels[l];
     max_x = std::max(max_x, F * H * W * std::max(ch, prev));
+    norm(std::max(ch, prev));
     max_img = std::max(max_img, (F + pad) * (H + 2) * (W + 2) * std::max(ch, prev));
     prev = ch;
     if (l != g.n_levels - 1) {
@@ -187,10 +189,11 @@ void plan(const dec_ctx* c, int n, int h, int w, Layout& L) {
   L.vt = take(rup(C0, 256) * rup(L.P0, 64) * 2);            // read as a second operand: rows up to a multiple of 256
   L.sc = take((size_t)L.P0 * L.P0 * 4);
   L.pm = take((size_t)L.P0 * rup(L.P0, 64) * 2);
-  // channel sums per chunk of 64 pixels, the smallest wave height of an unsplit product's tile.  A split product leaves
-  // them per 32 pixels: in decoders of several levels they fit beside the final image's chunks; where they do not (a
-  // single wide level beyond 256 pixels) conv3() leaves the product unsplit, and the workspace keeps its size.
-  L.gnp_bytes = std::max(group_norm_partial_bytes((long long)L.n_out * L.Hf * L.Wf, 1024), max_x / 64 * 8 + 2 * 1024 * 8);
+  // Channel sums: those that an unsplit product leaves per 64 pixels (the smallest wave height of its tiles), which also
+  // hold those of the norm's own pass (max_norm).  A split product leaves them per 32 pixels: in decoders of several levels they fit
+  // in a 1024-channel share per 256 pixels of the final image; where they do not (a single wide level beyond 256
+  // pixels) conv3() leaves the product unsplit, and the workspace keeps its size.
+  L.gnp_bytes = std::max(std::max(max_x / 64 * 8 + 2 * 1024 * 8, max_norm), ((size_t)L.n_out * L.Hf * L.Wf + 255) / 256 * 1024 * 8);
   L.gnp = take(L.gnp_bytes);
   L.gst = take(GN_STATS_BYTES);
   L.out4 = take((size_t)L.n_out * L.Hf * L.Wf * 4 * 4);

@@ -46,10 +46,13 @@ void launch_latent_to_image(hipStream_t s, const float* z, bf16_t* out, int C, i
 }
 
 // ---- group norm ---------------------------------------------------------------------------
-// pass 1: per chunk of `chunk` pixels (GN_CHUNK, fewer in small images), per channel: sum and sum of squares.  A thread owns 4
+// pass 1: per chunk of `chunk` pixels (gn_chunk), per channel: sum and sum of squares.  A thread owns 4
 // consecutive channels and strides over the chunk's pixels; threads that share channels combine
 // through LDS in a fixed order.  partial: [chunks][C][2].  C is a power of two in 64..1024.
-constexpr int GN_CHUNK = 256;
+// Pixels of a chunk.  Small images take 64 pixels a workgroup, as many partial sums as a convolution leaves (1024 pixels
+// on 4 workgroups took 15 us).  The rule looks at one image alone: an image's sums, and a video's first frames, do not move with
+// how many there are.
+static int gn_chunk(long long P) { return P < 65536 ? 64 : 256; }
 __global__ __launch_bounds__(256) void gn_partial_kernel(const float* __restrict__ x, float* __restrict__ partial,
                                                          long long P, int C, int qsh, int chunk) {
   extern __shared__ float red[];                // [pix_par][C][2]
@@ -222,7 +225,7 @@ __global__ __launch_bounds__(256) void gn_apply_kernel(const float* __restrict__
 // B images of H x W; statistics per image and group.  ready_chunks > 0: `partial` already holds
 // that many per-chunk channel sums PER IMAGE (written by the epilogue of the convolution that
 // produced x; chunks do not straddle images): pass 1 is skipped.  With B > 1 the standalone
-// pass 1 needs H*W to be a multiple of its chunk (256 pixels).
+// pass 1 needs H*W to be a multiple of its chunk (64 or 256 pixels).
 void launch_group_norm(hipStream_t s, const float* x, const float* gamma, const float* beta, bf16_t* out,
                        float* partial, float2* stats, int H, int W, int C, int groups, int silu, int pad,
                        int ready_chunks, int B, bf16_t* raw) {
@@ -234,8 +237,7 @@ void launch_group_norm(hipStream_t s, const float* x, const float* gamma, const 
   int gsh = 0;
   while ((groups << gsh) < C) ++gsh;             // channels per group = 1 << gsh
   if (chunks <= 0) {
-    // (small images: 64 pixels a workgroup, as many partial sums as a convolution leaves; 1024 pixels on 4 workgroups took 15 us)
-    const int chunk = P * B < 65536 ? 64 : GN_CHUNK;
+    const int chunk = gn_chunk(P);
     chunks = (int)((P + chunk - 1) / chunk);
     const int pix_par = 256 >> (csh - 2);
     hipLaunchKernelGGL(gn_partial_kernel, dim3(chunks * B), dim3(256), (size_t)pix_par * C * 2 * sizeof(float), s, x, partial, P * B, C, csh - 2, chunk);
@@ -249,8 +251,9 @@ void launch_group_norm(hipStream_t s, const float* x, const float* gamma, const 
   const int units = ((W + 3) >> 2) * (C >> 3);
   hipLaunchKernelGGL(gn_apply_kernel, dim3((units + 255) / 256, H, B), dim3(256), 0, s, x, stats, gamma, beta, out, W, C, csh - 3, gsh, silu, pad, groups, raw);
 }
-size_t group_norm_partial_bytes(long long pixels, int C) {
-  return (size_t)((pixels + GN_CHUNK - 1) / GN_CHUNK) * C * 2 * sizeof(float);
+size_t group_norm_partial_bytes(long long pixels, int C, int B) {
+  const int chunk = gn_chunk(pixels);
+  return (size_t)((pixels + chunk - 1) / chunk) * B * C * 2 * sizeof(float);
 }
 
 // nearest 2x upsampling of the fp32 stream into a bf16 bordered image: out pixel (y, x) = in (y/2, x/2).

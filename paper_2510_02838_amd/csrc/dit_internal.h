@@ -200,9 +200,9 @@ void launch_rel_bias_table(hipStream_t s, const float* table, float* bias, int H
 void launch_latent_to_image(hipStream_t s, const float* z, bf16_t* out, int C, int H, int W, int Cpad, int B = 1, int frames = 0);
 // GroupNorm (eps 1e-6, affine) of the fp32 stream x [H*W][C], optional SiLU, bf16 output with
 // (pad=1) or without a one-pixel border.  C in {64,128,256,512,1024}; partial: scratch of
-// group_norm_partial_bytes; stats: scratch of GN_STATS_BYTES (groups <= 32).  ready_chunks > 0: partial already holds
+// group_norm_partial_bytes (of B images of H*W pixels); stats: scratch of GN_STATS_BYTES (groups <= 32).  ready_chunks > 0: partial already holds
 // [ready_chunks][C][2] channel sums of x (GemmProblem::stats) and the statistics pass is skipped.
-size_t group_norm_partial_bytes(long long pixels, int C);
+size_t group_norm_partial_bytes(long long pixels, int C, int B);
 constexpr int GN_MAX_BATCH = 128;
 constexpr size_t GN_STATS_HEAD = (size_t)GN_MAX_BATCH * 32 * 8;                       // [B][groups] float2
 constexpr size_t GN_STATS_BYTES = GN_STATS_HEAD + (size_t)GN_MAX_BATCH * 32 * 16 * 16;   // + [B][groups][shares] double2

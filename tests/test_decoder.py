@@ -299,6 +299,26 @@ def test_decoder_batch_of_same_size_latents(torch, X):
 
 
 @pytest.mark.gpu
+def test_decoder_image_does_not_move_with_the_size_of_its_batch(torch, X):
+    """63 and 64 latents of 32 x 32, on either side of 65536 pixels in all and of the first full round of a convolution's
+    tiles: an image's statistics are its own, so it keeps its bits."""
+    arch = dict(latent_ch=4, out_ch=3, channels=(128,), n_res=1)
+    m = X.Decoder(arch)
+    m.ensure_workspace(32, 32, 64)
+    m.init_weights(3, 0.03)
+    z = torch.from_numpy(np.stack([_latent(arch, 32, 32, seed=30 + i) for i in range(64)])).cuda()
+    img = []
+    for n in (63, 64):
+        out = torch.full((n, 32, 32, 3), float("nan"), dtype=torch.float32, device="cuda")
+        m.forward(32, 32, z[:n].contiguous(), out, n=n)
+        torch.cuda.synchronize()
+        img.append(out)
+    assert bool(torch.isfinite(img[1]).all()) and float(img[1].std()) > 0
+    assert torch.equal(img[0], img[1][:63])
+    m.close()
+
+
+@pytest.mark.gpu
 def test_decoder_smaller_call_after_a_larger_one_is_unaffected(torch, X):
     """The workspace is reused with other image sizes: zero borders and padded channels must not
     carry over.  Same context, large then small latent, against a fresh context."""
