@@ -546,22 +546,17 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
             *(float*)(stg + acc_row(e) * RS + (j * 32 + acc_col) * 4) = acc[i][j][e];
         int drows[4];
         f32x4 rc0[4], rc1[4];
-        constexpr int RG = TM * TN >= 10 ? 1 : 4;     // (the 320-row tile has no registers to spare: row by row there;
-                                                      //  2 or 4 rows at a time spill and measured slower)
-        auto load_rope = [&](int first) {
-#pragma unroll
-          for (int it = first; it < first + RG; ++it) {
-            const int m = m0 + wm * (BM / WM) + i * 32 + it * RPI + lr;
-            rc0[it] = f32x4{1.f, 0.f, 1.f, 0.f}; rc1[it] = f32x4{1.f, 0.f, 1.f, 0.f};      // (cos, sin) pairs
-            if (Q.rope && m < P.M) {
-              const f32x4* rp = (const f32x4*)(Q.rope + (size_t)drows[it] * (Q.head_dim / 2) + (hc >> 1));
-              rc0[it] = rp[0]; rc1[it] = rp[1];
-            }
-          }
-        };
 #pragma unroll
         for (int it = 0; it < 4; ++it) drows[it] = dnext[it];
-        load_rope(0);
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const int m = m0 + wm * (BM / WM) + i * 32 + it * RPI + lr;
+          rc0[it] = f32x4{1.f, 0.f, 1.f, 0.f}; rc1[it] = f32x4{1.f, 0.f, 1.f, 0.f};      // (cos, sin) pairs
+          if (Q.rope && m < P.M) {
+            const f32x4* rp = (const f32x4*)(Q.rope + (size_t)drows[it] * (Q.head_dim / 2) + (hc >> 1));
+            rc0[it] = rp[0]; rc1[it] = rp[1];
+          }
+        }
         if (i + 1 < TM) load_drows(i + 1);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         float v[4][VEC], ss[4];
@@ -591,7 +586,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
         }
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-          if (RG < 4 && it > 0 && it % RG == 0) load_rope(it);
           const int m = m0 + wm * (BM / WM) + i * 32 + it * RPI + lr;
           if (m >= P.M) continue;
           const float r = rsqrtf(ss[it] * inv_dh + 1e-6f) * osc;
@@ -1742,8 +1736,9 @@ static void launch_t(hipStream_t s, GemmBatch& b) {
     // The norm that follows as well, from 96 workgroups of four rows on and up to 1536 columns: there it takes 2 % off a step (eight
     // blocks of 1536 columns: 410 rows 1122 -> 1101 us, 700 rows 1209 -> 1184, 1178 rows 1542 -> 1513).  Below that too few
     // workgroups read the partial sums (80 rows 817 -> 826 us, 272 rows 974 -> 976), and with 3072 columns a workgroup
-    // reads twice as many (256 rows 1278 -> 1295 us, 640 rows 1633 -> 1632).
-    bool ln = !b.geglu && b.n <= 2;
+    // reads twice as many (256 rows 1278 -> 1295 us, 640 rows 1633 -> 1632).  (The smaller tiles serve problems of at most 128
+    // rows, two of which are 64 workgroups.)
+    bool ln = BM == 128 && !b.geglu && b.n <= 2;
     int rows = 0;
     for (int i = 0; i < b.n; ++i) {
       ln = ln && b.p[i].ln_y && b.p[i].out_kind == OUT_RESID_F32 && b.p[i].N <= 1536;
@@ -1751,8 +1746,9 @@ static void launch_t(hipStream_t s, GemmBatch& b) {
     }
     ln = ln && rows >= 96;
     b.ln_done = ln;
-    if (ln) hipLaunchKernelGGL((splitk_reduce_ln_kernel<BM, BN, WM, WN>), dim3(rows), dim3(512), 0, s, b);
-    else hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, WM, WN>), dim3((b.geglu ? total / 2 : total) * (BM * BN / 1024)), dim3(256), 0, s, b);
+    if constexpr (BM == 128)
+      if (ln) hipLaunchKernelGGL((splitk_reduce_ln_kernel<BM, BN, WM, WN>), dim3(rows), dim3(512), 0, s, b);
+    if (!ln) hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, WM, WN>), dim3((b.geglu ? total / 2 : total) * (BM * BN / 1024)), dim3(256), 0, s, b);
   } else {
     hipLaunchKernelGGL(kern, dim3(total), dim3(WM * WN * 64), lds, s, b);
   }
