@@ -184,7 +184,7 @@ def test_encoder_intermediates_and_batch_independence(torch, X):
 def test_encoder_benchmark_widths_over_the_tiles(torch, X, lens):
     """One layer of the benchmark widths, from the split tiles for few rows to the 8-wave tiles, with prompts of odd length
     (the transposed values of a product's rows then start anywhere, break inside a tile and leave pad columns between
-    the prompts): prompts of up to 130 tokens against the oracle."""
+    the prompts): every prompt against the oracle."""
     arch = dict(synth.ENCODERS["t5_xxl"], n_layers=1, vocab=1024)
     m = X.Encoder(arch)
     m.ensure_workspace(lens)
@@ -199,9 +199,8 @@ def test_encoder_benchmark_widths_over_the_tiles(torch, X, lens):
     got, ora, at = out.cpu().numpy(), E.EncoderOracle(arch, params), 0
     assert np.isfinite(got).all()
     for n, t in zip(lens, toks):
-        if n <= 130:
-            ref = ora.forward(t)
-            assert rel_l2(got[at:at + n], ref) <= 1e-2, (n, rel_l2(got[at:at + n], ref))
+        ref = ora.forward(t)
+        assert rel_l2(got[at:at + n], ref) <= 1e-2, (n, rel_l2(got[at:at + n], ref))
         at += n
     m.close()
 

@@ -67,7 +67,7 @@ def test_set_get_tensor_round_trip(torch, B):
 
 # ---------------------------------------------------------------------------------- GEMM
 @pytest.mark.parametrize("M,N,K", [(300, 384, 256), (1, 256, 64), (517, 1000, 192), (4250, 1536, 1536)])
-@pytest.mark.parametrize("variant", [0, 128128, 10128128, 30128128, 30128064, 33128064, 30064128, 30064064, 30032128, 256256, 1256256, 1320256, 10256256, 11256256, 20256256, 21256256,
+@pytest.mark.parametrize("variant", [0, 128128, 10128128, 30128128, 30128064, 33128064, 30064128, 32064128, 30064064, 30032128, 256256, 1256256, 1320256, 10256256, 11256256, 20256256, 21256256,
                                      256128, 128256, 31256128, 32256128, 31128256])
 def test_gemm_against_float64_matmul(torch, B, M, N, K, variant):
     if M > 1000 and variant not in (0, 1256256, 1320256, 11256256, 128128, 32256128):
@@ -166,6 +166,120 @@ def test_gemm_gated_residual_on_the_large_tiles(torch, B, M, N, tile, per_reques
     assert bool(((out.double() - (x0.double() + g * prod)).abs() <= bound).all())
 
 
+FORM_VARIANTS = [128128, 30128128, 30128064, 30064128, 32064128, 30064064, 30032128, 1256256, 1320256, 32256128, 40128128, 40064064, 40032128]
+
+
+def form_operands(torch, M, N, K, seed):
+    """A [M][K] and W [N padded to 256][K] as bf16, and both as float64."""
+    A = to_dev_bf16(torch, rnd(seed, "A", (M, K)))
+    W = torch.zeros(((N + 255) // 256 * 256, K), dtype=torch.bfloat16, device="cuda")
+    W[:N] = to_dev_bf16(torch, rnd(seed + 1, "W", (N, K), 0.05))
+    return A, W, A.double(), W[:N].double()
+
+
+def form_scratch(torch, variant, M, N, splits, problems=1):
+    """Scratch of exactly the partial tiles, NaN-filled (None for an unsplit tile)."""
+    if variant < 40000000:
+        return None, 0
+    bm, bn = variant // 1000 % 1000, variant % 1000
+    n = problems * -(-M // bm) * -(-N // bn) * splits * bm * bn * 4
+    return torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda"), n
+
+
+# remainders in every direction; one slab; more tiles than workgroups on the 8-wave tiles; few rows
+FORM_SHAPES = [(300, 384, 256), (517, 1000, 192), (33, 130, 448), (4200, 4200, 64), (4250, 2100, 192)]
+
+
+@pytest.mark.parametrize("M,N,K", FORM_SHAPES)
+@pytest.mark.parametrize("variant", FORM_VARIANTS)
+def test_gemm_second_term_of_the_left_operand(torch, B, variant, M, N, K):
+    """(A + A_lo) W^T in one launch (two on the 8-wave tiles), plain and as a gated residual whose requests change in every
+    tile, against float64.  A_lo is a quarter of A here, where the models have 2^-9 of it: left out, or taken from the
+    wrong slab or row, it shows.  Bound: a chain of n float32 additions errs by at most n 2^-24 of the sum of absolute products."""
+    A, W, Ad, Wd = form_operands(torch, M, N, K, 81)
+    L = to_dev_bf16(torch, rnd(83, "lo", (M, K), 0.25))
+    Ld = L.double()
+    bias = torch.from_numpy(rnd(84, "b", (N,), 0.5)).cuda()
+    req = (torch.arange(M, dtype=torch.int32) // 97).cuda()
+    gate = torch.from_numpy(rnd(85, "g", ((M + 96) // 97, N))).cuda()
+    prod, mag = (Ad + Ld) @ Wd.T + bias.double(), (Ad.abs() + Ld.abs()) @ Wd.T.abs() + bias.double().abs()
+    splits = min(3, K // 64)
+    work, nbytes = form_scratch(torch, variant, M, N, splits)
+    ldc = (N + 3) // 4 * 4
+    x0 = torch.from_numpy(rnd(86, "x", (M, ldc))).cuda()
+    for kind in (1, 3):
+        out = x0.clone()
+        assert B.dit_op_gemm_two_term(None, A.data_ptr(), L.data_ptr(), K, W.data_ptr(), K, bias.data_ptr(), M, N, K, kind, out.data_ptr(), ldc,
+                                      gate.data_ptr() if kind == 3 else None, N, req.data_ptr() if kind == 3 else None, variant, splits,
+                                      work.data_ptr() if work is not None else None, nbytes) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(out[:, N:], x0[:, N:])
+        want, bound = prod, (2 * K + 3) * 2.0 ** -24 * mag
+        if kind == 3:
+            g = gate.double()[req.long()]
+            want = x0[:, :N].double() + g * prod
+            bound = (2 * K + 5) * 2.0 ** -24 * (x0[:, :N].double().abs() + g.abs() * mag)
+        worst = ((out[:, :N].double() - want).abs() / bound).max()
+        assert float(worst) <= 1, (kind, float(worst))
+
+
+@pytest.mark.parametrize("M,N,K", FORM_SHAPES)
+@pytest.mark.parametrize("variant", FORM_VARIANTS)
+def test_gemm_gated_pair(torch, B, variant, M, N, K):
+    """tanh-GELU(A W_gate^T) * (A W_up^T) as one launch whose tiles hold both, or as a split product whose reduction
+    does, against float64.  Bound: the float32 sums' (slope of the GELU at most 1.13), GELU and product by the hardware's exponential and
+    reciprocal (8 roundings), and the rounding to bf16."""
+    A, Wg, Ad, Gd = form_operands(torch, M, N, K, 91)
+    _, Wu, _, Ud = form_operands(torch, M, N, K, 93)
+    Wu, Ud = Wu * 4, Ud * 4
+    splits = min(3, K // 64)
+    work, nbytes = form_scratch(torch, variant, M, N, splits, 2)
+    ldc = (N + 7) // 8 * 8
+    out = torch.full((M, ldc), 7.0, dtype=torch.bfloat16, device="cuda")
+    assert B.dit_op_gemm_geglu(None, A.data_ptr(), K, Wg.data_ptr(), K, Wu.data_ptr(), K, M, N, K, out.data_ptr(), ldc, variant, splits,
+                               work.data_ptr() if work is not None else None, nbytes) == 0
+    torch.cuda.synchronize()
+    assert bool((out[:, N:] == 7).all())
+    g, u = Ad @ Gd.T, Ad @ Ud.T
+    eg, eu = K * 2.0 ** -24 * (Ad.abs() @ Gd.T.abs()), K * 2.0 ** -24 * (Ad.abs() @ Ud.T.abs())
+    act = 0.5 * g * (1 + torch.tanh(math.sqrt(2 / math.pi) * (g + 0.044715 * g ** 3)))
+    want = act * u
+    bound = 1.13 * eg * (u.abs() + eu) + act.abs() * eu + (2.0 ** -8 + 8 * 2.0 ** -24) * want.abs() + 8 * 2.0 ** -24 * (g * u).abs()
+    # (where g is far below 0 the GELU and its float32 form are both next to 0)
+    worst = ((out[:, :N].double() - want).abs() / (bound + 2.0 ** -120)).max()
+    assert float(worst) <= 1, float(worst)
+
+
+@pytest.mark.parametrize("M,N,K", FORM_SHAPES)
+@pytest.mark.parametrize("variant", FORM_VARIANTS)
+@pytest.mark.parametrize("lens", [[10 ** 6], [31, 64, 1, 200], [32, 3], [160, 96]])
+def test_gemm_transposed_result(torch, B, variant, M, N, K, lens):
+    """A product that leaves transposed, its rows in segments padded to 64 columns: one segment, odd ones (which break
+    inside a lane's 4 and 8 rows, a unit's 32, at odd and even columns) and aligned ones, against float64; the columns
+    between the segments keep what they had."""
+    A, W, Ad, Wd = form_operands(torch, M, N, K, 101)
+    bias = torch.from_numpy(rnd(103, "b", (N,), 0.5)).cuda()
+    col, at, i, m = np.empty(M, np.int32), 0, 0, 0
+    while m < M:
+        n = min(lens[i % len(lens)], M - m)
+        col[m:m + n] = at + np.arange(n)
+        at, m, i = at + -(-n // 64) * 64, m + n, i + 1
+    dcol = torch.from_numpy(col).cuda()
+    splits = min(3, K // 64)
+    work, nbytes = form_scratch(torch, variant, M, N, splits)
+    out = torch.full((N, at), 7.0, dtype=torch.bfloat16, device="cuda")
+    assert B.dit_op_gemm_transposed(None, A.data_ptr(), K, W.data_ptr(), K, bias.data_ptr(), M, N, K, out.data_ptr(), at, dcol.data_ptr(), variant,
+                                    splits, work.data_ptr() if work is not None else None, nbytes) == 0
+    torch.cuda.synchronize()
+    want, mag = (Ad @ Wd.T + bias.double()).T, (Ad.abs() @ Wd.T.abs() + bias.double().abs()).T
+    bound = (2.0 ** -8) * want.abs() + 1.01 * (K + 1) * 2.0 ** -24 * mag
+    worst = ((out[:, dcol.long()].double() - want).abs() / bound).max()
+    assert float(worst) <= 1, float(worst)
+    free = torch.ones(at, dtype=torch.bool, device="cuda")
+    free[dcol.long()] = False
+    assert bool((out[:, free] == 7).all())
+
+
 @pytest.mark.parametrize("M,N,K", [(321, 264, 64), (65, 256, 512), (700, 130, 4608)])
 def test_gemm_tiles_agree_bit_for_bit(torch, B, M, N, K):
     """Every tile adds a product's terms in the same order, also where it multiplies with 16x16x32 MFMAs instead of
@@ -176,7 +290,7 @@ def test_gemm_tiles_agree_bit_for_bit(torch, B, M, N, K):
     Wp = np.zeros(((N + 255) // 256 * 256, K), np.float32); Wp[:N] = W
     dA, dW = to_dev_bf16(torch, A), to_dev_bf16(torch, Wp)
     ldc, first = (N + 3) // 4 * 4, None
-    for variant in (128128, 30128128, 30128064, 30064128, 30064064, 30032128, 1256256, 1320256, 32256128):
+    for variant in (128128, 30128128, 30128064, 30064128, 32064128, 30064064, 30032128, 1256256, 1320256, 32256128):
         out = torch.zeros((M, ldc), dtype=torch.float32, device="cuda")
         assert B.dit_op_gemm_variant(None, dA.data_ptr(), K, dW.data_ptr(), K, None, M, N, K, 1, out.data_ptr(), ldc, variant) == 0
         torch.cuda.synchronize()
