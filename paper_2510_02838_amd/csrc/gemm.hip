@@ -781,8 +781,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(const GemmBatch batc
 // with a workgroup per tile and the results turned as fp32 in 4-byte LDS stores, is a quarter of the time at K = 1536.
 // Now 8 to 8.5 us, of which tanh-GELU is 3.6 and the stores 3 (each measured by leaving it out).  Before and after:
 // 18384 x 6144 x 1536 with GELU 303 -> 292 us, 18384 x 4608 x 1536 226 -> 216, 18384 x 1536 x 6144 into the residual
-// 307 -> 297, 32760 x 5120 x 5120 1400 -> 1363, 8192^3 722 -> 709; 3x3 convolutions of a million pixels with 128
-// channels 449 -> 426.  The 320-row tile has no registers to hold the next tile's offsets and starts each tile anew.
+// 307 -> 297, 32760 x 5120 x 5120 into the residual 1400 -> 1363 (as bf16 1177), 8192^3 722 -> 709; 3x3 convolutions of a million
+// pixels with 128 channels 449 -> 426.  Counters at 8192^3: matrix cores busy in 90 % of the cycles at 1.57 GHz, no bank conflicts but
+// the epilogue's.  The 320-row tile has no registers to hold the next tile's offsets and starts each tile anew.
 // Tried: two workgroups of 4 waves a CU with 256x128 tiles, to let one's epilogue run under the other's loop (8192^3 at
 // 1088 TFLOP/s); starts staggered over the CUs so that their stores do not collide (as much lost as gained);
 // non-temporal stores (0.4 % at 32760 tokens, nothing elsewhere).
@@ -1719,7 +1720,10 @@ static void launch8_t(hipStream_t s, GemmBatch& b) {
   static std::atomic<unsigned> seen{0};
   if (first_use_on_device(seen))
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  hipLaunchKernelGGL(kern, dim3(total < 256 ? total : 256), dim3(512), lds, s, b);    // one workgroup per CU
+  // One workgroup per CU.  Its tiles are fixed: beside other streams a workgroup whose CU is held starts late, and its tiles with it (a
+  // stage in a stream beside small calls of another: 0.82 to 0.98 of the time of one after the other, with a workgroup per tile
+  // 0.83 to 0.96; no pair of stages takes longer than it did).
+  hipLaunchKernelGGL(kern, dim3(total < 256 ? total : 256), dim3(512), lds, s, b);
 }
 
 template <int BM, int BN, int WM, int WN, int BKT, int NS, int MODE = 0, bool CONV = false>
@@ -1811,7 +1815,7 @@ static int small_m_tile(GemmBatch& b) {
 
 int choose_tile(GemmBatch& b, int force_tile) {
   // Tile choice.  The 256x256 tile (8 waves) halves the L2->LDS traffic per flop of the 128x128
-  // tile and takes 0.71 to 0.74 of its time where rounds are full (8192^3 709 against 964 us,
+  // tile and takes 0.71 to 0.74 of its time where rounds are full (bf16 results, 8192^3 709 against 964 us,
   // 32760 x 5120 x 5120 1177 against 1605), but one workgroup fills a CU, so its grid runs
   // in rounds of 256 tiles: use it from one full round on, unless the last round would hold only
   // a few tiles (a partly filled last round runs faster than a full one, lone tiles see less
