@@ -252,7 +252,7 @@ def main():
         "config": {"workload": head["workload"], "steps_per_sample": K, "finite": head["finite"]},
         # traffic: fabric-side bytes per launch need a rocprofv3 counter run (FETCH_SIZE / WRITE_SIZE); this
         # process cannot read them, so the figure lives in profiles/ with the command that produced it
-        "roofline": {"bound": "mfma", "kernel": "gemm_kernel (bf16 MFMA GEMM, all launches of the step)",
+        "roofline": {"bound": "mfma", "kernel": "gemm8_kernel and gemm_kernel (bf16 MFMA GEMM, all launches of the step)",
                      "achieved": mf["gemm_tflops"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": mf["gemm_frac_peak"], "traffic": None,
                      "algorithmic_bytes_per_launch": gl["algorithmic_bytes_per_launch"],
