@@ -45,7 +45,7 @@ struct QkNorm {
 struct GemmProblem {
   const bf16_t* A; int lda;     // [M][lda] activations
   const bf16_t* W; int ldw;     // [N_pad][ldw] weights, out-major
-  const bf16_t* A2 = nullptr;   // optional second term of A, same shape: (A + A2) W^T, all of A first (no convolutions)
+  const bf16_t* A2 = nullptr;   // optional second term of A, same shape: (A + A2) W^T, A2's sum first (no convolutions)
   const bf16_t* W2 = nullptr;   // OUT_GEGLU: the second matrix, same shape; N counts the columns of both
   const float* bias;            // [N] or null
   int M, N, K;

@@ -223,6 +223,35 @@ def test_gemm_second_term_of_the_left_operand(torch, B, variant, M, N, K):
         assert float(worst) <= 1, (kind, float(worst))
 
 
+@pytest.mark.parametrize("M,N,K", [(512, 384, 64), (56, 1536, 1536), (300, 264, 5120)])
+@pytest.mark.parametrize("variant", [128128, 30128064, 32256128, 40128128, 40064064])
+def test_gemm_second_term_costs_no_precision(torch, B, variant, M, N, K):
+    """A float32 operand as two bf16 terms, as the models' first and last products take it: the root mean square of the error against
+    float64 is that of two products added one after the other (the same tile and shares; all unsplit tiles add alike), with 5 %
+    for chance: the errors of some ten thousand results scatter by about 1 %."""
+    x = torch.from_numpy(synth.gaussian(87, "x", M * K).astype(np.float32).reshape(M, K)).cuda()
+    A = x.to(torch.bfloat16)
+    L = (x - A.float()).to(torch.bfloat16)
+    _, W, _, Wd = form_operands(torch, 1, N, K, 88)
+    ref = (A.double() + L.double()) @ Wd.T
+    splits = min(6, K // 64)
+    work, nbytes = form_scratch(torch, variant, M, N, splits)
+    wp = work.data_ptr() if work is not None else None
+    one, two = torch.empty((M, N), dtype=torch.float32, device="cuda"), torch.empty((M, N), dtype=torch.float32, device="cuda")
+    assert B.dit_op_gemm_two_term(None, A.data_ptr(), L.data_ptr(), K, W.data_ptr(), K, None, M, N, K, 1, one.data_ptr(), N, None, 0, None,
+                                  variant, splits, wp, nbytes) == 0
+    for term, kind in ((A, 1), (L, 3)):
+        if variant > 40000000:
+            assert B.dit_op_gemm_splitk_variant(None, term.data_ptr(), K, W.data_ptr(), K, None, M, N, K, kind, two.data_ptr(), N, None, 0, None,
+                                                splits, wp, nbytes, variant) == 0
+        else:
+            assert B.dit_op_gemm(None, term.data_ptr(), K, W.data_ptr(), K, None, M, N, K, kind, two.data_ptr(), N, None, 0, None) == 0
+    torch.cuda.synchronize()
+    e1, e2 = float((one.double() - ref).norm()), float((two.double() - ref).norm())
+    print("rel error: one launch %.2e, two products %.2e" % (e1 / float(ref.norm()), e2 / float(ref.norm())))
+    assert e1 <= 1.05 * e2, e1 / e2
+
+
 @pytest.mark.parametrize("M,N,K", FORM_SHAPES)
 @pytest.mark.parametrize("variant", FORM_VARIANTS)
 def test_gemm_gated_pair(torch, B, variant, M, N, K):
