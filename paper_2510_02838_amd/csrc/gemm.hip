@@ -1484,23 +1484,35 @@ __global__ __launch_bounds__(512) void gemm8_kernel(const GemmBatch) {
   wait_vm<0, true>();                        // drain the redundant tail loads before LDS is released
 }
 
+// N shares, STRIDE floats apart, fetched together and added in their order.
+template <int N, int STRIDE>
+__device__ __forceinline__ void add_shares(f32x4& acc, const float* pc) {
+  f32x4 t[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) t[u] = *(const f32x4*)(pc + (size_t)u * STRIDE);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < N; ++u)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] += t[u][c];
+}
 // The shares of one float4 of a split product, STRIDE floats apart, added in their order.  Eight loads are in flight and none
 // waits alone behind them: with four, and the rest one by one, 16 shares cost six memory latencies, with eight two (32 tokens
-// through the encoder 2985 -> 2962 us).
+// through the encoder 2985 -> 2962 us).  The last ones have a branch for their number: a condition for each load costs
+// more than it saves at few shares (see splitk_reduce_kernel).
 template <int STRIDE>
 __device__ __forceinline__ f32x4 sum_shares(const float* pc, int splits) {
   f32x4 acc = *(const f32x4*)pc;
-  for (int s = 1; s < splits; s += 8) {
-    f32x4 t[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (s + u < splits) t[u] = *(const f32x4*)(pc + (size_t)(s + u) * STRIDE);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (s + u < splits) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[c] += t[u][c];
-      }
+  int left = splits - 1;
+  for (pc += STRIDE; left >= 8; left -= 8, pc += 8 * STRIDE) add_shares<8, STRIDE>(acc, pc);
+  switch (left) {
+    case 7: add_shares<7, STRIDE>(acc, pc); break;
+    case 6: add_shares<6, STRIDE>(acc, pc); break;
+    case 5: add_shares<5, STRIDE>(acc, pc); break;
+    case 4: add_shares<4, STRIDE>(acc, pc); break;
+    case 3: add_shares<3, STRIDE>(acc, pc); break;
+    case 2: add_shares<2, STRIDE>(acc, pc); break;
+    case 1: add_shares<1, STRIDE>(acc, pc); break;
   }
   return acc;
 }
@@ -1509,9 +1521,11 @@ __device__ __forceinline__ f32x4 sum_shares(const float* pc, int splits) {
 // result does not depend on which workgroup finished first) and applies the epilogue.  One
 // thread per float4 of the chunk layout written above: 4 consecutive rows of one column, the
 // 32 lanes of a half-wave on 32 consecutive columns.
-//   A gated pair's reduction covers the tiles of the gate and adds up both; OUT_VT: 4 rows of a column are 4 neighbours
-// of a row of the transposed matrix.
-template <int BM, int BN, int WM, int WN>
+//   GEGLU: a gated pair's reduction covers the tiles of the gate and adds up both; VT: some problem is OUT_VT, where 4 rows
+// of a column are 4 neighbours of a row of the transposed matrix.  Both have instantiations of their own: in one kernel for all, with a
+// condition for each share, 6 and 7 shares of 235 rows took 7.75 us, 2 shares of 515 rows 9.6; now 7.35 and 9.4 (before
+// these forms were here 7.25 and 9.15).
+template <int BM, int BN, int WM, int WN, bool GEGLU, bool VT>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmBatch batch) {
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   constexpr int QPT = BM * BN / 4;                 // float4s per tile
@@ -1532,12 +1546,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmBatch batc
     return sum_shares<BM * BN>(pc, batch.splits);
   };
   f32x4 acc = sum(tile);
-  if (batch.geglu) {
+  if constexpr (GEGLU) {
     const f32x4 up = sum(tile + batch.p[1].tile_start);
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[c] = gelu_tanh(acc[c]) * up[c];
   }
-  if (P.out_kind == OUT_VT) {
+  if (VT && P.out_kind == OUT_VT) {
     if (n >= P.N) return;
     const float bias = P.bias ? P.bias[n] : 0.f;
     bf16_t* dst = P.qk.vt + (size_t)n * P.qk.ldvt;
@@ -1754,7 +1768,12 @@ static void launch_t(hipStream_t s, GemmBatch& b) {
     b.ln_done = ln;
     if constexpr (BM == 128)
       if (ln) hipLaunchKernelGGL((splitk_reduce_ln_kernel<BM, BN, WM, WN>), dim3(rows), dim3(512), 0, s, b);
-    if (!ln) hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, WM, WN>), dim3((b.geglu ? total / 2 : total) * (BM * BN / 1024)), dim3(256), 0, s, b);
+    bool vt = false;
+    for (int i = 0; i < b.n; ++i) vt = vt || b.p[i].out_kind == OUT_VT;
+    const dim3 grid((b.geglu ? total / 2 : total) * (BM * BN / 1024));
+    if (b.geglu) hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, WM, WN, true, false>), grid, dim3(256), 0, s, b);
+    else if (vt) hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, WM, WN, false, true>), grid, dim3(256), 0, s, b);
+    else if (!ln) hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, WM, WN, false, false>), grid, dim3(256), 0, s, b);
   } else {
     hipLaunchKernelGGL(kern, dim3(total), dim3(WM * WN * 64), lds, s, b);
   }
